@@ -508,8 +508,8 @@ QK_API qk_status qk_render_ibr_check(int32_t V, const qk_camera *in_cams, const 
  *              float32 or NULL, with the view's grid
  * Workspace, in the context (grown on demand like the others): up to 128
  * layers, one 4-byte record (the layer-pixel's index) per layer-pixel-view
- * whose footprint meets the view (at most V L H W words) plus 3 counters per
- * tile of 32 x th view pixels (th = 16 for L <= 4, halved as L doubles);
+ * whose footprint meets the view (at most V L H W words) plus 5 counters per
+ * tile of 32 x th view pixels (th = 8 for L = 4, halved as L doubles);
  * beyond, the projected planes, sum over views of L Hm Wm 4 floats.
  * Errors (nothing enqueued): QK_EINVAL (NULL or misaligned buffer, bad
  * camera), QK_ESHAPE (non-positive dims, V out of range), QK_EUNSUPPORTED

@@ -1335,8 +1335,8 @@ qk_status qk_render_to_views(qk_context *ctx, void *hip_stream, int32_t V,
     hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
     qk::ViewsParams p;
     std::memset(&p, 0, sizeof(p));
-    // The binned form holds all layers of a tile in 64 KiB of LDS (tiles of
-    // 32 x th pixels, 32 bytes per pixel and layer: th = 16 for L <= 4,
+    // The binned form holds all layers of a tile in 32 KiB of LDS (tiles of
+    // 32 x th pixels, 32 bytes per pixel and layer: th = 8 for L <= 4,
     // halved as L doubles) and indexes records and view coordinates in 32
     // and 16 bits; other calls take the planes form.
     const int64_t nrec = (int64_t)V * ldm->L * ldm->H * ldm->W;
@@ -1348,7 +1348,7 @@ qk_status qk_render_to_views(qk_context *ctx, void *hip_stream, int32_t V,
     if (p.binned) {
         p.tw = 32;
         p.th = 32;
-        while (p.th > 1 && (int64_t)ldm->L * p.th * p.tw * 32 > 65536) p.th /= 2;
+        while (p.th > 1 && (int64_t)ldm->L * p.th * p.tw * 32 > 32768) p.th /= 2;
         int32_t tiles = 0;
         for (int m = 0; m < V; ++m) {
             p.ntx[m] = (views[m].W + p.tw - 1) / p.tw;
@@ -1358,20 +1358,22 @@ qk_status qk_render_to_views(qk_context *ctx, void *hip_stream, int32_t V,
         }
         p.tbase[V] = tiles;
         p.nbins = 4 * tiles;
-        // count [nbins], start [nbins + 1, padded to nbins + 4], cursor
-        // [nbins], then the records (one 32-bit layer-pixel index each);
-        // nbins is a multiple of 4, so every array starts on a 16-byte
-        // boundary
-        rec_off = (size_t)3 * p.nbins + 4;
+        // cursor [nbins], the records' total (padded to 4), start [nbins /
+        // 4, padded to 4], then the records (one 32-bit layer-pixel index
+        // each); every array starts on a 16-byte boundary
+        rec_off = (size_t)p.nbins + 4 + (((size_t)tiles + 3) & ~(size_t)3);
         ws_floats = rec_off + (size_t)nrec;
     }
     st = grow(ctx, &ctx->vws, &ctx->vws_elems, ws_floats, stream);
     if (st != QK_OK) return st;
     if (p.binned) {
         uint32_t *u = reinterpret_cast<uint32_t *>(ctx->vws);
-        p.count = u;
-        p.start = u + p.nbins;
-        p.cursor = u + 2 * (size_t)p.nbins + 4;
+        p.cursor = u;
+        p.total = u + p.nbins;
+        p.start = u + p.nbins + 4;
+        p.div_hw = qk::make_fast_div((uint32_t)(ldm->H * ldm->W));
+        p.div_w = qk::make_fast_div((uint32_t)ldm->W);
+        while ((1 << p.log2_th) < p.th) ++p.log2_th;
         p.rec = reinterpret_cast<int32_t *>(ctx->vws + rec_off);
     }
     int64_t base = 0, maxpix = 0;

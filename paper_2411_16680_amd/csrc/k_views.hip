@@ -21,6 +21,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "uf_params.h"
 
@@ -144,10 +145,10 @@ __global__ void __launch_bounds__(256) k_views_composite(const ViewsParams p) {
 // Binned form.
 //
 //   k_vbin_zero    clears the bin counts
-//   k_vbin_count   a workgroup takes 1024 layer-pixels of one view: their
-//                  records' bins, counted in an LDS hash table, then one
-//                  global add per distinct bin
-//   k_vbin_scan    one workgroup: exclusive prefix sums of the counts, the
+//   k_vbin_count   a workgroup takes up to 8192 layer-pixels of one view:
+//                  their records' bins, counted in an LDS hash table, then
+//                  one global add per distinct bin
+//   k_vbin_scan    each tile's run of records; its bins' counts become their
 //                  write cursors
 //   k_vbin_write   the same records; per distinct bin of the workgroup one
 //                  global add on the bin's cursor reserves a run of slots,
@@ -173,10 +174,12 @@ __global__ void __launch_bounds__(256) k_views_composite(const ViewsParams p) {
 // once and read by at most four workgroups.
 // ---------------------------------------------------------------------------
 
-constexpr int kVbKpt = 4;                       // records per thread
-constexpr int kVbChunk = 256 * kVbKpt;          // records per workgroup
+constexpr int kVbThreads = 512;                 // counting and writing workgroups
 constexpr int kVbHashBits = 11;
-constexpr int kVbHash = 1 << kVbHashBits;       // LDS hash slots, > kVbChunk keys
+constexpr int kVbHash = 1 << kVbHashBits;       // LDS hash slots
+constexpr int kVbProbes = 16;                   // a key that finds no slot goes to global memory
+constexpr int kVbLog2Tw = 5;                    // tiles are 32 view pixels wide
+constexpr int kVbTileThreads = 512;
 constexpr float kVbFix = 4294967296.0f;         // fixed-point scale of the tile sums, 2^32
 constexpr float kVbUnfix = 2.3283064365386963e-10f;   // 2^-32
 
@@ -188,21 +191,28 @@ __device__ inline double recip_d(double x) {
     return fma(r, fma(-x, r, 1.0), r);
 }
 
-// The record of layer-pixel q in view m: its bin, or -1 when no tap lies in
+// The footprint of layer-pixel q in view m: its layer, the view pixel
+// (ix, iy) of its top left tap and the fractions; false when no tap lies in
 // the view.  The reprojection of k_splat (reciprocals as above); a sample
 // with fxc <= -1 or fxc >= vW (likewise y) has no tap inside.  Every binned
 // pass calls it: the tile pass recomputes a record's footprint from the
-// layer-pixel index the write pass stored.
+// layer-pixel index the write pass stored.  All three passes are bound by
+// VALU instructions, so the index divisions are multiplications.
 // (The binned form runs only while V L H W < 2^31, so a layer-pixel index
 // and its divisions fit 32 bits.)
-__device__ inline int vbin_record(const ViewsParams &p, int m, int q, float &fx, float &fy,
-                                  int &ix, int &iy, int &l) {
-    const uint32_t hw = (uint32_t)p.H * (uint32_t)p.W, uq = (uint32_t)q;
-    l = (int)(uq / hw);
-    const uint32_t r = uq - (uint32_t)l * hw;
-    const int y = (int)(r / (uint32_t)p.W), x = (int)(r - (uint32_t)y * (uint32_t)p.W);
+__device__ inline uint32_t fast_div(uint32_t n, const FastDiv &f) {
+    const uint32_t q = __umulhi(n, f.mul) >> f.shift;
+    return f.d == 1u ? n : q;
+}
+
+__device__ inline bool vbin_footprint(const ViewsParams &p, int m, int q, float depth, float &fx,
+                                      float &fy, int &ix, int &iy, int &l) {
+    const uint32_t uq = (uint32_t)q, ul = fast_div(uq, p.div_hw);
+    const uint32_t r = uq - ul * p.div_hw.d, uy = fast_div(r, p.div_w);
+    l = (int)ul;
+    const int y = (int)uy, x = (int)(r - uy * p.div_w.d);
     const double u = (double)x + 0.5, v = (double)y + 0.5;
-    const double invd = recip_d((double)p.depth[q]);
+    const double invd = recip_d((double)depth);
     const double *A = p.cam[m];
     const int vw = p.vW[m], vh = p.vH[m];
     const double pz = fma(A[6], u, fma(A[7], v, fma(A[11], invd, A[8])));
@@ -210,249 +220,293 @@ __device__ inline int vbin_record(const ViewsParams &p, int m, int q, float &fx,
     const double qy = fma(A[3], u, fma(A[4], v, fma(A[10], invd, A[5])));
     const double rz = recip_d(pz);
     const double fxc = qx * rz - 0.5, fyc = qy * rz - 0.5;
-    if (!((pz > 1e-6) && (fxc > -1.0) && (fxc < (double)vw) && (fyc > -1.0) && (fyc < (double)vh)))
-        return -1;
+    const bool ok = (pz > 1e-6) && (fxc > -1.0) && (fxc < (double)vw) && (fyc > -1.0) &&
+                    (fyc < (double)vh);
     const double xf = floor(fxc), yf = floor(fyc);
     fx = (float)(fxc - xf);
     fy = (float)(fyc - yf);
-    ix = (int)xf;
-    iy = (int)yf;
-    const int tx = min((ix + 1) / p.tw, p.ntx[m] - 1), ty = min((iy + 1) / p.th, p.nty[m] - 1);
-    const int cls = (ix == tx * p.tw - 1 ? 1 : 0) | (iy == ty * p.th - 1 ? 2 : 0);
+    ix = ok ? (int)xf : 0;
+    iy = ok ? (int)yf : 0;
+    return ok;
+}
+
+// The bin of a footprint (the tile sides are powers of two).
+__device__ inline int vbin_bin(const ViewsParams &p, int m, int ix, int iy) {
+    const int tx = min((ix + 1) >> kVbLog2Tw, p.ntx[m] - 1);
+    const int ty = min((iy + 1) >> p.log2_th, p.nty[m] - 1);
+    const int cls = (ix == (tx << kVbLog2Tw) - 1 ? 1 : 0) | (iy == (ty << p.log2_th) - 1 ? 2 : 0);
     return 4 * (p.tbase[m] + ty * p.ntx[m] + tx) + cls;
 }
 
-// Slot of key b in the workgroup's hash table (linear probing).  At most
-// kVbChunk distinct keys go into kVbHash > kVbChunk slots, so a free or
-// matching slot is always found within kVbHash probes.
+// Slot of key b in the workgroup's hash table (linear probing), or -1 when
+// its first kVbProbes slots hold other keys: such a record is counted (and
+// later placed) by a global add of its own.  A chunk is up to 8192
+// neighbouring layer-pixels of one view, whose bins lie in a band of tiles.
 __device__ inline int vbin_slot(int *hkey, int b) {
     int h = (int)(((uint32_t)b * 2654435761u) >> (32 - kVbHashBits));
-    for (int probe = 0; probe < kVbHash; ++probe) {
+    for (int probe = 0; probe < kVbProbes; ++probe) {
         const int old = atomicCAS(&hkey[h], -1, b);
         if (old == -1 || old == b) return h;
         h = (h + 1) & (kVbHash - 1);
     }
-    return -1;                                   // not reached
+    return -1;
+}
+
+// XCD-aware order: workgroups are dispatched round-robin over the 8 XCDs;
+// workgroup i takes item (i % 8) * per + i / 8, so each XCD walks one
+// contiguous range.
+__device__ inline int xcd_order(int i, int n) {
+    const int xcd = i & 7, loc = i >> 3, q8 = n >> 3, rem = n & 7;
+    return (xcd < rem) ? xcd * (q8 + 1) + loc : rem * (q8 + 1) + (xcd - rem) * q8 + loc;
+}
+
+// The workgroup's view and first layer-pixel, views slowest.  The chunks in
+// flight together add to the same bins' counters; dispatched round-robin,
+// each XCD's share of them is spread over a whole layer.  (In an XCD-aware
+// order, or with the views fastest, an XCD's chunks fall on a few counter
+// lines and both passes take 1.8 times as long.)
+template <int KPT>
+__device__ inline void vbin_chunk(const ViewsParams &p, int &m, int64_t &q0) {
+    constexpr int chunk = KPT * kVbThreads;
+    const int cpv = (int)((p.N + chunk - 1) / chunk);
+    m = (int)blockIdx.x / cpv;
+    q0 = (int64_t)((int)blockIdx.x - m * cpv) * chunk;
 }
 
 __global__ void __launch_bounds__(256) k_vbin_zero(const ViewsParams p) {
-    for (int i = blockIdx.x * 256 + threadIdx.x; i < p.nbins; i += gridDim.x * 256) p.count[i] = 0u;
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i <= p.nbins) p.cursor[i] = 0u;          // cursor[nbins] is the records' total
 }
 
-__global__ void __launch_bounds__(256) k_vbin_count(const ViewsParams p) {
+// KPT layer-pixels per thread.  What bounds both passes is the rate of global
+// adds, ~25 per ns whatever their locality, one per distinct bin of a chunk:
+// at 1080p chunks of 8192 make a third of the adds that chunks of 1024 do.
+template <int KPT>
+__global__ void __launch_bounds__(kVbThreads) k_vbin_count(const ViewsParams p) {
     __shared__ int hkey[kVbHash];
     __shared__ uint32_t hcnt[kVbHash];
-    for (int i = threadIdx.x; i < kVbHash; i += 256) {
+    for (int i = threadIdx.x; i < kVbHash; i += kVbThreads) {
         hkey[i] = -1;
         hcnt[i] = 0u;
     }
     __syncthreads();
-    const int64_t cpv = (p.N + kVbChunk - 1) / kVbChunk;
-    const int m = (int)(blockIdx.x / cpv);
-    const int64_t q0 = ((int64_t)blockIdx.x - (int64_t)m * cpv) * kVbChunk;
+    int m;
+    int64_t q0;
+    vbin_chunk<KPT>(p, m, q0);
 #pragma unroll
-    for (int k = 0; k < kVbKpt; ++k) {
-        const int64_t q = q0 + k * 256 + threadIdx.x;
+    for (int k = 0; k < KPT; ++k) {
+        const int64_t q = q0 + k * kVbThreads + threadIdx.x;
         if (q >= p.N) break;
         float fx, fy;
         int ix, iy, l;
-        const int b = vbin_record(p, m, (int)q, fx, fy, ix, iy, l);
-        if (b >= 0) {
-            const int sl = vbin_slot(hkey, b);
-            if (sl >= 0) atomicAdd(&hcnt[sl], 1u);
+        if (vbin_footprint(p, m, (int)q, p.depth[q], fx, fy, ix, iy, l)) {
+            const int b = vbin_bin(p, m, ix, iy), sl = vbin_slot(hkey, b);
+            atomicAdd(sl >= 0 ? &hcnt[sl] : &p.cursor[b], 1u);
         }
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < kVbHash; i += 256)
-        if (hkey[i] >= 0) atomicAdd(&p.count[hkey[i]], hcnt[i]);
+    for (int i = threadIdx.x; i < kVbHash; i += kVbThreads)
+        if (hkey[i] >= 0) atomicAdd(&p.cursor[hkey[i]], hcnt[i]);
 }
 
-// One workgroup of 1024 threads: each thread sums a run of consecutive
-// counts (read four at a time; nbins is a multiple of 4 and the arrays are
-// 16-byte aligned), the 1024 run totals are scanned in LDS, and each thread
-// writes its run's exclusive prefix sums (start and cursor); start[nbins] =
-// total.
-__global__ void __launch_bounds__(1024) k_vbin_scan(const ViewsParams p) {
-    __shared__ uint32_t tot[1024];
-    const int n4 = p.nbins / 4, t = threadIdx.x;
-    const int per = (n4 + 1023) / 1024;
-    const int b0 = min(t * per, n4), b1 = min(b0 + per, n4);
-    const uint4 *c4 = reinterpret_cast<const uint4 *>(p.count);
-    uint32_t s = 0u;
-#pragma unroll 4
-    for (int i = b0; i < b1; ++i) {
-        const uint4 c = c4[i];
-        s += c.x + c.y + c.z + c.w;
+// A tile's records lie in one run, its four bins in order; which run is of no
+// matter (the tile sums do not depend on it), so a workgroup sums its 256
+// tiles' counts, takes that many slots off the running total with one add and
+// scans the tiles inside.  (Ordered prefix sums by a single workgroup took
+// 80 us for the 65 280 bins of eight 1080p views, this takes 6 us.)
+__global__ void __launch_bounds__(256) k_vbin_scan(const ViewsParams p) {
+    __shared__ uint32_t wave_sum[4], base;
+    const int t = blockIdx.x * 256 + threadIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const bool live = 4 * t < p.nbins;
+    const uint4 c = live ? reinterpret_cast<const uint4 *>(p.cursor)[t] : make_uint4(0u, 0u, 0u, 0u);
+    const uint32_t s = c.x + c.y + c.z + c.w;
+    uint32_t inc = s;                            // inclusive scan over the wave
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t v = __shfl_up(inc, off);
+        if (lane >= off) inc += v;
     }
-    tot[t] = s;
+    if (lane == 63) wave_sum[wave] = inc;
     __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {   // inclusive scan (Hillis-Steele)
-        const uint32_t v = t >= off ? tot[t - off] : 0u;
-        __syncthreads();
-        tot[t] += v;
-        __syncthreads();
-    }
-    uint32_t run = tot[t] - s;                   // exclusive
-    uint4 *s4 = reinterpret_cast<uint4 *>(p.start), *k4 = reinterpret_cast<uint4 *>(p.cursor);
-#pragma unroll 4
-    for (int i = b0; i < b1; ++i) {
-        const uint4 c = c4[i];
-        uint4 o;
-        o.x = run;
-        o.y = o.x + c.x;
-        o.z = o.y + c.y;
-        o.w = o.z + c.z;
-        run = o.w + c.w;
-        s4[i] = o;
-        k4[i] = o;
-    }
-    if (t == 1023) p.start[p.nbins] = tot[1023];
+    if (threadIdx.x == 0) base = atomicAdd(p.total, wave_sum[0] + wave_sum[1] + wave_sum[2] + wave_sum[3]);
+    __syncthreads();
+    uint32_t run = base + inc - s;
+#pragma unroll
+    for (int w = 0; w < 3; ++w) run += (w < wave) ? wave_sum[w] : 0u;
+    if (!live) return;
+    p.start[t] = run;
+    reinterpret_cast<uint4 *>(p.cursor)[t] = make_uint4(run, run + c.x, run + c.x + c.y, run + c.x + c.y + c.z);
 }
 
-__global__ void __launch_bounds__(256) k_vbin_write(const ViewsParams p) {
+template <int KPT>
+__global__ void __launch_bounds__(kVbThreads) k_vbin_write(const ViewsParams p) {
     __shared__ int hkey[kVbHash];
     __shared__ uint32_t hcnt[kVbHash];
     __shared__ uint32_t hbase[kVbHash];
-    for (int i = threadIdx.x; i < kVbHash; i += 256) {
+    for (int i = threadIdx.x; i < kVbHash; i += kVbThreads) {
         hkey[i] = -1;
         hcnt[i] = 0u;
     }
     __syncthreads();
-    const int64_t cpv = (p.N + kVbChunk - 1) / kVbChunk;
-    const int m = (int)(blockIdx.x / cpv);
-    const int64_t q0 = ((int64_t)blockIdx.x - (int64_t)m * cpv) * kVbChunk;
-    int sl[kVbKpt], rb[kVbKpt];
-    uint32_t rank[kVbKpt];
+    int m;
+    int64_t q0;
+    vbin_chunk<KPT>(p, m, q0);
+    const uint32_t cap = (uint32_t)(p.V * p.N);      // both passes bin alike: never reached
+    uint32_t at[KPT];                                // hash slot and rank in its bin
 #pragma unroll
-    for (int k = 0; k < kVbKpt; ++k) {
-        sl[k] = -1;
-        rb[k] = 0;
-        rank[k] = 0u;
-        const int64_t q = q0 + k * 256 + threadIdx.x;
+    for (int k = 0; k < KPT; ++k) {
+        at[k] = ~0u;
+        const int64_t q = q0 + k * kVbThreads + threadIdx.x;
         if (q >= p.N) continue;
         float fx, fy;
         int ix, iy, l;
-        const int b = vbin_record(p, m, (int)q, fx, fy, ix, iy, l);
-        if (b < 0) continue;
-        rb[k] = b;
-        sl[k] = vbin_slot(hkey, b);
-        if (sl[k] >= 0) rank[k] = atomicAdd(&hcnt[sl[k]], 1u);
+        if (!vbin_footprint(p, m, (int)q, p.depth[q], fx, fy, ix, iy, l)) continue;
+        const int b = vbin_bin(p, m, ix, iy), sl = vbin_slot(hkey, b);
+        if (sl >= 0) {
+            at[k] = ((uint32_t)sl << 16) | atomicAdd(&hcnt[sl], 1u);
+        } else {
+            const uint32_t slot = atomicAdd(&p.cursor[b], 1u);
+            if (slot < cap) p.rec[slot] = (int)q;
+        }
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < kVbHash; i += 256)
+    for (int i = threadIdx.x; i < kVbHash; i += kVbThreads)
         if (hkey[i] >= 0) hbase[i] = atomicAdd(&p.cursor[hkey[i]], hcnt[i]);
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < kVbKpt; ++k) {
-        if (sl[k] < 0) continue;
-        const uint32_t slot = hbase[sl[k]] + rank[k];
-        if (slot >= p.start[rb[k] + 1]) continue;    // never taken: both passes bin alike
-        p.rec[slot] = (int)(q0 + k * 256 + threadIdx.x);
+    for (int k = 0; k < KPT; ++k) {
+        if (at[k] == ~0u) continue;
+        const uint32_t slot = hbase[at[k] >> 16] + (at[k] & 0xffffu);
+        if (slot < cap) p.rec[slot] = (int)(q0 + k * kVbThreads + threadIdx.x);
     }
 }
 
-__global__ void __launch_bounds__(256) k_vbin_tile(const ViewsParams p) {
-    extern __shared__ unsigned long long tacc[]; // [L][th][tw][4] (r, g, b, alpha) sums, 2^-32
-    const int t = blockIdx.x;
+// A contribution in 2^-32 units, rounded to the nearest (ties to even).  For
+// |c| < 2^19 (QUICK) by one double fma: adding 1.5 * 2^52 leaves the integer
+// in the low 51 bits (the constant's low word is zero, so taking its bits out
+// is one 32-bit subtraction), three instructions where the general conversion
+// of a float to 64 bits takes over ten; the same integer either way.
+template <bool QUICK>
+__device__ inline unsigned long long vbin_fixed(float c) {
+    if constexpr (QUICK) {
+        const double d = fma((double)c, 4294967296.0, 6755399441055744.0);
+        return __builtin_bit_cast(unsigned long long, d) - 0x4338000000000000ull;
+    } else {
+        return (unsigned long long)__float2ll_rn(c * kVbFix);
+    }
+}
+
+// What bounds it: VALU instructions (the footprint in double and 16
+// conversions per record, ~60 % of the time) beside the LDS adds, with the
+// gathers hidden only by waves in flight: 32 KiB of sums and 512 threads, so
+// four workgroups fill a CU's wave slots (64 KiB tiles, with 6 % fewer
+// records read twice, ran at half the waves and 14 % longer; 256 or 1024
+// threads and two or four records at a time were slower too).  Eight 1080p
+// views of a 1080p LDM of 4 layers: 1.445 -> 0.76 ms, the whole call 2.34 ->
+// 1.17 ms, the counting and writing passes 0.36 -> 0.21 and 0.49 -> 0.25 ms.
+// PL: the distance of the channels' planes where the tile fits it (the adds'
+// offsets are then immediates), 0: as the layers ask.
+template <int PL>
+__global__ void __launch_bounds__(kVbTileThreads) k_vbin_tile(const ViewsParams p) {
+    // four planes of [L][th][tw] (r, g, b, alpha) sums, 2^-32: one per channel, so
+    // the lanes of one add, at scattered pixels, spread over all LDS banks
+    // (with a pixel's four sums adjacent each add reached a quarter of them)
+    extern __shared__ unsigned long long tacc[];
+    // XCD-aware order: each XCD walks one band of tile rows, whose records
+    // come from a band of LDM rows that stays in its L2
+    const int t = xcd_order(blockIdx.x, gridDim.x);
     int m = 0;
     for (int i = 1; i < p.V; ++i) m = (t >= p.tbase[i]) ? i : m;
     const int ntx = p.ntx[m], nty = p.nty[m];
     const int lt = t - p.tbase[m];
     const int tx = lt % ntx, ty = lt / ntx;
-    const int tw = p.tw, th = p.th, tpix = tw * th;
+    const int tw = 1 << kVbLog2Tw, th = p.th, tpix = tw * th;
+    const int plane = PL > 0 ? PL : p.L * tpix;
     const int x0 = tx * tw, y0 = ty * th;
     const int vw = p.vW[m], vh = p.vH[m];
-    for (int i = threadIdx.x; i < 4 * p.L * tpix; i += 256) tacc[i] = 0ull;
+    const unsigned xlim = (unsigned)min(tw, vw - x0), ylim = (unsigned)min(th, vh - y0);
+    {
+        for (int i = threadIdx.x; i < p.L * tpix; i += kVbTileThreads)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) tacc[c * plane + i] = 0ull;
+    }
     __syncthreads();
     // the record ranges: own bins, then the crossing bins of the tiles to the
     // right (left-crossing), below (top-crossing) and below right (both)
     uint32_t rs[5] = {0u, 0u, 0u, 0u, 0u}, re[5] = {0u, 0u, 0u, 0u, 0u};
     {
-        const int b = 4 * (p.tbase[m] + ty * ntx + tx);
-        rs[0] = p.start[b];
-        re[0] = p.start[b + 4];
-        if (tx + 1 < ntx) {
-            rs[1] = p.start[b + 4 + 1];
-            re[1] = p.start[b + 4 + 2];
-            rs[2] = p.start[b + 4 + 3];
-            re[2] = p.start[b + 4 + 4];
+        // a tile's bins lie one after the other, and the write pass has left
+        // every cursor at its bin's end
+        auto range = [&](int j, int tile, int first, int last) {
+            rs[j] = first == 0 ? p.start[tile] : p.cursor[4 * tile + first - 1];
+            re[j] = p.cursor[4 * tile + last];
+        };
+        const int right = tx + 1 < ntx ? 1 : 0, below = ty + 1 < nty ? ntx : 0;
+        range(0, t, 0, 3);
+        if (right) {
+            range(1, t + 1, 1, 1);
+            range(2, t + 1, 3, 3);
         }
-        if (ty + 1 < nty) {
-            const int bb = 4 * (p.tbase[m] + (ty + 1) * ntx + tx);
-            rs[3] = p.start[bb + 2];
-            re[3] = p.start[bb + 4];
-            if (tx + 1 < ntx) {
-                rs[4] = p.start[bb + 4 + 3];
-                re[4] = p.start[bb + 4 + 4];
-            }
-        }
+        if (below) range(3, t + ntx, 2, 3);
+        if (right && below) range(4, t + ntx + 1, 3, 3);
     }
-    // the five ranges as one index space; a thread takes its records two
-    // at a time so both records' loads are in flight together (each record
-    // is a chain: its index, then the layer-pixel's depth and payload)
+    // the five ranges as one index space
     uint32_t cum[6];
     cum[0] = 0u;
 #pragma unroll
     for (int j = 0; j < 5; ++j) cum[j + 1] = cum[j] + (re[j] - rs[j]);
     const uint32_t total = cum[5];
-    constexpr int U = 2;
-    for (uint32_t k0 = threadIdx.x; k0 < total; k0 += 256u * U) {
-        int q[U];
+    for (uint32_t k = threadIdx.x; k < total; k += (uint32_t)kVbTileThreads) {
+        uint32_t o = rs[0];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint32_t k = k0 + 256u * u;
-            q[u] = -1;
-            if (k < total) {
-                int j = 0;
+        for (int j = 1; j < 5; ++j) o = (k >= cum[j]) ? rs[j] - cum[j] : o;
+        // the record is the layer-pixel's index: its footprint is recomputed
+        // by the same function the binning passes ran (so it is the one they
+        // binned) and its payload read from the LDM; an index out of range is
+        // only a record never written
+        const int q = p.rec[o + k];
+        if ((unsigned)q >= (unsigned)p.N) continue;
+        const float d = p.depth[q];
+        const float *c = p.color + (int64_t)q * 3;
+        const float4 v = make_float4(c[0], c[1], c[2], p.alpha[q]);
+        float fx, fy;
+        int ix, iy, l;
+        if (!vbin_footprint(p, m, q, d, fx, fy, ix, iy, l)) continue;
+        const float w[4] = {(1.0f - fx) * (1.0f - fy), fx * (1.0f - fy), (1.0f - fx) * fy, fx * fy};
+        const int lx = ix - x0, ly = iy - y0;
+        const bool inx[2] = {(unsigned)lx < xlim, (unsigned)(lx + 1) < xlim};
+        const bool iny[2] = {(unsigned)ly < ylim, (unsigned)(ly + 1) < ylim};
+        unsigned long long *d0 = tacc + ((l * th + ly) * tw + lx);
+        auto add = [&](auto quick) {
+            constexpr bool Q = decltype(quick)::value;
 #pragma unroll
-                for (int jj = 1; jj < 5; ++jj) j += (k >= cum[jj]) ? 1 : 0;
-                q[u] = p.rec[rs[j] + (k - cum[j])];
+            for (int t4 = 0; t4 < 4; ++t4) {
+                if (!(inx[t4 & 1] && iny[t4 >> 1])) continue;
+                unsigned long long *dst = d0 + (t4 >> 1) * tw + (t4 & 1);
+                atomicAdd(dst, vbin_fixed<Q>(w[t4] * v.x));
+                atomicAdd(dst + plane, vbin_fixed<Q>(w[t4] * v.y));
+                atomicAdd(dst + 2 * plane, vbin_fixed<Q>(w[t4] * v.z));
+                atomicAdd(dst + 3 * plane, vbin_fixed<Q>(w[t4] * v.w));
             }
-        }
-        float fx[U], fy[U];
-        int ix[U], iy[U], l[U];
-        float4 v[U];
-        bool ok[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            // the record is the layer-pixel's index: its footprint is
-            // recomputed by the same function the binning passes ran (so it
-            // is the one they binned) and its payload read from the LDM; an
-            // index out of range is only a record never written
-            ok[u] = (unsigned)q[u] < (unsigned)p.N;
-            const int qq = ok[u] ? q[u] : 0;
-            ok[u] = ok[u] && vbin_record(p, m, qq, fx[u], fy[u], ix[u], iy[u], l[u]) >= 0;
-            v[u] = make_float4(p.color[(int64_t)qq * 3 + 0], p.color[(int64_t)qq * 3 + 1],
-                               p.color[(int64_t)qq * 3 + 2], p.alpha[qq]);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (!ok[u]) continue;
-            const float w[4] = {(1.0f - fx[u]) * (1.0f - fy[u]), fx[u] * (1.0f - fy[u]),
-                                (1.0f - fx[u]) * fy[u], fx[u] * fy[u]};
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int x = ix[u] + (k & 1), y = iy[u] + (k >> 1);
-                const int lx = x - x0, ly = y - y0;
-                if (lx < 0 || lx >= tw || ly < 0 || ly >= th || x >= vw || y >= vh) continue;
-                unsigned long long *d = &tacc[4 * ((l[u] * th + ly) * tw + lx)];
-                atomicAdd(d + 0, (unsigned long long)__float2ll_rn(w[k] * v[u].x * kVbFix));
-                atomicAdd(d + 1, (unsigned long long)__float2ll_rn(w[k] * v[u].y * kVbFix));
-                atomicAdd(d + 2, (unsigned long long)__float2ll_rn(w[k] * v[u].z * kVbFix));
-                atomicAdd(d + 3, (unsigned long long)__float2ll_rn(w[k] * v[u].w * kVbFix));
-            }
-        }
+        };
+        // payloads under 2^18 (and finite) convert by a double add
+        const float big = fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w)));
+        const bool quick = big < 262144.0f && !__builtin_isnan(v.x + v.y + v.z + v.w);
+        if (__all(quick)) add(std::true_type{});
+        else add(std::false_type{});
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < tpix; i += 256) {
+    for (int i = threadIdx.x; i < tpix; i += kVbTileThreads) {
         const int lx = i % tw, ly = i / tw;
         const int x = x0 + lx, y = y0 + ly;
         if (x >= vw || y >= vh) continue;
         float T = 1.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f;
         for (int l = 0; l < p.L; ++l) {
-            const unsigned long long *e = &tacc[4 * ((l * th + ly) * tw + lx)];
-            const float4 s = make_float4((float)(long long)e[0] * kVbUnfix, (float)(long long)e[1] * kVbUnfix,
-                                         (float)(long long)e[2] * kVbUnfix, (float)(long long)e[3] * kVbUnfix);
+            const unsigned long long *e = &tacc[(l * th + ly) * tw + lx];
+            const float4 s = make_float4((float)(long long)e[0] * kVbUnfix,
+                                         (float)(long long)e[plane] * kVbUnfix,
+                                         (float)(long long)e[2 * plane] * kVbUnfix,
+                                         (float)(long long)e[3 * plane] * kVbUnfix);
             const float w = T * s.w;
             c0 = fmaf(w, s.x, c0);
             c1 = fmaf(w, s.y, c1);
@@ -472,20 +526,36 @@ __global__ void __launch_bounds__(256) k_vbin_tile(const ViewsParams p) {
 
 hipError_t launch_render_to_views(const ViewsParams &p, hipStream_t s) {
     if (p.binned) {
-        const int zb = (p.nbins + 255) / 256 < 1024 ? (p.nbins + 255) / 256 : 1024;
-        hipLaunchKernelGGL(k_vbin_zero, dim3(zb > 0 ? zb : 1), dim3(256), 0, s, p);
+        hipLaunchKernelGGL(k_vbin_zero, dim3(p.nbins / 256 + 1), dim3(256), 0, s, p);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        const int64_t cpv = (p.N + kVbChunk - 1) / kVbChunk;
-        const unsigned g = (unsigned)(cpv * p.V);
-        hipLaunchKernelGGL(k_vbin_count, dim3(g), dim3(256), 0, s, p);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        hipLaunchKernelGGL(k_vbin_scan, dim3(1), dim3(1024), 0, s, p);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        hipLaunchKernelGGL(k_vbin_write, dim3(g), dim3(256), 0, s, p);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        const size_t lds = (size_t)p.L * p.th * p.tw * 32;
-        hipLaunchKernelGGL(k_vbin_tile, dim3((unsigned)p.tbase[p.V]), dim3(256), lds, s, p);
+        // layer-pixels per thread: as many as leave ~8 workgroups per CU
+        const int64_t per = p.N * p.V / ((int64_t)kVbThreads * 2048);
+        auto passes = [&](auto kpt) {
+            constexpr int K = decltype(kpt)::value;
+            const int64_t cpv = (p.N + K * kVbThreads - 1) / (K * kVbThreads);
+            const dim3 g((unsigned)(cpv * p.V)), b(kVbThreads);
+            hipLaunchKernelGGL(k_vbin_count<K>, g, b, 0, s, p);
+            hipError_t pe = hipGetLastError();
+            if (pe != hipSuccess) return pe;
+            hipLaunchKernelGGL(k_vbin_scan, dim3((p.nbins / 4 + 255) / 256), dim3(256), 0, s, p);
+            if ((pe = hipGetLastError()) != hipSuccess) return pe;
+            hipLaunchKernelGGL(k_vbin_write<K>, g, b, 0, s, p);
+            return hipGetLastError();
+        };
+        e = per >= 16 ? passes(std::integral_constant<int, 16>{})
+          : per >= 4 ? passes(std::integral_constant<int, 4>{}) : passes(std::integral_constant<int, 1>{});
+        if (e != hipSuccess) return e;
+        // the distance of the sums' planes, fixed where it can be
+        const int tile_sums = p.L * p.th * p.tw;
+        const dim3 tg((unsigned)p.tbase[p.V]), tb(kVbTileThreads);
+        auto tile = [&](auto pl) {
+            constexpr int PL = decltype(pl)::value;
+            const size_t lds = ((size_t)3 * (PL > 0 ? PL : tile_sums) + tile_sums) * 8;
+            hipLaunchKernelGGL(k_vbin_tile<PL>, tg, tb, lds, s, p);
+        };
+        if (tile_sums <= 1024) tile(std::integral_constant<int, 1024>{});
+        else tile(std::integral_constant<int, 0>{});
         return hipGetLastError();
     }
     const int64_t n4 = p.ws_floats / 4;

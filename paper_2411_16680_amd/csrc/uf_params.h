@@ -6,6 +6,20 @@ namespace qk {
 
 constexpr int kMaxViews = 16;
 
+// Division of 0 <= n < 2^31 by a fixed d >= 1 as a multiplication: with
+// l = ceil(log2 d) and mul = ceil(2^(31 + l) / d) < 2^32, the error
+// mul d - 2^(31 + l) is below d, so n times it stays below 2^(31 + l) and
+// n mul >> (31 + l) is exact (d = 1 passes n through).
+struct FastDiv {
+    uint32_t mul, shift, d;        // quotient = (n mul >> 32) >> shift
+};
+inline FastDiv make_fast_div(uint32_t d) {
+    uint32_t l = 0;
+    while ((1ull << l) < d) ++l;
+    if (l == 0) return {0u, 0u, 1u};
+    return {(uint32_t)(((1ull << (31 + l)) + d - 1) / d), l - 1, d};
+}
+
 // Fixed scratch of the allocation-free Update & Fuse entry point (floats):
 // the folded weights W_qk, W_vo (2 heads C C_feat <= kScratchFold) and, after
 // them, the e4m3 scales (7) and running maximum (1).
@@ -196,9 +210,11 @@ struct ViewsParams {
     int32_t ntx[kMaxViews], nty[kMaxViews];
     int32_t tbase[kMaxViews + 1];   // first tile of view m in the list of all views' tiles
     int32_t nbins;                  // 4 x tiles
-    uint32_t *count;                // [nbins] records per bin
-    uint32_t *start;                // [nbins + 1] exclusive prefix sums of count
-    uint32_t *cursor;               // [nbins] next free record of a bin
+    uint32_t *cursor;               // [nbins] records per bin, then a bin's next free record
+    uint32_t *start;                // [nbins / 4] a tile's first record
+    uint32_t *total;                // records handed out so far
+    FastDiv div_hw, div_w;          // by H W and by W of the LDM grid
+    int32_t log2_th;                // th is a power of two (tw is 32)
     int32_t *rec;                   // [V N]: the layer-pixel index of each record
 };
 
