@@ -68,7 +68,8 @@ struct Shape {
 
 // Weight-fragment slots in LDS: Q, [K, V,] O, decode.  The K/V slots exist
 // only when the view loop projects per-sample keys and values on MFMA.
-template <int C, bool KV, int HQ = 1>
+// RE: the reassociated standard form's two extra products.
+template <int C, bool KV, int HQ = 1, bool RE = false>
 struct Frags {
     // HQ query blocks (the heads of the one-to-many form, 1 otherwise); the
     // output projection reads their HQ C-channel concatenation
@@ -79,7 +80,9 @@ struct Frags {
     static constexpr int OFF_V = OFF_K + (KV ? KC * NT : 0);
     static constexpr int OFF_O = OFF_V + (KV ? KC * NT : 0);
     static constexpr int OFF_D = OFF_O + KCO * NT;
-    static constexpr int N = OFF_D + KC * ND;
+    static constexpr int OFF_QK = OFF_D + KC * ND;
+    static constexpr int OFF_OV = OFF_QK + (RE ? KC * NT : 0);
+    static constexpr int N = OFF_OV + (RE ? KC * NT : 0);
 };
 
 // ---------------------------------------------------------------------------
@@ -557,6 +560,28 @@ struct Occupancy {
 // device memory (uniform per workgroup).
 constexpr int kPlain = 0, kBlend = 1, kBatch = 2;
 
+// The float32 standard form with one head runs the view loop of the
+// one-to-many form, its four projections applied in another order: the key
+// projection to the query once per layer-pixel, q . (s_m W_k) = (W_k q) . s_m,
+// and the value projection to the weighted sum of the samples,
+// sum_m p_m (s_m W_v) = (sum_m p_m s_m) W_v.  Two C x C products per
+// layer-pixel take the place of two per sample, on matrix cores that run
+// float32 at a sixteenth of their bfloat16 rate (480x270, L = 16, C = 32, V =
+// 4: 622 -> 420 us a step; 960x540, L = 8, C = 16, V = 8: 1.10 -> 0.84 ms; at
+// V = 1 3 to 15 % less), and nothing is folded ahead, so no workspace is shared.  The
+// result differs by float32 rounding only.  In bfloat16 it would differ by
+// the operands' rounding, and with several heads every head would add a
+// C-wide dot product per sample to the vector units: both keep the samples'
+// projections.
+template <int C, bool BF16, bool FOLD, int HD>
+constexpr bool kReassoc = !BF16 && !FOLD && HD == C;
+
+// ROWS: rows of a workgroup, four waves each.  The reassociated form at C = 64
+// holds 68 KiB of weight fragments, so one workgroup fits a CU: eight waves
+// over two rows share them where that still leaves a workgroup per CU (two
+// waves per SIMD instead of one; 240x135, L = 32, V = 8: 1.16 -> 1.10 ms).
+// With one row a wave has the registers to keep the two extra products'
+// fragments in.
 template <bool BATCH>
 struct UFArgs {
     UFParams p;
@@ -575,11 +600,12 @@ __device__ __forceinline__ int xcd_tile(int i, int nt) {
     return (xcd < rem) ? xcd * (q + 1) + loc : rem * (q + 1) + (xcd - rem) * q + loc;
 }
 
-template <int C, bool BF16, bool FOLD, bool F8, int HD, int VAR>
-__global__ void __launch_bounds__(256)
-__attribute__((amdgpu_waves_per_eu((FOLD && HD != C) ? 2
+template <int C, bool BF16, bool FOLD, bool F8, int HD, int VAR, int ROWS = 1>
+__global__ void __launch_bounds__(256 * ROWS)
+__attribute__((amdgpu_waves_per_eu(ROWS > 1 ? 2
+                                   : (FOLD && HD != C) ? 2
                                    : (!BF16 && VAR == kBlend) ? 1    // its extra stores spill at 3
-                                   : Occupancy<C, BF16, FOLD>::waves)))
+                                   : Occupancy<C, BF16, FOLD || kReassoc<C, BF16, FOLD, HD>>::waves)))
 k_update_fuse(const UFArgs<VAR == kBatch> args) {
     constexpr bool BATCH = VAR == kBatch;
     static_assert(VAR != kBlend || HD == C, "blend-weight logits: one head");
@@ -610,7 +636,9 @@ k_update_fuse(const UFArgs<VAR == kBatch> args) {
     using Coord = typename CoordT<BF16>::type;
     constexpr int G = SH::G, KC = SH::KC, NT = SH::NT, ND = SH::ND, PIX = SH::PIX, P = SH::P;
     constexpr bool TAPK = SH::TAPK;
-    constexpr bool STDLOOP = !FOLD || TAPK;     // the MFMA view loop
+    constexpr bool RE = kReassoc<C, BF16, FOLD, HD>;
+    constexpr bool OTM = FOLD || RE;            // samples stand for keys and values
+    constexpr bool STDLOOP = !OTM || TAPK;      // the MFMA view loop
     // softmax states per lane: one per 16-pixel sub-tile (G > 1), else one
     // per head whose channels the lane holds (TPH output tiles per head)
     constexpr int TPH = (HD >= 16) ? HD / 16 : 1;
@@ -620,7 +648,7 @@ k_update_fuse(const UFArgs<VAR == kBatch> args) {
     // the one-to-many form with several heads keeps one C-channel query, one
     // softmax state and one running sum of the samples per head
     constexpr int HQ = FOLD ? C / HD : 1;
-    using FR = Frags<C, STDLOOP, HQ>;
+    using FR = Frags<C, STDLOOP, HQ, RE>;
     static_assert(!TAPK || 64 * sizeof(MA) <= PIX * P * sizeof(float),
                   "tap staging must fit the o tile it shares");
     static_assert(TAPK || PIX * (C / 8 + (sizeof(MA) <= 16 ? 1 : 0)) * sizeof(MA) <= PIX * P * sizeof(float),
@@ -643,8 +671,9 @@ k_update_fuse(const UFArgs<VAR == kBatch> args) {
                   "the pad columns hold the camera table");
     __shared__ Coord scam[(GR > 1 && !PADTAB) ? kMaxViews * 12 : 1];
     __shared__ int sfwh[(GR > 1 && !PADTAB) ? kMaxViews * 2 : 1];
-    __shared__ float sF[4][PIX * P];
-    __shared__ float sO[4][PIX * P];   // o tile; for C = 8 also the tap exchange
+    constexpr int THREADS = 256 * ROWS;
+    __shared__ float sF[4 * ROWS][PIX * P];
+    __shared__ float sO[4 * ROWS][PIX * P];   // o tile; for C = 8 also the tap exchange
     // word w of the padded table: pad row w / 4 (rows run through the four
     // slices), float w % 4; view m's entries are words 12 m .. 12 m + 11, its
     // map width and height words 12 kMaxViews + 2 m and + 1
@@ -668,22 +697,26 @@ k_update_fuse(const UFArgs<VAR == kBatch> args) {
     // workgroup.  Fragment lane (c, k) holds element [k-slot 8k..8k+7][c] of
     // W (the A operand of the transposed products).  Every projection is
     // block-diagonal over the G sub-tiles.
-    for (int e = tid; e < FR::N * 64; e += 256) {
+    for (int e = tid; e < FR::N * 64; e += THREADS) {
         const int f = e >> 6, ln = e & 63;
         const int nn = ln & 15, gg = ln >> 4;
         // kinds: 0 Q, 1 K, 2 V, 3 O, 4 decode (no K/V slots in the
-        // one-to-many form: the O slots follow Q)
+        // one-to-many form: the O slots follow Q); reassociated form: 5 W_k
+        // on the query, 6 W_v on the output
         const int kind = f < FR::OFF_K ? 0 : f < FR::OFF_V ? 1 : f < FR::OFF_O ? 2
-                       : f < FR::OFF_D ? 3 : 4;
+                       : f < FR::OFF_D ? 3 : (!RE || f < FR::OFF_QK) ? 4 : f < FR::OFF_OV ? 5 : 6;
         int fi = f - (kind == 0 ? FR::OFF_Q : kind == 1 ? FR::OFF_K : kind == 2 ? FR::OFF_V
-                      : kind == 3 ? FR::OFF_O : FR::OFF_D);
+                      : kind == 3 ? FR::OFF_O : (!RE || kind == 4) ? FR::OFF_D
+                      : kind == 5 ? FR::OFF_QK : FR::OFF_OV);
         int head = 0;                             // query block of a Q fragment
         if (HQ > 1 && kind == 0) { head = fi / (KC * NT); fi -= head * KC * NT; }
         const int ntile = (kind == 4) ? ND : NT;
         const int kc = fi / ntile, t = fi % ntile;
         const int ng = 16 * t + nn;               // output channel row of this lane
-        const float *Wm = kind == 0 ? (FOLD ? p.Wqk + (size_t)head * C * C : p.Wq) : kind == 1 ? p.Wk
-                        : kind == 2 ? p.Wv : (FOLD ? p.Wvo : p.Wo);
+        const float *Wm = kind == 0 ? (FOLD ? p.Wqk + (size_t)head * C * C : p.Wq)
+                        : (kind == 1 || (RE && kind == 5)) ? p.Wk
+                        : (kind == 2 || (RE && kind == 6)) ? p.Wv
+                        : (FOLD ? p.Wvo : p.Wo);
         float vals[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
@@ -693,15 +726,17 @@ k_update_fuse(const UFArgs<VAR == kBatch> args) {
                 // K slot kap = tap (kap / 8) x channel (kap % 8); output rows
                 // 8t..8t+7 of the tile hold row-group t of a pair
                 if (nn / 8 == t) {
-                    if (FOLD) w = (kap % 8 == nn % 8) ? 1.0f : 0.0f;     // the blended sample itself
+                    if (OTM) w = (kap % 8 == nn % 8) ? 1.0f : 0.0f;      // the blended sample itself
                     else w = Wm[(kap % 8) * C + (nn % 8)];
                 }
             } else if (HQ > 1 && kind == 3) {
                 // output projection over the heads' concatenation: K slot kap
                 // is channel kap % C of head kap / C
                 w = (Wm + (size_t)(kap / C) * C * C)[(kap % C) * C + ng];
-            } else if (kind < 4) {
+            } else if (kind < 4 || (RE && kind == 6)) {
                 if (kap / C == ng / C) w = Wm[(kap % C) * C + (ng % C)];
+            } else if (RE && kind == 5) {           // transposed: W_k q
+                if (kap / C == ng / C) w = Wm[(ng % C) * C + (kap % C)];
             } else {                                // decode heads: sigma, depth, r, g, b
                 const int s = (G == 1) ? 0 : ng / 8;
                 const int j = (G == 1) ? ng : ng % 8;
@@ -727,8 +762,8 @@ k_update_fuse(const UFArgs<VAR == kBatch> args) {
             *padw(12 * kMaxViews + 2 * e + 1) = __int_as_float(p.fH[e]);
         }
     } else if constexpr (GR > 1) {
-        for (int e = tid; e < p.V * 12; e += 256) scam[e] = cam_entry<BF16>(p, e / 12, e % 12);
-        for (int e = tid; e < p.V; e += 256) {
+        for (int e = tid; e < p.V * 12; e += THREADS) scam[e] = cam_entry<BF16>(p, e / 12, e % 12);
+        for (int e = tid; e < p.V; e += THREADS) {
             sfwh[2 * e] = p.fW[e];
             sfwh[2 * e + 1] = p.fH[e];
         }
@@ -741,9 +776,9 @@ k_update_fuse(const UFArgs<VAR == kBatch> args) {
     const int chunk = tile % p.chunks;
     const int rest = tile / p.chunks;
     const int xb = rest % p.x_blocks;
-    const int y = rest / p.x_blocks;
-    const int x0w = xb * (4 * PIX) + wave * PIX;       // first pixel of this wave
-    if (x0w >= p.W) return;                            // no later barrier: safe to leave
+    const int y = ROWS > 1 ? rest / p.x_blocks * ROWS + (wave >> 2) : rest / p.x_blocks;
+    const int x0w = xb * (4 * PIX) + (ROWS > 1 ? wave & 3 : wave) * PIX;   // first pixel of this wave
+    if (x0w >= p.W || (ROWS > 1 && y >= p.H)) return;  // no later barrier: safe to leave
     const int l_begin = chunk * p.layers_per_chunk;
     const int l_end = min(p.L, l_begin + p.layers_per_chunk);
 
@@ -787,6 +822,18 @@ k_update_fuse(const UFArgs<VAR == kBatch> args) {
             for (int t = 0; t < NT; ++t) {
                 Bk[kc][t] = pfrag(FR::OFF_K + kc * NT + t);
                 Bv[kc][t] = pfrag(FR::OFF_V + kc * NT + t);
+            }
+    }
+    constexpr bool REREG = RE && C == 64 && ROWS == 1;
+    constexpr int KCR = REREG ? KC : 1, NTR = REREG ? NT : 1;
+    MA Rk[KCR][NTR], Rv[KCR][NTR];
+    if constexpr (REREG) {
+#pragma unroll
+        for (int kc = 0; kc < KC; ++kc)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                Rk[kc][t] = pfrag(FR::OFF_QK + kc * NT + t);
+                Rv[kc][t] = pfrag(FR::OFF_OV + kc * NT + t);
             }
     }
     // scale of a key logit and of a value in the FP8 form (1 otherwise)
@@ -858,7 +905,38 @@ k_update_fuse(const UFArgs<VAR == kBatch> args) {
             }
         }
 
+        // ---- reassociated form: y = W x for a vector in the result layout
+        // (per-tile rows, through the wave's slice to the operand layout)
+        auto apply = [&](int off, const MA (&W)[KCR][NTR], const MA (&x)[HQ * KC],
+                         f32x4 (&y)[HQ * NT]) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                y[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int kc = 0; kc < KC; ++kc) {
+                    if constexpr (REREG) y[t] = MM::mma(W[kc][t], x[kc], y[t]);
+                    else y[t] = MM::mma(pfrag(off + kc * NT + t), x[kc], y[t]);
+                }
+            }
+        };
+        auto to_operand = [&](const f32x4 (&y)[HQ * NT], MA (&x)[HQ * KC]) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                float y4[4] = {y[t][0], y[t][1], y[t][2], y[t][3]};
+                lds_write4(&tO[(16 * sd(t) + n) * P + ed(t)], y4);
+            }
+#pragma unroll
+            for (int kc = 0; kc < KC; ++kc) {
+                float t8[8];
+                lds_read8(&tO[pl_b * P + ch0 + 32 * kc], t8);
+                x[kc] = MM::make(t8, 1.0f);
+            }
+        };
         MA Ob[HQ * KC];                                // o, operand layout
+        if constexpr (RE) {                            // Q <- W_k Q
+            to_operand(Q, Ob);
+            apply(FR::OFF_QK, Rk, Ob, Q);
+        }
         const Coord invdc = recip((Coord)d);
         const float d_ld = TAPK ? d : (ld_ok ? p.depth_in[rowbase + x_ld] : 1.0f);
         const Coord invdc_ld = TAPK ? invdc : recip((Coord)d_ld);
@@ -1068,7 +1146,7 @@ k_update_fuse(const UFArgs<VAR == kBatch> args) {
 #pragma unroll
                 for (int t = 0; t < NT; ++t) {
                     f32x4 Vt = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-                    if constexpr (TAPK && FOLD) {
+                    if constexpr (TAPK && OTM) {
                         Vt = Kt[t];                      // values are the samples themselves
                     } else if constexpr (TAPK) {
                         Vt = MM::mma(Bv[0][0], Sb[2 * t], Vt);
@@ -1118,7 +1196,10 @@ k_update_fuse(const UFArgs<VAR == kBatch> args) {
                 for (int kc = 0; kc < KC; ++kc) {
                     lds_read8(&tO[pl_b * P + ch0 + 32 * kc], qa[hq][kc]);
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) ob[hq][kc][i] = 0.0f;
+                    for (int i = 0; i < 8; ++i) {
+                        if constexpr (RE) qa[hq][kc][i] *= scale;   // folded: W_qk carries it
+                        ob[hq][kc][i] = 0.0f;
+                    }
                 }
             }
             float Mx[HQ], Zs[HQ];
@@ -1173,6 +1254,12 @@ k_update_fuse(const UFArgs<VAR == kBatch> args) {
                     Ob[hq * KC + kc] = MM::make(t8, f8_inv_o);
                 }
             }
+        }
+
+        if constexpr (RE) {                            // o <- W_v^T o
+            f32x4 y[HQ * NT];
+            apply(FR::OFF_OV, Rv, Ob, y);
+            to_operand(y, Ob);
         }
 
         // ---- F'^T = W_o^T o^T + F^T (the accumulator starts from F)
@@ -1292,6 +1379,23 @@ struct UFLaunch {
     const UFBatch *batch;
 };
 
+// One level.
+template <int C, bool BF16, bool FOLD, bool F8, int HD, int VAR>
+static hipError_t launch_level(const UFParams &p, hipStream_t s) {
+    UFArgs<false> a{p};
+    if constexpr (C == 64 && kReassoc<C, BF16, FOLD, HD>) {
+        const int rows2 = p.x_blocks * ((p.H + 1) / 2) * p.chunks;   // tiles of two rows
+        if (rows2 >= 256) {
+            a.p.n_tiles = rows2;
+            hipLaunchKernelGGL((k_update_fuse<C, BF16, FOLD, F8, HD, VAR, 2>), dim3(rows2), dim3(512),
+                               0, s, a);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((k_update_fuse<C, BF16, FOLD, F8, HD, VAR>), dim3(p.n_tiles), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
 template <int C, bool BF16, bool FOLD, bool F8, int HD>
 static hipError_t launch_uf(const UFLaunch &l, hipStream_t s) {
     if (l.batch != nullptr) {
@@ -1300,24 +1404,17 @@ static hipError_t launch_uf(const UFLaunch &l, hipStream_t s) {
             const UFArgs<true> a{l.reqs, *l.batch};
             hipLaunchKernelGGL((k_update_fuse<C, BF16, FOLD, F8, HD, kBatch>),
                                dim3(l.batch->total_tiles), dim3(256), 0, s, a);
+            return hipGetLastError();
         } else {
             return hipErrorInvalidValue;
         }
-    } else if (l.p->blend_logit != nullptr) {
-        // blend-weight logits: one head, no e4m3 projections
-        if constexpr (HD == C && !F8) {
-            const UFArgs<false> a{*l.p};
-            hipLaunchKernelGGL((k_update_fuse<C, BF16, FOLD, F8, HD, kBlend>), dim3(l.p->n_tiles),
-                               dim3(256), 0, s, a);
-        } else {
-            return hipErrorInvalidValue;
-        }
-    } else {
-        const UFArgs<false> a{*l.p};
-        hipLaunchKernelGGL((k_update_fuse<C, BF16, FOLD, F8, HD, kPlain>), dim3(l.p->n_tiles),
-                           dim3(256), 0, s, a);
     }
-    return hipGetLastError();
+    if (l.p->blend_logit != nullptr) {
+        // blend-weight logits: one head, no e4m3 projections
+        if constexpr (HD == C && !F8) return launch_level<C, BF16, FOLD, F8, HD, kBlend>(*l.p, s);
+        else return hipErrorInvalidValue;
+    }
+    return launch_level<C, BF16, FOLD, F8, HD, kPlain>(*l.p, s);
 }
 
 // prec: 0 float32, 1 bfloat16, 2 bfloat16 storage with e4m3 projections
