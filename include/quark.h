@@ -159,7 +159,9 @@ typedef struct qk_context qk_context;
  * workspaces that grow on demand and live until qk_context_destroy: the
  * folded weights of the one-to-many form (2 C C_feat floats per request),
  * the e4m3 scales (8 floats), the backward pass's scratch (16 bytes per
- * layer-pixel when d_rgb is given, plus 5 KiB per backward workgroup), the
+ * layer-pixel when d_rgb is given, plus 5 KiB per backward workgroup, plus,
+ * where it is 4 GiB or less, fits the cap and can be had, 4 C + 4 bytes per
+ * layer-pixel and view for larger problems), the
  * render to input views' records (4 bytes per layer-pixel-view) or
  * projected planes, the low-resolution ray encodings, the residual block's
  * weight fragments and the batched launch's parameter table.  Growing one
@@ -385,9 +387,8 @@ QK_API qk_status qk_camera_tables(int32_t V, const qk_camera *in_cams, const int
  *               may be NULL, meaning zero
  *   d_in        receives dLoss/dF, dLoss/ddepth, dLoss/dalpha (overwritten)
  *   d_feats     host array [V] of device pointers, each [Hf][Wf][C_feat]
- *               float: receives dLoss/dI_m (overwritten: cleared, then
- *               scatter-added with float atomics, so its last bits vary
- *               from run to run)
+ *               float: receives dLoss/dI_m (overwritten; summed in an order
+ *               that varies from run to run, and so do its last bits)
  *   d_weights   receives every weight gradient (overwritten, summed in a
  *               fixed order: bitwise reproducible)
  * Through a clamp (alpha outside (1e-6, 1 - 1e-6), disparity outside

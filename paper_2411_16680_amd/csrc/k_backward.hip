@@ -6,40 +6,44 @@
 // Sec. 3.1-3.3 (reprojection, bilinear back-projection, attention across
 // views, decode heads, over composite).  Nothing is taped: each layer-pixel
 // re-gathers its samples and recomputes its attention, so the extra memory
-// is 16 bytes per layer-pixel plus per-workgroup weight-gradient partials.
+// is 16 bytes per layer-pixel, per-workgroup weight-gradient partials and, for
+// the sorted scatter, the samples' gradients.
 //
-// Four launches on the caller's stream:
-//   k_zero_maps         clear the feature-map gradients (scatter targets)
+// On the caller's stream:
+//   k_zero_maps         clear the feature-map gradients (atomics' targets; the
+//                       sorted scatter writes every pixel)
 //   k_composite_adjoint one thread per pixel: for every layer, the gradient
 //                       of rgb with respect to its colour and alpha
 //                       (dc = g T a, da = g . T (c - B_behind))
-//   k_uf_backward<C>    one thread per layer-pixel, persistent workgroups:
+//   k_uf_backward<C>    256 / C layer-pixels per wave, persistent workgroups:
 //                       forward recompute with the key folded into the query
 //                       (a_m = (scale W_k q) . s_m) and the value folded out
 //                       (o = (sum_m p_m s_m) W_v), then the adjoint of
 //                       decode, residual, W_o, W_v, softmax, W_k, W_q and
-//                       RMSNorm; a second pass over the views scatters dI
-//                       with float atomics (rows of C channels regrouped
-//                       through LDS so that each atomic instruction covers
-//                       whole rows) and differentiates the sample
-//                       position with respect to depth.  Weight gradients are
-//                       sums over layer-pixels of outer products; each wave
-//                       forms them on the matrix cores (v_mfma_f32_16x16x4_f32,
-//                       pixels along K), each workgroup writes one partial.
+//                       RMSNorm; a second pass over the views forms every
+//                       sample's gradient ds and differentiates the sample
+//                       position with respect to depth.  ds goes to the maps
+//                       by float atomics (small problems) or to memory, from
+//                       where records sorted by map tile are summed without
+//                       atomics (k_scatter.hip).  Products and weight gradients
+//                       (sums over layer-pixels of outer products) run on the
+//                       matrix cores (v_mfma_f32_16x16x4_f32); each workgroup
+//                       writes one partial.
 //   k_reduce_wgrad      sums the partials in a fixed order (deterministic).
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "uf_params.h"
+#include "vbin.h"
 
 namespace qk {
 namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef const __attribute__((address_space(3))) float lds_f32;
 
 constexpr int kBlock = 256;
 constexpr int kWaves = kBlock / 64;
@@ -145,466 +149,667 @@ __global__ void __launch_bounds__(kBlock) k_composite_backward(const CompBwdPara
 }
 
 // ---------------------------------------------------------------------------
-// One view's sample of one layer-pixel: position (double, as in the float32
-// forward), its derivative with respect to depth, the four clamped taps and
-// their bilinear weights (zero for taps outside the map).
+// The per-layer-pixel kernel.  A wave takes PPT = 256 / C layer-pixels of one
+// layer at a time and holds their C-vectors in one of two layouts, four floats
+// per lane (C = 8: per lane and tile) each:
+//
+//   matrix layout   tile t of 16 pixels, lane (n, g) = (l % 16, l / 16): channels
+//                   4g .. 4g+3 of pixel 16 t + n -- the result rows of
+//                   v_mfma_f32_16x16x4_f32.  With the K slots taken in the
+//                   order 4g + s at step s it is the B operand as well, so
+//                   products chain without moving data (the weights, the A
+//                   operand, are read to match).  C = 8 leaves the lanes of
+//                   channels 8..15 at zero.
+//   load layout     LPP = C / 4 adjacent lanes per pixel: 16-byte chunks of a
+//                   tap's channels, which the texture path serves together.
+//                   A pixel's dot products are sums over its lanes (DPP);
+//                   each lane projects the pixel into a view of its own, LPP
+//                   views at a time.
+//
+// Vectors cross between the two (and to one lane per pixel, for the decode)
+// through the wave's own LDS rows; no barrier is needed for a slice that one
+// wave writes and reads in order.
 // ---------------------------------------------------------------------------
-template <int C>
-struct Sample {
-    float t[4][C];       // taps 00, 10, 01, 11 (zero outside the map)
-    float fx, fy;        // fractional position
-    float dXdd, dYdd;    // d(position) / d(depth)
-    int off[4];          // element offsets of the taps
-    bool in[4];          // tap inside the map
-    bool ok;             // the point is in front of view m
+__device__ inline float rcp(float x) { return __builtin_amdgcn_rcpf(x); }   // about 1 ulp
+// sigma'(x) = sigma(x) sigma(-x) = e / (1 + e)^2 with e = e^-|x|: no
+// cancellation when sigma(x) is near one
+__device__ inline float dsigm(float x) {
+    const float e = __expf(-fabsf(x)), r = rcp(1.0f + e);
+    return e * r * r;
+}
+// tanh x and its derivative 4 e / (1 + e)^2, with e = e^-2|x|
+__device__ inline void tanh_grad(float x, float &th, float &dth) {
+    const float e = __expf(-2.0f * fabsf(x)), r = rcp(1.0f + e);
+    th = copysignf((1.0f - e) * r, x);
+    dth = 4.0f * e * r * r;
+}
+
+constexpr int kTapOob = (int)0x80000000; // past any map under 2 GiB
+
+template <int CTRL>
+__device__ inline float dpp_f(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+// value of lane K of the pixel's LPP lanes
+template <int LPP, int K>
+__device__ inline int pix_bcast(int v) {
+    constexpr int ctrl = LPP == 4 ? K * 0x55 : (K == 0 ? 0xA0 : 0xF5);
+    return __builtin_amdgcn_update_dpp(0, v, ctrl, 0xf, 0xf, true);
+}
+template <int LPP, int K>
+__device__ inline float pix_bcast(float v) {
+    return __int_as_float(pix_bcast<LPP, K>(__float_as_int(v)));
+}
+// sum over the pixel's lanes
+template <int LPP>
+__device__ inline float pix_sum(float v) {
+    v += dpp_f<0xB1>(v);                          // lanes 1, 0, 3, 2
+    if constexpr (LPP == 4) v += dpp_f<0x4E>(v);  // lanes 2, 3, 0, 1
+    return v;
+}
+// sum over a pixel's rows in the matrix layout (all four lane rows; for C = 8
+// the upper two hold zeros)
+__device__ inline float row_sum(float v) {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    const float p = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(p), __float_as_uint(p), false, false);
+    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
+// One layer-pixel in one view: the four taps' byte offsets in the map (in
+// 16-byte units in the WIDE form), kTapOob (-1) where outside it, their
+// bilinear weights, the fractions and d(position) / d(depth).
+struct ViewProj {
+    int o[4];
+    float fx, fy, dx, dy;
 };
 
-template <int C>
-__device__ inline void sample_view(const BwdParams &p, int m, double uc, double vc, double d,
-                                   Sample<C> &S) {
-    const double *A = p.camd[m];
-    const double invd = 1.0 / d;
+template <int C, bool WIDE>
+__device__ __forceinline__ void project(const double *A, int fw, int fh, double uc, double vc, double invd,
+                               bool live, ViewProj &P) {
+    constexpr int U = WIDE ? C / 4 : C * 4;       // one pixel of the map
+    constexpr int OUT = WIDE ? -1 : kTapOob;
     const double pz = fma(A[6], uc, fma(A[7], vc, fma(A[11], invd, A[8])));
     const double qx = fma(A[0], uc, fma(A[1], vc, fma(A[9], invd, A[2])));
     const double qy = fma(A[3], uc, fma(A[4], vc, fma(A[10], invd, A[5])));
-    const double rz = 1.0 / pz;
+    const double rz = recip_d(pz);
     const double X = qx * rz - 0.5, Y = qy * rz - 0.5;
-    S.ok = (pz > 1e-6) && (fabs(X) < 1e7) && (fabs(Y) < 1e7);
+    const bool ok = live && (pz > 1e-6) && (fabs(X) < 1e7) && (fabs(Y) < 1e7);
     // d p / d d = -b / d^2;  d(q / pz) / d d = (dq pz - q dpz) / pz^2
-    const double k = invd * invd * rz * rz;
-    S.dXdd = (float)((qx * A[11] - A[9] * pz) * k);
-    S.dYdd = (float)((qy * A[11] - A[10] * pz) * k);
+    const double k = ok ? invd * invd * rz * rz : 0.0;
+    P.dx = ok ? (float)((qx * A[11] - A[9] * pz) * k) : 0.0f;
+    P.dy = ok ? (float)((qy * A[11] - A[10] * pz) * k) : 0.0f;
     const double xf = floor(X), yf = floor(Y);
-    S.fx = (float)(X - xf);
-    S.fy = (float)(Y - yf);
-    const int fw = p.fW[m], fh = p.fH[m];
-    const int ix = S.ok ? (int)xf : -4, iy = S.ok ? (int)yf : -4;
+    P.fx = ok ? (float)(X - xf) : 0.0f;
+    P.fy = ok ? (float)(Y - yf) : 0.0f;
+    const int ix = ok ? (int)xf : -4, iy = ok ? (int)yf : -4;
     const bool vx0 = (unsigned)ix < (unsigned)fw, vx1 = (unsigned)(ix + 1) < (unsigned)fw;
     const bool vy0 = (unsigned)iy < (unsigned)fh, vy1 = (unsigned)(iy + 1) < (unsigned)fh;
-    S.in[0] = vx0 && vy0;
-    S.in[1] = vx1 && vy0;
-    S.in[2] = vx0 && vy1;
-    S.in[3] = vx1 && vy1;
-    const int cx0 = min(max(ix, 0), fw - 1), cx1 = min(max(ix + 1, 0), fw - 1);
-    const int cy0 = min(max(iy, 0), fh - 1), cy1 = min(max(iy + 1, 0), fh - 1);
-    S.off[0] = (cy0 * fw + cx0) * C;
-    S.off[1] = (cy0 * fw + cx1) * C;
-    S.off[2] = (cy1 * fw + cx0) * C;
-    S.off[3] = (cy1 * fw + cx1) * C;
-    const float *fm = p.feat[m];
+    const int o = (iy * fw + ix) * U;
+    P.o[0] = (vx0 && vy0) ? o : OUT;
+    P.o[1] = (vx1 && vy0) ? o + U : OUT;
+    P.o[2] = (vx0 && vy1) ? o + fw * U : OUT;
+    P.o[3] = (vx1 && vy1) ? o + fw * U + U : OUT;
+}
+
+// One view's taps of the lane's channels, as loaded, and the projection.
+struct Taps {
+    float4 t[4];
+    ViewProj p;
+};
+
+template <int C, bool WIDE, int K>
+__device__ __forceinline__ void issue_taps(const BwdParams &p, int m, const ViewProj &mine, int chunk, Taps &T) {
+    constexpr int LPP = C / 4;
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        const float4 *src = reinterpret_cast<const float4 *>(fm + S.off[t]);
-        const float keep = S.in[t] ? 1.0f : 0.0f;
+    for (int j = 0; j < 4; ++j) T.p.o[j] = pix_bcast<LPP, K>(mine.o[j]);
+    T.p.fx = pix_bcast<LPP, K>(mine.fx);
+    T.p.fy = pix_bcast<LPP, K>(mine.fy);
+    T.p.dx = pix_bcast<LPP, K>(mine.dx);
+    T.p.dy = pix_bcast<LPP, K>(mine.dy);
+    if constexpr (WIDE) {
+        const float4 *f = reinterpret_cast<const float4 *>(p.feat[m]);
 #pragma unroll
-        for (int c4 = 0; c4 < C / 4; ++c4) {
-            const float4 v = src[c4];
-            S.t[t][4 * c4 + 0] = v.x * keep;
-            S.t[t][4 * c4 + 1] = v.y * keep;
-            S.t[t][4 * c4 + 2] = v.z * keep;
-            S.t[t][4 * c4 + 3] = v.w * keep;
+        for (int j = 0; j < 4; ++j)
+            T.t[j] = T.p.o[j] >= 0 ? f[T.p.o[j] + chunk] : make_float4(0.f, 0.f, 0.f, 0.f);
+    } else {
+        // a load past the map's bytes returns zeros
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float *>(p.feat[m]), 0, p.fH[m] * p.fW[m] * C * 4, 0x00020000);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const auto a = __builtin_amdgcn_raw_buffer_load_b128(r, T.p.o[j] + 16 * chunk, 0, 0);
+            T.t[j] = make_float4(__uint_as_float(a[0]), __uint_as_float(a[1]), __uint_as_float(a[2]),
+                                 __uint_as_float(a[3]));
         }
     }
 }
 
-template <int C>
-__device__ inline void blend(const Sample<C> &S, float *s) {
-    const float w00 = (1.f - S.fx) * (1.f - S.fy), w10 = S.fx * (1.f - S.fy);
-    const float w01 = (1.f - S.fx) * S.fy, w11 = S.fx * S.fy;
-#pragma unroll
-    for (int c = 0; c < C; ++c)
-        s[c] = fmaf(w00, S.t[0][c], fmaf(w10, S.t[1][c], fmaf(w01, S.t[2][c], w11 * S.t[3][c])));
+__device__ inline float4 blend(const Taps &T) {
+    const float fx = T.p.fx, fy = T.p.fy;
+    const float w00 = (1.f - fx) * (1.f - fy), w10 = fx * (1.f - fy);
+    const float w01 = (1.f - fx) * fy, w11 = fx * fy;
+    float4 s;
+    s.x = fmaf(w00, T.t[0].x, fmaf(w10, T.t[1].x, fmaf(w01, T.t[2].x, w11 * T.t[3].x)));
+    s.y = fmaf(w00, T.t[0].y, fmaf(w10, T.t[1].y, fmaf(w01, T.t[2].y, w11 * T.t[3].y)));
+    s.z = fmaf(w00, T.t[0].z, fmaf(w10, T.t[1].z, fmaf(w01, T.t[2].z, w11 * T.t[3].z)));
+    s.w = fmaf(w00, T.t[0].w, fmaf(w10, T.t[1].w, fmaf(w01, T.t[2].w, w11 * T.t[3].w)));
+    return s;
 }
 
-// Sum over the wave's 64 layer-pixels of a_p (x) b_p, added to a 16 x 16
-// accumulator (rows: index of a, columns: index of b; vectors zero-padded to
-// 16).  The wave's vectors go through its own LDS slice: lane l feeds the
-// matrix cores a_{4s + l/16}[l % 16] and b_{4s + l/16}[l % 16] at step s.
-template <int NA, int NB>
-__device__ inline void outer_accumulate(float *sa, float *sb, int lane, const float *a,
-                                        const float *b, bool live, f32x4 &acc) {
-    __syncthreads();   // the previous pair's reads are done
-#pragma unroll
-    for (int c4 = 0; c4 < 4; ++c4) {
-        float va[4], vb[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int c = 4 * c4 + i;
-            va[i] = (live && c < NA) ? a[c < NA ? c : 0] : 0.0f;
-            vb[i] = (live && c < NB) ? b[c < NB ? c : 0] : 0.0f;
-        }
-        reinterpret_cast<float4 *>(sa + lane * 16)[c4] = make_float4(va[0], va[1], va[2], va[3]);
-        reinterpret_cast<float4 *>(sb + lane * 16)[c4] = make_float4(vb[0], vb[1], vb[2], vb[3]);
-    }
-    __syncthreads();
-    const int r = lane & 15, k = lane >> 4;
-#pragma unroll
-    for (int s = 0; s < 16; ++s) {
-        const int idx = (4 * s + k) * 16 + r;
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(sa[idx], sb[idx], acc, 0, 0, 0);
-    }
+__device__ inline float dot4(const float4 &a, const float4 &b) {
+    return fmaf(a.x, b.x, fmaf(a.y, b.y, fmaf(a.z, b.z, a.w * b.w)));
 }
 
-// Per-use view of the weights in LDS.  Every use site takes a fresh opaque
-// base address, so the compiler neither keeps a whole matrix live across
-// uses nor hoists it out of the loops; rows are read contiguously, the same
-// address in every lane (a broadcast).
-__device__ inline lds_f32 *weights_at(lds_f32 *base, int offset) {
-    lds_f32 *w = base + offset;
-    asm volatile("" : "+v"(w));
-    return w;
-}
-
-// y[j] = sum_c x[c] W[c][j]   (W row-major R x K)
-template <int R, int K>
-__device__ inline void vec_mat(const float *x, lds_f32 *W, float *y) {
-#pragma unroll
-    for (int j = 0; j < K; ++j) y[j] = 0.f;
-#pragma unroll 2
-    for (int c = 0; c < R; ++c) {
-        lds_f32 *row = W + c * K;
-#pragma unroll
-        for (int j = 0; j < K; ++j) y[j] = fmaf(x[c], row[j], y[j]);
-        __builtin_amdgcn_sched_barrier(0);      // one row in flight at a time
-    }
-}
-
-// y[c] = sum_j W[c][j] x[j]   (W row-major R x K)
-template <int R, int K>
-__device__ inline void mat_vec(lds_f32 *W, const float *x, float *y) {
-#pragma unroll 2
-    for (int c = 0; c < R; ++c) {
-        lds_f32 *row = W + c * K;
-        float acc = 0.f;
-#pragma unroll
-        for (int j = 0; j < K; ++j) acc = fmaf(row[j], x[j], acc);
-        y[c] = acc;
-        __builtin_amdgcn_sched_barrier(0);      // one row in flight at a time
-    }
-}
-
-// Loads a layer-pixel's feature vector and returns its RMS-normalised form
-// and the RMS r (unit gain, eps 1e-6 inside the root).
-template <int C>
-__device__ inline float load_normalised(const float *F, int64_t e, float *xn) {
-    const float4 *f4 = reinterpret_cast<const float4 *>(F + e * C);
-#pragma unroll
-    for (int c4 = 0; c4 < C / 4; ++c4) {
-        const float4 v = f4[c4];
-        xn[4 * c4 + 0] = v.x;
-        xn[4 * c4 + 1] = v.y;
-        xn[4 * c4 + 2] = v.z;
-        xn[4 * c4 + 3] = v.w;
-    }
-    float ss = 0.f;
-#pragma unroll
-    for (int c = 0; c < C; ++c) ss = fmaf(xn[c], xn[c], ss);
-    const float r = sqrtf(ss * (1.0f / (float)C) + 1e-6f);
-    const float ir = 1.0f / r;
-#pragma unroll
-    for (int c = 0; c < C; ++c) xn[c] *= ir;
-    return r;
-}
+// The weight matrices in LDS, each 16 x 16 row-major, zero beyond C; H the
+// decode heads' (sigma, depth, r, g, b).  As the A operand of a product lane
+// (m, g) takes elements [4g .. 4g+3][m] (y = x W) or, transposed, [m][4g ..
+// 4g+3] (y = W x).
+enum { kMatQ, kMatK, kMatV, kMatO, kMatH, kNumMat };
 
 template <int C>
-__device__ inline void load_vec(const float *src, int64_t e, float *v) {
-    const float4 *s4 = reinterpret_cast<const float4 *>(src + e * C);
+__device__ __forceinline__ float mat_element(const BwdParams &p, int w, int in, int out) {
+    if (in >= C) return 0.0f;
+    if (w == kMatH)
+        return out == 0 ? p.w_sigma[in] : out == 1 ? p.w_depth[in]
+             : out < 5 ? p.W_color[in * 3 + out - 2] : 0.0f;
+    if (out >= C) return 0.0f;
+    const float *W = w == kMatQ ? p.Wq : w == kMatK ? p.Wk : w == kMatV ? p.Wv : p.Wo;
+    return W[in * C + out];
+}
+
+// y += x W, or y += W x when TRANS, for the wave's vectors (matrix layout)
+template <bool TRANS, int MT>
+__device__ __forceinline__ void product(const float *W, int n, int g, const f32x4 (&x)[MT], f32x4 (&y)[MT]) {
+    f32x4 a;
+    if constexpr (TRANS) a = *reinterpret_cast<const f32x4 *>(W + 16 * n + 4 * g);
+    else
 #pragma unroll
-    for (int c4 = 0; c4 < C / 4; ++c4) {
-        const float4 t = s4[c4];
-        v[4 * c4 + 0] = t.x;
-        v[4 * c4 + 1] = t.y;
-        v[4 * c4 + 2] = t.z;
-        v[4 * c4 + 3] = t.w;
+        for (int i = 0; i < 4; ++i) a[i] = W[16 * (4 * g + i) + n];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int t = 0; t < MT; ++t) y[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], x[t][i], y[t], 0, 0, 0);
+}
+
+template <int MT>
+__device__ __forceinline__ void zero4(f32x4 (&y)[MT]) {
+#pragma unroll
+    for (int t = 0; t < MT; ++t) y[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+}
+
+// Orders the wave's LDS accesses before and after it (no instruction: a wave's
+// LDS accesses complete in order)
+__device__ __forceinline__ void wave_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// A wave's pixel rows in LDS: C channels, then four scalars (d depth so far,
+// softmax reference, 1 / normaliser, ob . dob).
+template <int C>
+constexpr int kRow = C + 4;
+
+// matrix layout <-> rows (lanes of channels past C: not stored, zero)
+template <int C, int MT>
+__device__ __forceinline__ void rows_store(float *rows, int n, int g, const f32x4 (&x)[MT]) {
+    if (C < 16 && 4 * g >= C) return;
+#pragma unroll
+    for (int t = 0; t < MT; ++t) *reinterpret_cast<f32x4 *>(rows + (16 * t + n) * kRow<C> + 4 * g) = x[t];
+}
+template <int C, int MT>
+__device__ __forceinline__ void rows_load(const float *rows, int n, int g, f32x4 (&x)[MT]) {
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+        x[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (C == 16 || 4 * g < C) x[t] = *reinterpret_cast<const f32x4 *>(rows + (16 * t + n) * kRow<C> + 4 * g);
     }
 }
 
+// acc += sum over the wave's pixels of a (x) b, from their rows (pixels along
+// K: lane (c, k) feeds element c of pixel 4 s + k at step s; for C = 8
+// elements 8..15 hold what lies there and reach only entries never read)
 template <int C>
-__device__ inline void store_vec(float *dst, int64_t e, const float *v) {
-    float4 *d4 = reinterpret_cast<float4 *>(dst + e * C);
+__device__ __forceinline__ void outer_rows(const float *a, const float *b, int n, int g, f32x4 &acc) {
+    const int c = C < 16 ? n & (C - 1) : n;
 #pragma unroll
-    for (int c4 = 0; c4 < C / 4; ++c4)
-        d4[c4] = make_float4(v[4 * c4 + 0], v[4 * c4 + 1], v[4 * c4 + 2], v[4 * c4 + 3]);
+    for (int s = 0; s < 64 / C; ++s)
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[(4 * s + g) * kRow<C> + c],
+                                                   b[(4 * s + g) * kRow<C> + c], acc, 0, 0, 0);
 }
 
-// One thread per layer-pixel.  Live ranges are kept short: the input
-// feature is re-read where it is needed again, and dF' is parked in the dF
-// output across the second pass over the views.
-template <int C>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2)))
+// Calls f(integral_constant<int, K>) for K = B .. N - 1.
+template <int B, int N, typename F>
+__device__ __forceinline__ void static_for(F &&f) {
+    if constexpr (B < N) {
+        f(std::integral_constant<int, B>{});
+        static_for<B + 1, N>(f);
+    }
+}
+
+// How the samples' gradients reach the maps: float atomics (32-bit byte
+// offsets, or for maps of 2 GiB and more 64-bit addresses), or rows of ds in
+// memory for the sorted scatter -- with up to kKeep views the taps of the first
+// pass are kept in registers for the second.
+enum { kNarrow, kWide, kSort, kSortKeep };
+constexpr int kKeep = kBwdKeep;
+
+// What bounds it (960x540, L = 8, C = 16, V = 4, i.i.d. depths).  The float
+// atomics alone take 3.5 ms: they execute at the memory side, ~19 rows of C
+// floats per ns however they are grouped, so from kScatterMin on the gradients
+// go through the sort (0.65 ms, k_scatter.hip).  What is left was, with a pixel
+// per lane, 2.1 ms of 64-line gathers, LDS reads of the weights and 4700 vector
+// instructions per 64 pixels; quads of lanes per tap row, the products on the
+// matrix cores, 16 pixels at a time (few enough registers to keep the taps of
+// four views for the second pass, at two waves per SIMD) and one e^-|x| per
+// logistic leave 0.93 ms: latency at that occupancy (VALU 37 % busy; gathering
+// again at three waves per SIMD 1.10 ms, four waves spill).  The whole adjoint
+// 4.0 -> 1.75 ms.
+template <int C, int MODE>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(MODE == kSortKeep ? kBwdWavesKeep : kBwdWaves)))
 k_uf_backward(const BwdParams p) {
-    static_assert(C == 8 || C == 16, "the backward kernel holds C <= 16 channels per thread");
-    __shared__ float s_a[kWaves][64 * 16];
-    __shared__ float s_b[kWaves][64 * 16];
-    __shared__ int s_o[kWaves][256];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    float *sa = s_a[wave], *sb = s_b[wave];
-    int *so = s_o[wave];
+    static_assert(C == 8 || C == 16, "the backward kernel holds C <= 16 channels per pixel");
+    constexpr bool WIDE = MODE == kWide, SORT = MODE >= kSort, KEEP = MODE == kSortKeep;
+    constexpr int LPP = C / 4;                    // lanes per pixel in the load layout
+    constexpr int PPT = 64 / LPP;                 // pixels of a wave
+    constexpr int MT = PPT / 16;                  // their tiles in the matrix layout
+    constexpr int ROW = kRow<C>;
+    __shared__ __attribute__((aligned(16))) float s_a[kWaves][PPT * ROW > 256 ? PPT * ROW : 256];
+    __shared__ __attribute__((aligned(16))) float s_b[kWaves][PPT * ROW];
+    __shared__ int2 s_ow[SORT ? 1 : kWaves][SORT ? 1 : PPT * 4];   // one view's tap offsets and weights
+    __shared__ __attribute__((aligned(16))) float s_w[kNumMat][256];
+    __shared__ double s_cam[kMaxViews * 12];
+    __shared__ int2 s_wh[kMaxViews];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = lane & 15, g = lane >> 4;       // matrix layout
+    const int chunk = lane % LPP, lp = lane / LPP;   // load layout
+    float *A = s_a[wave], *B = s_b[wave];
+    int2 *Sow = s_ow[SORT ? 0 : wave];
 
-    // The weights live in LDS for the whole kernel; every lane reads the same
-    // address (a broadcast).
-    constexpr int NW = 4 * C * C + 5 * C;
-    __shared__ __attribute__((aligned(16))) float s_w[NW];
-    for (int i = threadIdx.x; i < NW; i += kBlock) {
-        float v;
-        if (i < C * C) v = p.Wq[i];
-        else if (i < 2 * C * C) v = p.Wk[i - C * C];
-        else if (i < 3 * C * C) v = p.Wv[i - 2 * C * C];
-        else if (i < 4 * C * C) v = p.Wo[i - 3 * C * C];
-        else if (i < 4 * C * C + C) v = p.w_sigma[i - 4 * C * C];
-        else if (i < 4 * C * C + 2 * C) v = p.w_depth[i - 4 * C * C - C];
-        else v = p.W_color[i - 4 * C * C - 2 * C];
-        s_w[i] = v;
-    }
+    for (int i = threadIdx.x; i < kNumMat * 256; i += kBlock)
+        s_w[i >> 8][i & 255] = mat_element<C>(p, i >> 8, (i >> 4) & 15, i & 15);
+    for (int i = threadIdx.x; i < p.V * 12; i += kBlock) s_cam[i] = p.camd[i / 12][i % 12];
+    for (int i = threadIdx.x; i < p.V; i += kBlock) s_wh[i] = make_int2(p.fW[i], p.fH[i]);
     __syncthreads();
-    lds_f32 *wb = (lds_f32 *)(s_w);
-    constexpr int OQ = 0, OK = C * C, OV = 2 * C * C, OO = 3 * C * C, OH = 4 * C * C;
 
     f32x4 gQ = {0.f, 0.f, 0.f, 0.f}, gK = gQ, gV = gQ, gO = gQ, gH = gQ;
-    const int32_t npix = p.H * p.W;
-    const int32_t N = (int32_t)p.N;
     const float half_l = 0.5f / (float)p.L;
     const float band = p.inv_near - p.inv_far;
     const float kap = half_l * band;
-    const float scale = p.scale;
+    const bool has_ch = 4 * g < C;                // this lane's channels exist
 
-    for (int32_t base = blockIdx.x * kBlock; base < N; base += gridDim.x * kBlock) {
-        const bool live = base + (int32_t)threadIdx.x < N;
-        const int32_t e = live ? base + (int32_t)threadIdx.x : N - 1;
-        const int32_t li = e / npix;
-        const int32_t rem = e - li * npix;
-        const int32_t y = rem / p.W, x = rem - y * p.W;
-        const double uc = x + 0.5, vc = y + 0.5;
-        const float d = p.depth_in[e];
+    // A wave's pixels lie in one layer; the items run through the layers of
+    // PPT pixels before the next PPT, and each XCD (workgroups are dispatched
+    // round-robin over the 8) takes one contiguous range of them, so the rows of
+    // the maps that a band of pixels samples stay in its L2.
+    const int32_t npix = p.H * p.W, items = p.L * ((npix + PPT - 1) / PPT);
+    const int nr = min(8, (int)gridDim.x), r = (int)blockIdx.x % nr;
+    const int32_t item_end = (int32_t)((int64_t)items * (r + 1) / nr);
+    const int32_t item_step = ((int)gridDim.x - r + nr - 1) / nr * kWaves;
+    const int32_t item0 = (int32_t)((int64_t)items * r / nr) + (int)blockIdx.x / nr * kWaves + wave;
+    // the depth of this lane's pixel (load layout) of an item, read one item
+    // ahead: the projections wait on it, and the taps on them
+    auto item_depth = [&](int32_t item) {
+        const int32_t q0 = (int32_t)fast_div((uint32_t)item, p.div_l), li = item - q0 * p.L;
+        return p.depth_in[min(li * npix + q0 * PPT + lp, (li + 1) * npix - 1)];
+    };
+    float depth_next = item0 < item_end ? item_depth(item0) : 1.0f;
+    for (int32_t item = item0; item < item_end; item += item_step) {
+        const float depth_ld = depth_next;
+        if (item + item_step < item_end) depth_next = item_depth(item + item_step);
+        const int32_t q0 = (int32_t)fast_div((uint32_t)item, p.div_l), li = item - q0 * p.L;
+        const int32_t base = li * npix + q0 * PPT, N = (li + 1) * npix;
+        const bool full = N - base >= PPT;        // no pixel past the layer's end
+        // vectors of this wave's pixels in memory (matrix layout); pixels past
+        // the layer's end read its last one and count as zero
+        auto load_vec = [&](const float *src, f32x4 (&x)[MT]) {
+#pragma unroll
+            for (int t = 0; t < MT; ++t) {
+                const int32_t e = min(base + 16 * t + n, N - 1);
+                x[t] = has_ch ? *reinterpret_cast<const f32x4 *>(src + (int64_t)e * C + 4 * g)
+                              : f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+        };
+        // rows of a vector, zero for pixels past the end
+        auto rows_live = [&](float *rows, f32x4 (&x)[MT]) {
+            if (!full) {
+#pragma unroll
+                for (int t = 0; t < MT; ++t)
+                    if (base + 16 * t + n >= N) x[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+            rows_store<C>(rows, n, g, x);
+        };
+
+        // ---- the pixel of this lane in the load layout, and its first views'
+        //      projections
+        const int32_t e_ld = base + lp;
+        const bool live_ld = e_ld < N;
+        const uint32_t ec_ld = (uint32_t)(live_ld ? e_ld : N - 1);
+        const uint32_t rem = ec_ld - (uint32_t)(li * npix), yy = fast_div(rem, p.div_w);
+        const double uc = (double)(rem - yy * p.div_w.d) + 0.5, vc = (double)yy + 0.5;
+        const double invd = recip_d((double)depth_ld);
+        ViewProj mine;
+        auto proj = [&](int m0) {
+            const int m = min(m0 + chunk, p.V - 1);
+            const int2 wh = s_wh[m];
+            project<C, WIDE>(s_cam + 12 * m, wh.x, wh.y, uc, vc, invd, live_ld, mine);
+        };
+        // the views in order: all in flight and kept (up to kKeep), or the taps
+        // of the next view in flight behind the current one
+        Taps kept[KEEP ? kKeep : 1];
+        if constexpr (KEEP) {
+            static_for<0, kKeep>([&](auto kk) {
+                constexpr int k = decltype(kk)::value;
+                if (k < p.V) {
+                    if constexpr (k % LPP == 0) proj(k);
+                    issue_taps<C, WIDE, k % LPP>(p, k, mine, chunk, kept[k]);
+                }
+            });
+        }
+        auto run_views = [&](auto &&step) {
+            if constexpr (KEEP) {
+                static_for<0, kKeep>([&](auto kk) {
+                    constexpr int k = decltype(kk)::value;
+                    if (k < p.V) step(kept[k], k);
+                });
+            } else {
+                Taps ta, tb;
+                proj(0);
+                issue_taps<C, WIDE, 0>(p, 0, mine, chunk, ta);
+                for (int m0 = 0; m0 < p.V; m0 += LPP) {
+                    static_for<0, LPP>([&](auto kk) {
+                        constexpr int k = decltype(kk)::value;
+                        Taps &cur = k % 2 == 0 ? ta : tb, &nxt = k % 2 == 0 ? tb : ta;
+                        const int mn = min(m0 + k + 1, p.V - 1);
+                        if constexpr (k + 1 < LPP) {
+                            issue_taps<C, WIDE, k + 1>(p, mn, mine, chunk, nxt);
+                        } else {
+                            if (m0 + LPP < p.V) proj(m0 + LPP);
+                            issue_taps<C, WIDE, 0>(p, mn, mine, chunk, nxt);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (m0 + k < p.V) step(cur, m0 + k);
+                        __builtin_amdgcn_sched_barrier(0);
+                    });
+                }
+            }
+        };
 
         // ---- query folded with the key: q~ = scale W_k (N(F) W_q)
-        float qt[C];
-        {
-            float xn[C], q[C];
-            load_normalised<C>(p.F_in, e, xn);
-            vec_mat<C, C>(xn, weights_at(wb, OQ), q);
-            mat_vec<C, C>(weights_at(wb, OK), q, qt);
-#pragma unroll
-            for (int c = 0; c < C; ++c) qt[c] *= scale;
+        f32x4 f[MT], q[MT];
+        float ir[MT];                             // 1 / RMS
+        load_vec(p.F_in, f);
+        // what the decode will need (one lane per pixel), read now
+        const int32_t e_px = base + lane, ec_px = min(e_px, N - 1);
+        float4 cg = make_float4(0.f, 0.f, 0.f, 0.f);          // dLoss/d(colour, alpha)
+        float ddn = 0.f, d_px = 1.f, a_px = 0.5f;
+        if (lane < PPT) {
+            if (p.comp) cg = reinterpret_cast<const float4 *>(p.comp)[ec_px];
+            if (p.d_alpha_out) cg.w += p.d_alpha_out[ec_px];
+            if (p.d_depth_out) ddn = p.d_depth_out[ec_px];
+            d_px = p.depth_in[ec_px];
+            a_px = p.alpha_in[ec_px];
         }
+#pragma unroll
+        for (int t = 0; t < MT; ++t) {
+            const float ss = row_sum(fmaf(f[t][0], f[t][0], fmaf(f[t][1], f[t][1],
+                                     fmaf(f[t][2], f[t][2], f[t][3] * f[t][3]))));
+            ir[t] = __builtin_amdgcn_rsqf(ss * (1.0f / (float)C) + 1e-6f);
+        }
+        auto normalised = [&](f32x4 (&x)[MT]) {
+#pragma unroll
+            for (int t = 0; t < MT; ++t)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) x[t][i] = f[t][i] * ir[t];
+        };
+        {
+            f32x4 x[MT], y[MT];
+            normalised(x);
+            zero4(q);
+            product<false>(s_w[kMatQ], n, g, x, q);
+            zero4(y);
+            product<true>(s_w[kMatK], n, g, q, y);
+#pragma unroll
+            for (int t = 0; t < MT; ++t)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) y[t][i] *= p.scale;
+            wave_order();
+            rows_store<C>(B, n, g, y);
+            wave_order();
+        }
+        float *row_ld = A + lp * ROW;
+        const float4 qv = *reinterpret_cast<const float4 *>(B + lp * ROW + 4 * chunk);
 
         // ---- pass 1 over the views: online softmax of a_m = q~ . s_m and
         //      ob = sum_m p_m s_m.  The weights are exp(a_m - mx) for a
         //      reference mx moved only when a logit passes it by more than 8
         //      (always at the first view), as in the forward kernel; pass 2
         //      uses the same reference.
-        float mx = -1e30f, z = 0.f, ob[C];
-#pragma unroll
-        for (int c = 0; c < C; ++c) ob[c] = 0.f;
-#pragma unroll 1
-        for (int m = 0; m < p.V; ++m) {
-            Sample<C> S;
-            sample_view<C>(p, m, uc, vc, (double)d, S);
-            float s[C];
-            blend<C>(S, s);
-            float a = 0.f;
-#pragma unroll
-            for (int c = 0; c < C; ++c) a = fmaf(qt[c], s[c], a);
-            float diff = a - mx;
-            if (diff > 8.0f) {
-                const float r = __expf(-diff);
-                z *= r;
-#pragma unroll
-                for (int c = 0; c < C; ++c) ob[c] *= r;
-                mx = a;
-                diff = 0.0f;
-            }
-            const float pw = __expf(diff);
-            z += pw;
-#pragma unroll
-            for (int c = 0; c < C; ++c) ob[c] = fmaf(pw, s[c], ob[c]);
+        float mx = -1e30f, iz, logit[KEEP ? kKeep : 1];
+        {
+            float z = 0.f;
+            float4 ob = make_float4(0.f, 0.f, 0.f, 0.f);
+            run_views([&](const Taps &T, int m) {
+                const float4 s = blend(T);
+                const float a = pix_sum<LPP>(dot4(qv, s));
+                if constexpr (KEEP) logit[m] = a;
+                float diff = a - mx;
+                if (diff > 8.0f) {
+                    const float rr = __expf(-diff);
+                    z *= rr;
+                    ob.x *= rr; ob.y *= rr; ob.z *= rr; ob.w *= rr;
+                    mx = a;
+                    diff = 0.0f;
+                }
+                const float pw = __expf(diff);
+                z += pw;
+                ob.x = fmaf(pw, s.x, ob.x);
+                ob.y = fmaf(pw, s.y, ob.y);
+                ob.z = fmaf(pw, s.z, ob.z);
+                ob.w = fmaf(pw, s.w, ob.w);
+            });
+            iz = rcp(z);
+            *reinterpret_cast<float4 *>(row_ld + 4 * chunk) = make_float4(ob.x * iz, ob.y * iz, ob.z * iz, ob.w * iz);
+            wave_order();
         }
-        const float iz = 1.0f / z;
-#pragma unroll
-        for (int c = 0; c < C; ++c) ob[c] *= iz;
 
         // ---- o = ob W_v; F' = F + o W_o; decode and its adjoint; back
         //      through W_o and W_v to dob = W_v W_o^T dF'
-        float dob[C], dd_in = 0.f, da_in = 0.f;
+        f32x4 dfp[MT];
         {
-            float o[C], fp[C];
-            vec_mat<C, C>(ob, weights_at(wb, OV), o);
-            vec_mat<C, C>(o, weights_at(wb, OO), fp);
-            {
-                float f[C];
-                load_vec<C>(p.F_in, e, f);
+            f32x4 ob[MT], o[MT], fp[MT], x[MT];
+            rows_load<C>(A, n, g, ob);
+            zero4(o);
+            product<false>(s_w[kMatV], n, g, ob, o);
 #pragma unroll
-                for (int c = 0; c < C; ++c) fp[c] += f[c];
-            }
-            float xs = 0.f, xd = 0.f, xc[3] = {0.f, 0.f, 0.f};
-            {
-                lds_f32 *wh = weights_at(wb, OH);            // w_sigma, w_depth, W_color
+            for (int t = 0; t < MT; ++t) fp[t] = f[t];
+            product<false>(s_w[kMatO], n, g, o, fp);
+            zero4(x);
+            product<false>(s_w[kMatH], n, g, fp, x);
+            wave_order();
+            rows_store<C>(A, n, g, x);            // columns 0..4: the heads
+            wave_order();
+            if (lane < PPT) {
+                // one lane per pixel
+                const bool live = e_px < N;
+                float *row = A + lane * ROW;
+                const float4 x4 = *reinterpret_cast<const float4 *>(row);
+                const float xs = x4.x, xd = x4.y, xc[3] = {x4.z, x4.w, row[4]};
+                const float dco[3] = {cg.x, cg.y, cg.z}, dal = cg.w;
+                float dd_in = 0.f, da_in = 0.f;
+                float h[5];                       // d x_sigma, d x_depth, d x_color
 #pragma unroll
-                for (int c = 0; c < C; ++c) {
-                    xs = fmaf(fp[c], wh[c], xs);
-                    xd = fmaf(fp[c], wh[C + c], xd);
-                    xc[0] = fmaf(fp[c], wh[2 * C + c * 3 + 0], xc[0]);
-                    xc[1] = fmaf(fp[c], wh[2 * C + c * 3 + 1], xc[1]);
-                    xc[2] = fmaf(fp[c], wh[2 * C + c * 3 + 2], xc[2]);
+                for (int j = 0; j < 3; ++j) h[2 + j] = dco[j] * dsigm(xc[j]);
+                float th, dth;
+                tanh_grad(xd, th, dth);
+                if (p.mode == 0) {
+                    const float a_in = a_px, ac = fminf(fmaxf(a_in, 1e-6f), 1.0f - 1e-6f);
+                    h[0] = dal * dsigm(logf(ac * rcp(1.0f - ac)) + xs);
+                    if (a_in > 1e-6f && a_in < 1.0f - 1e-6f) da_in = h[0] * rcp(a_in * (1.0f - a_in));
+                    const float invd = rcp(d_px), disp = fmaf(kap, th, invd);
+                    h[1] = 0.f;
+                    if (disp > p.inv_far && disp < p.inv_near) {
+                        const float dn = rcp(disp);
+                        const float ddisp = -ddn * dn * dn;
+                        dd_in = -ddisp * invd * invd;
+                        h[1] = ddisp * kap * dth;
+                    }
+                } else {
+                    h[0] = dal * dsigm(xs);
+                    const float delta = ((float)(p.L - li) - 0.5f) * rcp((float)p.L);
+                    const float dn = rcp(fmaf(delta + half_l * th, band, p.inv_far));
+                    h[1] = -ddn * dn * dn * kap * dth;
                 }
+                if (live) p.d_alpha[e_px] = da_in;
+                const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
+                float4 *r4 = reinterpret_cast<float4 *>(row);
+                r4[0] = live ? make_float4(h[0], h[1], h[2], h[3]) : z4;
+                r4[1] = live ? make_float4(h[4], 0.f, 0.f, 0.f) : z4;
+                if constexpr (C == 16) r4[2] = r4[3] = z4;
+                row[C] = dd_in;
             }
-            float dco[3] = {0.f, 0.f, 0.f}, dal = 0.f, ddn = 0.f;
-            if (p.comp) {
-                const float4 cg = reinterpret_cast<const float4 *>(p.comp)[e];
-                dco[0] = cg.x;
-                dco[1] = cg.y;
-                dco[2] = cg.z;
-                dal = cg.w;
-            }
-            if (p.d_alpha_out) dal += p.d_alpha_out[e];
-            if (p.d_depth_out) ddn = p.d_depth_out[e];
-            // sigma'(z) = sigma(z) sigma(-z): the second factor is not taken as
-            // 1 - sigma(z), which loses its digits when sigma(z) is near one
-            float h[5];                                   // d x_sigma, d x_depth, d x_color
+            rows_live(B, fp);
+            wave_order();
+            outer_rows<C>(B, A, n, g, gH);
+            rows_load<C>(A, n, g, x);             // h
+            if (p.dF_out) load_vec(p.dF_out, dfp);
+            else zero4(dfp);
+            product<true>(s_w[kMatH], n, g, x, dfp);
+            f32x4 dov[MT], dob[MT];
+            zero4(dov);
+            product<true>(s_w[kMatO], n, g, dfp, dov);
+            wave_order();
+            rows_live(A, o);
+            rows_live(B, dfp);
+            wave_order();
+            outer_rows<C>(A, B, n, g, gO);
+            zero4(dob);
+            product<true>(s_w[kMatV], n, g, dov, dob);
+            float delta[MT];
 #pragma unroll
-            for (int j = 0; j < 3; ++j) h[2 + j] = dco[j] * sigm(xc[j]) * sigm(-xc[j]);
-            const float th = tanhf(xd);
-            if (p.mode == 0) {
-                const float a_in = p.alpha_in[e];
-                const float ac = fminf(fmaxf(a_in, 1e-6f), 1.0f - 1e-6f);
-                const float z = logf(ac / (1.0f - ac)) + xs;
-                h[0] = dal * sigm(z) * sigm(-z);
-                if (a_in > 1e-6f && a_in < 1.0f - 1e-6f) da_in = h[0] / (a_in * (1.0f - a_in));
-                const float disp = 1.0f / d + kap * th;
-                h[1] = 0.f;
-                if (disp > p.inv_far && disp < p.inv_near) {
-                    const float dn = 1.0f / disp;
-                    const float ddisp = -ddn * dn * dn;
-                    dd_in = -ddisp / (d * d);
-                    h[1] = ddisp * kap * (1.0f - th * th);
-                }
-            } else {
-                h[0] = dal * sigm(xs) * sigm(-xs);
-                const float delta = ((float)(p.L - li) - 0.5f) / (float)p.L;
-                const float dn = 1.0f / fmaf(delta + half_l * th, band, p.inv_far);
-                h[1] = -ddn * dn * dn * kap * (1.0f - th * th);
-            }
-            outer_accumulate<C, 5>(sa, sb, lane, fp, h, live, gH);
-            float dfp[C];
-            {
-                lds_f32 *wh = weights_at(wb, OH);
+            for (int t = 0; t < MT; ++t)
+                delta[t] = row_sum(fmaf(ob[t][0], dob[t][0], fmaf(ob[t][1], dob[t][1],
+                                   fmaf(ob[t][2], dob[t][2], ob[t][3] * dob[t][3]))));
+            wave_order();
+            rows_live(A, ob);
+            rows_live(B, dov);
+            wave_order();
+            outer_rows<C>(A, B, n, g, gV);
+            wave_order();
+            rows_store<C>(A, n, g, dob);
+            if (g == 0) {
 #pragma unroll
-                for (int c = 0; c < C; ++c) {
-                    float g = fmaf(wh[c], h[0], wh[C + c] * h[1]);
-                    g = fmaf(wh[2 * C + c * 3 + 0], h[2], g);
-                    g = fmaf(wh[2 * C + c * 3 + 1], h[3], g);
-                    g = fmaf(wh[2 * C + c * 3 + 2], h[4], g);
-                    dfp[c] = g;
-                }
+                for (int t = 0; t < MT; ++t) A[(16 * t + n) * ROW + C + 1] = delta[t];
             }
-            if (p.dF_out) {
-                float u[C];
-                load_vec<C>(p.dF_out, e, u);
-#pragma unroll
-                for (int c = 0; c < C; ++c) dfp[c] += u[c];
-            }
-            outer_accumulate<C, C>(sa, sb, lane, o, dfp, live, gO);
-            float dov[C];
-            mat_vec<C, C>(weights_at(wb, OO), dfp, dov);
-            if (live) store_vec<C>(p.dF, e, dfp);        // the residual path; RMSNorm term added below
-            outer_accumulate<C, C>(sa, sb, lane, ob, dov, live, gV);
-            mat_vec<C, C>(weights_at(wb, OV), dov, dob);
+            wave_order();
         }
-        float delta = 0.f;
-#pragma unroll
-        for (int c = 0; c < C; ++c) delta = fmaf(ob[c], dob[c], delta);
 
         // ---- pass 2 over the views: softmax adjoint, dI scatter, depth
         //      through the sample position.  ds_m = p_m dob + da_m q~
-        float sh[C];                                      // sum_m da_m s_m
-#pragma unroll
-        for (int c = 0; c < C; ++c) sh[c] = 0.f;
-#pragma unroll 1
-        for (int m = 0; m < p.V; ++m) {
-            Sample<C> S;
-            sample_view<C>(p, m, uc, vc, (double)d, S);
-            float s[C];
-            blend<C>(S, s);
-            float a = 0.f, sd = 0.f;
-#pragma unroll
-            for (int c = 0; c < C; ++c) {
-                a = fmaf(qt[c], s[c], a);
-                sd = fmaf(s[c], dob[c], sd);
-            }
-            const float pm = __expf(a - mx) * iz;
-            const float da = pm * (sd - delta);
-            const float w[4] = {(1.f - S.fx) * (1.f - S.fy), S.fx * (1.f - S.fy),
-                                (1.f - S.fx) * S.fy, S.fx * S.fy};
-            // ds goes straight to the wave's LDS slice (row of this lane),
-            // the tap offsets and weights beside it
-            float gX = 0.f, gY = 0.f;
-#pragma unroll
-            for (int c4 = 0; c4 < C / 4; ++c4) {
-                float d4[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int c = 4 * c4 + i;
-                    sh[c] = fmaf(da, s[c], sh[c]);
-                    const float ds = fmaf(pm, dob[c], da * qt[c]);
-                    d4[i] = ds;
-                    gX = fmaf(ds, (1.f - S.fy) * (S.t[1][c] - S.t[0][c]) + S.fy * (S.t[3][c] - S.t[2][c]), gX);
-                    gY = fmaf(ds, (1.f - S.fx) * (S.t[2][c] - S.t[0][c]) + S.fx * (S.t[3][c] - S.t[1][c]), gY);
+        {
+            const float4 dob = *reinterpret_cast<const float4 *>(row_ld + 4 * chunk);
+            const float dd0 = row_ld[C], delta = row_ld[C + 1];
+            float ddv = 0.f;
+            float4 sh = make_float4(0.f, 0.f, 0.f, 0.f);    // sum_m da_m s_m
+            run_views([&](const Taps &T, int m) {
+                const float4 s = blend(T);
+                const float a = KEEP ? logit[KEEP ? m : 0] : pix_sum<LPP>(dot4(qv, s));
+                const float sd = pix_sum<LPP>(dot4(s, dob));
+                const float pm = __expf(a - mx) * iz;
+                const float da = pm * (sd - delta);
+                sh.x = fmaf(da, s.x, sh.x);
+                sh.y = fmaf(da, s.y, sh.y);
+                sh.z = fmaf(da, s.z, sh.z);
+                sh.w = fmaf(da, s.w, sh.w);
+                const float4 ds = make_float4(fmaf(pm, dob.x, da * qv.x), fmaf(pm, dob.y, da * qv.y),
+                                              fmaf(pm, dob.z, da * qv.z), fmaf(pm, dob.w, da * qv.w));
+                const float fx = T.p.fx, fy = T.p.fy, ex = 1.f - fx, ey = 1.f - fy;
+                // along x: (1 - fy)(t10 - t00) + fy (t11 - t01), along y alike,
+                // as dot products of ds with the four taps
+                const float g00 = dot4(ds, T.t[0]), g10 = dot4(ds, T.t[1]);
+                const float g01 = dot4(ds, T.t[2]), g11 = dot4(ds, T.t[3]);
+                const float gX = fmaf(ey, g10 - g00, fy * (g11 - g01));
+                const float gY = fmaf(ex, g01 - g00, fx * (g11 - g10));
+                ddv = fmaf(gX, T.p.dx, fmaf(gY, T.p.dy, ddv));
+                if constexpr (SORT) {                        // scattered afterwards
+                    if (live_ld)
+                        __builtin_nontemporal_store(f32x4{ds.x, ds.y, ds.z, ds.w}, reinterpret_cast<f32x4 *>(
+                            p.ds + ((int64_t)m * p.N + e_ld) * C + 4 * chunk));
+                    return;
                 }
-                reinterpret_cast<float4 *>(sa + lane * C)[c4] = make_float4(d4[0], d4[1], d4[2], d4[3]);
-            }
-            if (S.ok) dd_in = fmaf(gX, S.dXdd, fmaf(gY, S.dYdd, dd_in));
+                // dI scatter: the ds rows and tap offsets to LDS, then every
+                // atomic instruction covers whole rows of C floats, a pixel's
+                // two taps of a row side by side
+                wave_order();
+                reinterpret_cast<float4 *>(B)[lane] = ds;
+                if (chunk == 0) {
+                    int4 *ow = reinterpret_cast<int4 *>(Sow + 4 * lp);
+                    ow[0] = make_int4(T.p.o[0], __float_as_int(ex * ey), T.p.o[1], __float_as_int(fx * ey));
+                    ow[1] = make_int4(T.p.o[2], __float_as_int(ex * fy), T.p.o[3], __float_as_int(fx * fy));
+                }
+                wave_order();
+                constexpr int PPI = 64 / (2 * C);            // pixels per instruction (one tap row)
+                const int c = lane % C, tx = (lane / C) & 1, pi = lane / (2 * C);
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                so[4 * lane + t] = (live && S.ok && S.in[t]) ? S.off[t] : -1;
-                sb[4 * lane + t] = w[t];
-            }
-            __syncthreads();
-            // dI scatter, channel-coalesced: one atomic instruction covers
-            // 64 / C whole (pixel, tap) rows of C consecutive floats instead
-            // of 64 scattered addresses
-            {
-                float *dI = p.dfeat[m];
-                constexpr int RPI = 64 / C;               // rows per instruction
-                const int c_l = lane % C, r_l = lane / C;
-#pragma unroll 2
-                for (int j = 0; j < C; ++j) {
-                    const int row = r_l + RPI * j;
-                    const float dsr = sa[row * C + c_l];
+                for (int j = 0; j < PPT / PPI; ++j) {
+                    const int px = PPI * j + pi;
+                    const float d1 = B[px * C + c];
 #pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        const int o = so[4 * row + t];
-                        if (o >= 0) unsafeAtomicAdd(dI + o + c_l, sb[4 * row + t] * dsr);
+                    for (int ty = 0; ty < 2; ++ty) {
+                        const int2 ow = Sow[4 * px + 2 * ty + tx];
+                        const float val = __int_as_float(ow.y) * d1;
+                        if constexpr (WIDE) {
+                            if (ow.x >= 0) unsafeAtomicAdd(p.dfeat[m] + (int64_t)ow.x * 4 + c, val);
+                        } else {
+                            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                                p.dfeat[m], 0, p.fH[m] * p.fW[m] * C * 4, 0x00020000);
+                            __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(val, rs, ow.x + 4 * c, 0, 0);
+                        }
                     }
                 }
-            }
-            __syncthreads();
+            });
+            wave_order();
+            *reinterpret_cast<float4 *>(B + lp * ROW + 4 * chunk) = sh;
+            wave_order();
+            ddv = pix_sum<LPP>(ddv);
+            if (chunk == 0 && live_ld) p.d_depth[e_ld] = dd0 + ddv;
         }
 
         // ---- dq = scale W_k^T sh; key and query weight gradients; RMSNorm
         //      adjoint dF += (dxn - xn (xn . dxn) / C) / r
         {
-            float xn[C], q[C], dq[C];
-            const float r = load_normalised<C>(p.F_in, e, xn);
-            vec_mat<C, C>(xn, weights_at(wb, OQ), q);
+            f32x4 sh[MT], x[MT], dq[MT], dx[MT];
+            rows_load<C>(B, n, g, sh);
 #pragma unroll
-            for (int c = 0; c < C; ++c) sh[c] *= scale;
-            vec_mat<C, C>(sh, weights_at(wb, OK), dq);
-            outer_accumulate<C, C>(sa, sb, lane, sh, q, live, gK);
-            outer_accumulate<C, C>(sa, sb, lane, xn, dq, live, gQ);
-            float dxn[C], xdx = 0.f;
-            mat_vec<C, C>(weights_at(wb, OQ), dq, dxn);
+            for (int t = 0; t < MT; ++t)
 #pragma unroll
-            for (int c = 0; c < C; ++c) xdx = fmaf(xn[c], dxn[c], xdx);
-            if (live) {
-                const float ir = 1.0f / r, k = xdx * (1.0f / (float)C);
-                float g[C];
-                load_vec<C>(p.dF, e, g);
+                for (int i = 0; i < 4; ++i) sh[t][i] *= p.scale;
+            normalised(x);
+            zero4(dq);
+            product<false>(s_w[kMatK], n, g, sh, dq);
+            wave_order();
+            rows_live(A, sh);
+            rows_live(B, q);
+            wave_order();
+            outer_rows<C>(A, B, n, g, gK);
+            zero4(dx);
+            product<true>(s_w[kMatQ], n, g, dq, dx);
 #pragma unroll
-                for (int c = 0; c < C; ++c) g[c] += (dxn[c] - xn[c] * k) * ir;
-                store_vec<C>(p.dF, e, g);
-                p.d_depth[e] = dd_in;
-                p.d_alpha[e] = da_in;
+            for (int t = 0; t < MT; ++t) {
+                const float k = row_sum(fmaf(x[t][0], dx[t][0], fmaf(x[t][1], dx[t][1],
+                                        fmaf(x[t][2], dx[t][2], x[t][3] * dx[t][3])))) * (1.0f / (float)C);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) dfp[t][i] += (dx[t][i] - x[t][i] * k) * ir[t];
+                const int32_t e = base + 16 * t + n;
+                if (has_ch && e < N)
+                    __builtin_nontemporal_store(dfp[t], reinterpret_cast<f32x4 *>(p.dF + (int64_t)e * C + 4 * g));
             }
+            wave_order();
+            rows_live(A, x);
+            rows_live(B, dq);
+            wave_order();
+            outer_rows<C>(A, B, n, g, gQ);
+            wave_order();
         }
     }
 
@@ -675,16 +880,52 @@ hipError_t launch_composite_backward(const CompBwdParams &p, hipStream_t s) {
     return hipGetLastError();
 }
 
+hipError_t launch_scatter(const ViewsParams &p, const ScatterParams &sp, int C, hipStream_t s);
+
+// The maps' tiles, the cameras and the workspace of the sorted scatter.
+static void scatter_params(const BwdParams &p, ViewsParams &v, ScatterParams &sp) {
+    v.V = p.V;
+    v.L = p.L;
+    v.H = p.H;
+    v.W = p.W;
+    v.N = p.N;
+    v.depth = p.depth_in;
+    v.tw = 1 << kVbLog2Tw;
+    v.th = kScatterTh;
+    while ((1 << v.log2_th) < v.th) ++v.log2_th;
+    for (int m = 0; m < p.V; ++m) {
+        for (int k = 0; k < 12; ++k) v.cam[m][k] = p.camd[m][k];
+        v.vH[m] = p.fH[m];
+        v.vW[m] = p.fW[m];
+        v.ntx[m] = (p.fW[m] + v.tw - 1) / v.tw;
+        v.nty[m] = (p.fH[m] + v.th - 1) / v.th;
+        v.tbase[m + 1] = v.tbase[m] + v.ntx[m] * v.nty[m];
+        sp.dfeat[m] = p.dfeat[m];
+    }
+    const int tiles = v.tbase[p.V];
+    v.nbins = 4 * tiles;
+    v.cursor = p.bins;
+    v.total = p.bins + v.nbins;
+    v.start = v.total + 4;
+    v.rec = reinterpret_cast<int32_t *>(v.start + ((tiles + 3) & ~3));
+    v.div_hw = make_fast_div((uint32_t)(p.H * p.W));
+    v.div_w = make_fast_div((uint32_t)p.W);
+    sp.ds = p.ds;
+}
+
 hipError_t launch_update_fuse_backward(const BwdParams &p, hipStream_t s) {
     if (p.C != 8 && p.C != 16) return hipErrorInvalidValue;
-    int64_t zero_blocks = 1;
-    for (int m = 0; m < p.V; ++m) {
-        const int64_t n4 = (int64_t)p.fH[m] * p.fW[m] * p.C / 4;
-        zero_blocks = std::max<int64_t>(zero_blocks, std::min<int64_t>(1024, (n4 + kBlock - 1) / kBlock));
+    hipError_t e;
+    if (p.ds == nullptr) {
+        int64_t zero_blocks = 1;
+        for (int m = 0; m < p.V; ++m) {
+            const int64_t n4 = (int64_t)p.fH[m] * p.fW[m] * p.C / 4;
+            zero_blocks = std::max<int64_t>(zero_blocks, std::min<int64_t>(1024, (n4 + kBlock - 1) / kBlock));
+        }
+        hipLaunchKernelGGL(k_zero_maps, dim3((unsigned)zero_blocks, (unsigned)p.V), dim3(kBlock), 0, s, p);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(k_zero_maps, dim3((unsigned)zero_blocks, (unsigned)p.V), dim3(kBlock), 0, s, p);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
     if (p.comp != nullptr) {
         const int64_t npix = (int64_t)p.H * p.W;
         hipLaunchKernelGGL(k_composite_adjoint, dim3((unsigned)((npix + kBlock - 1) / kBlock)),
@@ -692,12 +933,25 @@ hipError_t launch_update_fuse_backward(const BwdParams &p, hipStream_t s) {
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    if (p.C == 8)
-        hipLaunchKernelGGL((k_uf_backward<8>), dim3((unsigned)p.blocks), dim3(kBlock), 0, s, p);
-    else
-        hipLaunchKernelGGL((k_uf_backward<16>), dim3((unsigned)p.blocks), dim3(kBlock), 0, s, p);
+    const dim3 g((unsigned)p.blocks), b(kBlock);
+    auto main_pass = [&](auto c) {
+        constexpr int C = decltype(c)::value;
+        if (p.ds != nullptr && p.V <= kKeep) hipLaunchKernelGGL((k_uf_backward<C, kSortKeep>), g, b, 0, s, p);
+        else if (p.ds != nullptr) hipLaunchKernelGGL((k_uf_backward<C, kSort>), g, b, 0, s, p);
+        else if (p.wide) hipLaunchKernelGGL((k_uf_backward<C, kWide>), g, b, 0, s, p);
+        else hipLaunchKernelGGL((k_uf_backward<C, kNarrow>), g, b, 0, s, p);
+    };
+    if (p.C == 8) main_pass(std::integral_constant<int, 8>{});
+    else main_pass(std::integral_constant<int, 16>{});
     e = hipGetLastError();
     if (e != hipSuccess) return e;
+    if (p.ds != nullptr) {
+        ViewsParams v{};
+        ScatterParams sp{};
+        scatter_params(p, v, sp);
+        if ((e = launch_vbin(v, s)) != hipSuccess) return e;
+        if ((e = launch_scatter(v, sp, p.C, s)) != hipSuccess) return e;
+    }
     hipLaunchKernelGGL(k_reduce_wgrad, dim3(kGradTiles * kGradTileElems / 16), dim3(kBlock), 0, s, p);
     return hipGetLastError();
 }

@@ -24,6 +24,7 @@
 #include <type_traits>
 
 #include "uf_params.h"
+#include "vbin.h"
 
 // multiply-adds fused within an expression only: the binned form's counting
 // and writing passes evaluate the same reprojection and must round it alike
@@ -178,65 +179,9 @@ constexpr int kVbThreads = 512;                 // counting and writing workgrou
 constexpr int kVbHashBits = 11;
 constexpr int kVbHash = 1 << kVbHashBits;       // LDS hash slots
 constexpr int kVbProbes = 16;                   // a key that finds no slot goes to global memory
-constexpr int kVbLog2Tw = 5;                    // tiles are 32 view pixels wide
 constexpr int kVbTileThreads = 512;
 constexpr float kVbFix = 4294967296.0f;         // fixed-point scale of the tile sums, 2^32
 constexpr float kVbUnfix = 2.3283064365386963e-10f;   // 2^-32
-
-// 1 / x in double: the hardware reciprocal refined by one Newton step (its
-// relative error squares, far below what the coordinates need).  The binned
-// passes all reproject through it, so they agree bit for bit.
-__device__ inline double recip_d(double x) {
-    const double r = __builtin_amdgcn_rcp(x);
-    return fma(r, fma(-x, r, 1.0), r);
-}
-
-// The footprint of layer-pixel q in view m: its layer, the view pixel
-// (ix, iy) of its top left tap and the fractions; false when no tap lies in
-// the view.  The reprojection of k_splat (reciprocals as above); a sample
-// with fxc <= -1 or fxc >= vW (likewise y) has no tap inside.  Every binned
-// pass calls it: the tile pass recomputes a record's footprint from the
-// layer-pixel index the write pass stored.  All three passes are bound by
-// VALU instructions, so the index divisions are multiplications.
-// (The binned form runs only while V L H W < 2^31, so a layer-pixel index
-// and its divisions fit 32 bits.)
-__device__ inline uint32_t fast_div(uint32_t n, const FastDiv &f) {
-    const uint32_t q = __umulhi(n, f.mul) >> f.shift;
-    return f.d == 1u ? n : q;
-}
-
-__device__ inline bool vbin_footprint(const ViewsParams &p, int m, int q, float depth, float &fx,
-                                      float &fy, int &ix, int &iy, int &l) {
-    const uint32_t uq = (uint32_t)q, ul = fast_div(uq, p.div_hw);
-    const uint32_t r = uq - ul * p.div_hw.d, uy = fast_div(r, p.div_w);
-    l = (int)ul;
-    const int y = (int)uy, x = (int)(r - uy * p.div_w.d);
-    const double u = (double)x + 0.5, v = (double)y + 0.5;
-    const double invd = recip_d((double)depth);
-    const double *A = p.cam[m];
-    const int vw = p.vW[m], vh = p.vH[m];
-    const double pz = fma(A[6], u, fma(A[7], v, fma(A[11], invd, A[8])));
-    const double qx = fma(A[0], u, fma(A[1], v, fma(A[9], invd, A[2])));
-    const double qy = fma(A[3], u, fma(A[4], v, fma(A[10], invd, A[5])));
-    const double rz = recip_d(pz);
-    const double fxc = qx * rz - 0.5, fyc = qy * rz - 0.5;
-    const bool ok = (pz > 1e-6) && (fxc > -1.0) && (fxc < (double)vw) && (fyc > -1.0) &&
-                    (fyc < (double)vh);
-    const double xf = floor(fxc), yf = floor(fyc);
-    fx = (float)(fxc - xf);
-    fy = (float)(fyc - yf);
-    ix = ok ? (int)xf : 0;
-    iy = ok ? (int)yf : 0;
-    return ok;
-}
-
-// The bin of a footprint (the tile sides are powers of two).
-__device__ inline int vbin_bin(const ViewsParams &p, int m, int ix, int iy) {
-    const int tx = min((ix + 1) >> kVbLog2Tw, p.ntx[m] - 1);
-    const int ty = min((iy + 1) >> p.log2_th, p.nty[m] - 1);
-    const int cls = (ix == (tx << kVbLog2Tw) - 1 ? 1 : 0) | (iy == (ty << p.log2_th) - 1 ? 2 : 0);
-    return 4 * (p.tbase[m] + ty * p.ntx[m] + tx) + cls;
-}
 
 // Slot of key b in the workgroup's hash table (linear probing), or -1 when
 // its first kVbProbes slots hold other keys: such a record is counted (and
@@ -250,14 +195,6 @@ __device__ inline int vbin_slot(int *hkey, int b) {
         h = (h + 1) & (kVbHash - 1);
     }
     return -1;
-}
-
-// XCD-aware order: workgroups are dispatched round-robin over the 8 XCDs;
-// workgroup i takes item (i % 8) * per + i / 8, so each XCD walks one
-// contiguous range.
-__device__ inline int xcd_order(int i, int n) {
-    const int xcd = i & 7, loc = i >> 3, q8 = n >> 3, rem = n & 7;
-    return (xcd < rem) ? xcd * (q8 + 1) + loc : rem * (q8 + 1) + (xcd - rem) * q8 + loc;
 }
 
 // The workgroup's view and first layer-pixel, views slowest.  The chunks in
@@ -431,40 +368,14 @@ __global__ void __launch_bounds__(kVbTileThreads) k_vbin_tile(const ViewsParams 
             for (int c = 0; c < 4; ++c) tacc[c * plane + i] = 0ull;
     }
     __syncthreads();
-    // the record ranges: own bins, then the crossing bins of the tiles to the
-    // right (left-crossing), below (top-crossing) and below right (both)
-    uint32_t rs[5] = {0u, 0u, 0u, 0u, 0u}, re[5] = {0u, 0u, 0u, 0u, 0u};
-    {
-        // a tile's bins lie one after the other, and the write pass has left
-        // every cursor at its bin's end
-        auto range = [&](int j, int tile, int first, int last) {
-            rs[j] = first == 0 ? p.start[tile] : p.cursor[4 * tile + first - 1];
-            re[j] = p.cursor[4 * tile + last];
-        };
-        const int right = tx + 1 < ntx ? 1 : 0, below = ty + 1 < nty ? ntx : 0;
-        range(0, t, 0, 3);
-        if (right) {
-            range(1, t + 1, 1, 1);
-            range(2, t + 1, 3, 3);
-        }
-        if (below) range(3, t + ntx, 2, 3);
-        if (right && below) range(4, t + ntx + 1, 3, 3);
-    }
-    // the five ranges as one index space
-    uint32_t cum[6];
-    cum[0] = 0u;
-#pragma unroll
-    for (int j = 0; j < 5; ++j) cum[j + 1] = cum[j] + (re[j] - rs[j]);
-    const uint32_t total = cum[5];
+    const VbinRanges ranges = vbin_ranges(p, t, tx, ty, ntx, nty);
+    const uint32_t total = ranges.cum[5];
     for (uint32_t k = threadIdx.x; k < total; k += (uint32_t)kVbTileThreads) {
-        uint32_t o = rs[0];
-#pragma unroll
-        for (int j = 1; j < 5; ++j) o = (k >= cum[j]) ? rs[j] - cum[j] : o;
         // the record is the layer-pixel's index: its footprint is recomputed
         // by the same function the binning passes ran (so it is the one they
         // binned) and its payload read from the LDM; an index out of range is
         // only a record never written
-        const int q = p.rec[o + k];
+        const int q = p.rec[ranges.at(k)];
         if ((unsigned)q >= (unsigned)p.N) continue;
         const float d = p.depth[q];
         const float *c = p.color + (int64_t)q * 3;
@@ -524,27 +435,32 @@ __global__ void __launch_bounds__(kVbTileThreads) k_vbin_tile(const ViewsParams 
 
 }  // namespace
 
+hipError_t launch_vbin(const ViewsParams &p, hipStream_t s) {
+    hipLaunchKernelGGL(k_vbin_zero, dim3(p.nbins / 256 + 1), dim3(256), 0, s, p);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    // layer-pixels per thread: as many as leave ~8 workgroups per CU
+    const int64_t per = p.N * p.V / ((int64_t)kVbThreads * 2048);
+    auto passes = [&](auto kpt) {
+        constexpr int K = decltype(kpt)::value;
+        const int64_t cpv = (p.N + K * kVbThreads - 1) / (K * kVbThreads);
+        const dim3 g((unsigned)(cpv * p.V)), b(kVbThreads);
+        hipLaunchKernelGGL(k_vbin_count<K>, g, b, 0, s, p);
+        hipError_t pe = hipGetLastError();
+        if (pe != hipSuccess) return pe;
+        hipLaunchKernelGGL(k_vbin_scan, dim3((p.nbins / 4 + 255) / 256), dim3(256), 0, s, p);
+        if ((pe = hipGetLastError()) != hipSuccess) return pe;
+        hipLaunchKernelGGL(k_vbin_write<K>, g, b, 0, s, p);
+        return hipGetLastError();
+    };
+    e = per >= 16 ? passes(std::integral_constant<int, 16>{})
+      : per >= 4 ? passes(std::integral_constant<int, 4>{}) : passes(std::integral_constant<int, 1>{});
+    return e;
+}
+
 hipError_t launch_render_to_views(const ViewsParams &p, hipStream_t s) {
     if (p.binned) {
-        hipLaunchKernelGGL(k_vbin_zero, dim3(p.nbins / 256 + 1), dim3(256), 0, s, p);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        // layer-pixels per thread: as many as leave ~8 workgroups per CU
-        const int64_t per = p.N * p.V / ((int64_t)kVbThreads * 2048);
-        auto passes = [&](auto kpt) {
-            constexpr int K = decltype(kpt)::value;
-            const int64_t cpv = (p.N + K * kVbThreads - 1) / (K * kVbThreads);
-            const dim3 g((unsigned)(cpv * p.V)), b(kVbThreads);
-            hipLaunchKernelGGL(k_vbin_count<K>, g, b, 0, s, p);
-            hipError_t pe = hipGetLastError();
-            if (pe != hipSuccess) return pe;
-            hipLaunchKernelGGL(k_vbin_scan, dim3((p.nbins / 4 + 255) / 256), dim3(256), 0, s, p);
-            if ((pe = hipGetLastError()) != hipSuccess) return pe;
-            hipLaunchKernelGGL(k_vbin_write<K>, g, b, 0, s, p);
-            return hipGetLastError();
-        };
-        e = per >= 16 ? passes(std::integral_constant<int, 16>{})
-          : per >= 4 ? passes(std::integral_constant<int, 4>{}) : passes(std::integral_constant<int, 1>{});
+        hipError_t e = launch_vbin(p, s);
         if (e != hipSuccess) return e;
         // the distance of the sums' planes, fixed where it can be
         const int tile_sums = p.L * p.th * p.tw;

@@ -106,6 +106,9 @@ namespace qk {
 // W_q, W_k, W_v, W_o, then the decode heads (columns sigma, depth, r, g, b).
 constexpr int kGradTiles = 5;
 constexpr int kGradTileElems = 256;
+// Workgroups per compute unit (waves per SIMD) of its persistent kernel: three,
+// or two where the taps of up to kBwdKeep views stay in registers.
+constexpr int kBwdKeep = 4, kBwdWaves = 3, kBwdWavesKeep = 2;
 
 // Adjoint of one float32 Update & Fuse step (and of the composite).
 struct BwdParams {
@@ -130,6 +133,10 @@ struct BwdParams {
     int32_t V, L, H, W, C;
     int64_t N;          // L * H * W
     int32_t blocks;     // workgroups of the per-layer-pixel kernel
+    FastDiv div_w, div_l;    // by W and by L
+    int32_t wide;       // a feature map of 2 GiB or more
+    float *ds;          // [V][N][C] sample gradients of the sorted scatter, or NULL (atomics)
+    uint32_t *bins;     // its binning workspace (scatter_bin_words)
     float inv_near, inv_far, scale;
     int32_t mode;
 };
@@ -217,6 +224,25 @@ struct ViewsParams {
     int32_t log2_th;                // th is a power of two (tw is 32)
     int32_t *rec;                   // [V N]: the layer-pixel index of each record
 };
+
+}  // namespace qk
+
+namespace qk {
+
+// Sorted scatter of the feature-map gradients: tiles of 32 x kScatterTh map
+// pixels, binned like the render to the views (words of its workspace: bin
+// cursors, total, tile starts, records).
+constexpr int kScatterTh = 4;
+struct ScatterParams {
+    const float *ds;                // [V][N][C]
+    float *dfeat[kMaxViews];        // [fH][fW][C], written
+};
+inline int64_t scatter_tiles(int32_t fH, int32_t fW) {
+    return (int64_t)((fW + 31) / 32) * ((fH + kScatterTh - 1) / kScatterTh);
+}
+inline int64_t scatter_bin_words(int64_t tiles, int64_t records) {
+    return 4 * tiles + 4 + ((tiles + 3) & ~(int64_t)3) + records;
+}
 
 }  // namespace qk
 
