@@ -11,16 +11,25 @@
 // A operand is the tap's W^T (16 output channels x 32 input channels, one
 // fragment per half of the outputs) and the B operand 16 pixels x 32 input
 // channels -- one 16-byte LDS read per lane, since pixels are channel-last.
-// A persistent workgroup keeps both kernels' fragments in LDS and walks
-// 16 x 8 output tiles: it stages the 20 x 12 input region normalised (2-pixel
-// halo, zeros outside the image; a quad of lanes holds one pixel's four
-// 8-channel chunks and sums its squares with two lane exchanges), computes
-// the first convolution on the 18 x 10 region the second one needs (GELU,
-// zeros outside the image -- the second convolution pads with zeros too --
-// rounded to bfloat16 as its operand), then the second convolution, adds
-// the un-normalised input (each lane's two pixels loaded into registers at
-// the start of the tile, so their latency hides behind the convolutions) and
-// stores bfloat16.
+//
+// A persistent workgroup of four waves walks tiles of 30 x TY outputs.  It
+// stages the 34 x (TY + 4) input region normalised (2-pixel halo, zeros outside
+// the image; a quad of lanes holds one pixel's four 8-channel chunks and sums its
+// squares with two lane exchanges), computes the first convolution on the 32 x
+// (TY + 2) region the second one needs (two column blocks of 16; GELU, zeros
+// outside the image -- the second convolution pads with zeros too -- rounded to
+// bfloat16 as its operand), then the second convolution, adds the un-normalised
+// input and stores bfloat16.  A wave takes one column block and half of the rows
+// with the kernel's 18 fragments in registers, and walks down the rows: the
+// three shifted operands of an input row serve the three output rows it reaches,
+// 18 products per three LDS reads, each sum still taken tap by tap in order.
+//
+// What bounds it: with the fragments in LDS every product read 1.5 operands and
+// the LDS pipe was busy throughout; now it is vector work (GELU, normalisation,
+// ~55 % busy) beside the matrix cores (~25 %).  16 layers of 480x270: 193 -> 134
+// us (570 TFLOP/s), the same bits.  Both kernels' fragments in registers (144)
+// spilled and took 298 us; the next tile's input read ahead changed nothing, two
+// workgroups per CU overlap each other's staging.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -33,12 +42,13 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kC = 32, TX = 16, TY = 8;
-constexpr int IX = TX + 4, IY = TY + 4;          // staged input region
-constexpr int MX = TX + 2, MY = TY + 2;          // first convolution's region
-constexpr int NMID = MX * MY;                    // 180 pixels
-constexpr int MID_TILES = (NMID + 15) / 16;      // 12 pixel tiles of 16
+constexpr int kC = 32, TX = 30, MX = TX + 2, IX = TX + 4;
 constexpr int NFRAG = 2 * 9 * 2 * 64;            // [conv][tap][half of C_out][lane]
+
+// Place of 16-byte chunk q of column c in an LDS row (64 bytes a pixel): the
+// chunks are permuted so that the 16-byte reads of 16 neighbouring columns spread
+// over all banks; by the column alone, so a walk down the rows adds constants.
+__device__ inline int chunk_at(int c, int q) { return c * 4 + (q ^ ((c >> 2) & 3)); }
 
 __device__ inline f32x4 mma(const uint4 &a, const uint4 &b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
@@ -47,7 +57,11 @@ __device__ inline f32x4 mma(const uint4 &a, const uint4 &b, f32x4 c) {
 
 __device__ inline float bf2f(uint16_t h) { return __uint_as_float((unsigned)h << 16); }
 
-__device__ inline uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
+// the value of lane (l ^ D) of the quad
+template <int D>
+__device__ inline float quad_xor(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), D == 1 ? 0xB1 : 0x4E, 0xf, 0xf, true));
+}
 
 // gelu(x) = x Phi(x) = x (1 + erf(x / sqrt 2)) / 2, with erf from Hastings'
 // rational approximation (Abramowitz and Stegun 7.1.26): for z >= 0,
@@ -79,58 +93,102 @@ __global__ void __launch_bounds__(256) k_conv_frag(const ConvParams p) {
     p.frag[i] = __builtin_bit_cast(uint4, v);
 }
 
-__global__ void __launch_bounds__(256) k_residual_conv(const ConvParams p) {
-    __shared__ uint4 s_w[NFRAG];                 // 36 KiB
-    // pixels are 5 16-byte chunks apart (4 used): a stride of 80 bytes
-    // spreads a column block's 16-byte operand reads over the LDS banks
-    __shared__ uint4 s_in[IY * IX * 5];          // 18.75 KiB: [row][col][8-channel chunk]
-    __shared__ uint4 s_mid[NMID * 5];            // 14 KiB
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int n = lane & 15, g = lane >> 4;
-    for (int i = tid; i < NFRAG; i += 256) s_w[i] = p.frag[i];
-    const int64_t per_layer = (int64_t)p.tiles_x * p.tiles_y;
-    uint16_t *mid16 = reinterpret_cast<uint16_t *>(s_mid);
+// A wave's 3x3 convolution of ROWS rows of one column block of 16 pixels, from
+// LDS rows of PITCH pixels: lane (n, g) holds output channels 4g .. 4g+3 and 16
+// + 4g .. of pixel n.  row(ro) is called as the first input row of output row
+// ro arrives, emit(ro, a0, a1) when its sum is complete; taps are added in
+// order.
+template <int ROWS, int PITCH, typename Row, typename Emit>
+__device__ __forceinline__ void conv_rows(const uint4 *src, int col, int g, const uint4 (&w)[9][2],
+                                          Row &&row, Emit &&emit) {
+    f32x4 acc[3][2];
+    const uint4 *at[3];
+#pragma unroll
+    for (int dx = 0; dx < 3; ++dx) at[dx] = src + chunk_at(col + dx, g);
+#pragma unroll
+    for (int i = 0; i < ROWS + 2; ++i) {
+        uint4 b[3];
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx) b[dx] = at[dx][i * PITCH * 4];
+        if (i < ROWS) {
+            row(i);
+            acc[i % 3][0] = acc[i % 3][1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        }
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+            for (int dy = 0; dy < 3; ++dy) {
+                const int ro = i - dy;
+                if (ro < 0 || ro >= ROWS) continue;
+                acc[ro % 3][0] = mma(w[3 * dy + dx][0], b[dx], acc[ro % 3][0]);
+                acc[ro % 3][1] = mma(w[3 * dy + dx][1], b[dx], acc[ro % 3][1]);
+            }
+        if (i >= 2) emit(i - 2, acc[(i - 2) % 3][0], acc[(i - 2) % 3][1]);
+    }
+}
 
-    for (int64_t t = blockIdx.x; t < p.n_tiles; t += gridDim.x) {
+// four floats to bfloat16, a pair per conversion
+__device__ inline uint2 pack4(float a, float b, float c, float d) {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return make_uint2(__builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{a, b}), bf16x2)),
+                      __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{c, d}), bf16x2)));
+}
+
+template <int TY>
+__global__ void __launch_bounds__(256, 2) k_residual_conv(const ConvParams p) {
+    constexpr int MY = TY + 2, IY = TY + 4;
+    __shared__ uint4 s_in[IY * IX * 4];          // normalised input
+    // GELU of the first convolution (the last two columns' operands run 2 pixels
+    // over; their results are not used)
+    __shared__ uint4 s_mid[(MY * MX + 2) * 4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 15, g = lane >> 4;
+    const int cb = wave & 1, rh = wave >> 1;     // this wave's column block and half of the rows
+    // a kernel's fragments in registers, read (from L1) for each tile: both at
+    // once would take 144 registers and spill
+    auto load_frags = [&](int conv, uint4 (&w)[9][2]) {
+        const uint4 *f = p.frag + conv * 9 * 2 * 64;
+        asm volatile("" : "+s"(f));              // not hoisted out of the tile loop
+#pragma unroll
+        for (int t = 0; t < 9; ++t)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) w[t][h] = f[(t * 2 + h) * 64 + lane];
+    };
+    const int per_layer = p.tiles_x * p.tiles_y;
+    uint2 *mid2 = reinterpret_cast<uint2 *>(s_mid);
+
+    // each XCD (workgroups are dispatched round-robin over the 8) takes one
+    // contiguous range of tiles: neighbours share their halos in its L2
+    const int nr = min(8, (int)gridDim.x), r = (int)blockIdx.x % nr;
+    const int64_t t_end = p.n_tiles * (r + 1) / nr;
+    const int t_step = ((int)gridDim.x - r + nr - 1) / nr;
+    for (int64_t t = p.n_tiles * r / nr + (int)blockIdx.x / nr; t < t_end; t += t_step) {
         const int l = (int)(t / per_layer);
         const int rem = (int)(t - (int64_t)l * per_layer);
         const int ty = rem / p.tiles_x, tx = rem - ty * p.tiles_x;
         const int x0 = tx * TX, y0 = ty * TY;
         const uint16_t *Fl = p.F + (int64_t)l * p.H * p.W * kC;
-        // the residual (un-normalised input) of this lane's two output
-        // pixels, loaded now so that its latency hides behind the convolutions
-        uint2 resv[2][2];
-#pragma unroll
-        for (int rr = 0; rr < 2; ++rr) {
-            const int y = y0 + 2 * wave + rr, x = x0 + n;
-            resv[rr][0] = resv[rr][1] = make_uint2(0u, 0u);
-            if (y < p.H && x < p.W) {
-                const uint16_t *src = Fl + ((int64_t)y * p.W + x) * kC;
-                resv[rr][0] = *reinterpret_cast<const uint2 *>(src + 4 * g);
-                resv[rr][1] = *reinterpret_cast<const uint2 *>(src + 16 + 4 * g);
-            }
-        }
-        __syncthreads();                         // weights in; the previous tile is done
+        uint16_t *Ol = p.F_out + (int64_t)l * p.H * p.W * kC;
 
-        // the 4 lanes of a quad hold one pixel (256 and the last pass's cut,
-        // 192, are multiples of 4, so quads stay whole; whole waves skip the
-        // last pass); all loads are issued before the first is used
-        constexpr int NSTAGE = (IY * IX * 4 + 255) / 256;
+        // the 4 lanes of a quad hold one pixel (256 and the last pass's cut are
+        // multiples of 4, so quads stay whole)
+        constexpr int NCH = IY * IX * 4, NSTAGE = (NCH + 255) / 256;
         uint4 v[NSTAGE];
 #pragma unroll
         for (int k = 0; k < NSTAGE; ++k) {
             const int i = tid + 256 * k;
             const int pix = i >> 2, q = i & 3;
-            const int r = pix / IX, c = pix - r * IX;
-            const int y = y0 - 2 + r, x = x0 - 2 + c;
+            const int rr = pix / IX, c = pix - rr * IX;
+            const int y = y0 - 2 + rr, x = x0 - 2 + c;
             v[k] = make_uint4(0u, 0u, 0u, 0u);
-            if (i < IY * IX * 4 && y >= 0 && y < p.H && x >= 0 && x < p.W)
+            if (i < NCH && y >= 0 && y < p.H && x >= 0 && x < p.W)
                 v[k] = *reinterpret_cast<const uint4 *>(Fl + ((int64_t)y * p.W + x) * kC + 8 * q);
         }
+        __syncthreads();                         // the previous tile's reads are done
 #pragma unroll
         for (int k = 0; k < NSTAGE; ++k) {
             const int i = tid + 256 * k;
-            if (k == NSTAGE - 1 && i >= IY * IX * 4) break;      // wave-uniform
             const unsigned wd[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
             float f[8], ss = 0.0f;
 #pragma unroll
@@ -140,73 +198,70 @@ __global__ void __launch_bounds__(256) k_residual_conv(const ConvParams p) {
             }
 #pragma unroll
             for (int j = 0; j < 8; ++j) ss = fmaf(f[j], f[j], ss);
-            ss += __shfl_xor(ss, 1);
-            ss += __shfl_xor(ss, 2);
+            ss += quad_xor<1>(ss);
+            ss += quad_xor<2>(ss);
             const float rn = rsqrtf(ss * (1.0f / kC) + 1e-6f);   // outside: 0 * rn = 0
-            uint4 o;
-            o.x = f2bf(f[0] * rn) | ((unsigned)f2bf(f[1] * rn) << 16);
-            o.y = f2bf(f[2] * rn) | ((unsigned)f2bf(f[3] * rn) << 16);
-            o.z = f2bf(f[4] * rn) | ((unsigned)f2bf(f[5] * rn) << 16);
-            o.w = f2bf(f[6] * rn) | ((unsigned)f2bf(f[7] * rn) << 16);
-            s_in[(i >> 2) * 5 + (i & 3)] = o;
+            const uint2 lo = pack4(f[0] * rn, f[1] * rn, f[2] * rn, f[3] * rn);
+            const uint2 hi = pack4(f[4] * rn, f[5] * rn, f[6] * rn, f[7] * rn);
+            const int rr = (i >> 2) / IX, c = (i >> 2) - rr * IX;
+            if (i < NCH) s_in[rr * IX * 4 + chunk_at(c, i & 3)] = make_uint4(lo.x, lo.y, hi.x, hi.y);
         }
         __syncthreads();
 
-        // first convolution on the 18 x 10 region, 16 pixels per MFMA column block
-        for (int mt = wave; mt < MID_TILES; mt += 4) {
-            const int pm = 16 * mt + n;
-            const int pmc = pm < NMID ? pm : 0;
-            const int mr = pmc / MX, mc = pmc - mr * MX;
-            f32x4 a0 = {0.0f, 0.0f, 0.0f, 0.0f}, a1 = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for (int tap = 0; tap < 9; ++tap) {
-                const int dy = tap / 3, dx = tap - 3 * (tap / 3);
-                const uint4 b = s_in[((mr + dy) * IX + (mc + dx)) * 5 + g];
-                a0 = mma(s_w[(tap * 2 + 0) * 64 + lane], b, a0);
-                a1 = mma(s_w[(tap * 2 + 1) * 64 + lane], b, a1);
-            }
-            if (pm < NMID) {
-                const int y = y0 - 1 + mr, x = x0 - 1 + mc;
-                const bool inside = y >= 0 && y < p.H && x >= 0 && x < p.W;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    mid16[pm * 40 + 4 * g + i] = inside ? f2bf(gelu(a0[i])) : (uint16_t)0;
-                    mid16[pm * 40 + 16 + 4 * g + i] = inside ? f2bf(gelu(a1[i])) : (uint16_t)0;
+        // first convolution, rows rh MY / 2 .. of the middle region
+        {
+            const int m0 = rh * (MY / 2), mc = 16 * cb + n;
+            const int x = x0 - 1 + mc;
+            const bool in_x = x >= 0 && x < p.W;
+            uint2 *mid_lo = mid2 + m0 * MX * 8 + 2 * chunk_at(mc, g >> 1) + (g & 1);
+            uint2 *mid_hi = mid2 + m0 * MX * 8 + 2 * chunk_at(mc, 2 + (g >> 1)) + (g & 1);
+            uint4 w[9][2];
+            load_frags(0, w);
+            conv_rows<MY / 2, IX>(s_in + m0 * IX * 4, mc, g, w, [](int) {},
+                                  [&](int ro, const f32x4 &a0, const f32x4 &a1) {
+                const int y = y0 - 1 + m0 + ro;
+                uint2 o0 = make_uint2(0u, 0u), o1 = o0;
+                if (in_x && y >= 0 && y < p.H) {
+                    o0 = pack4(gelu(a0[0]), gelu(a0[1]), gelu(a0[2]), gelu(a0[3]));
+                    o1 = pack4(gelu(a1[0]), gelu(a1[1]), gelu(a1[2]), gelu(a1[3]));
                 }
-            }
+                mid_lo[ro * MX * 8] = o0;
+                mid_hi[ro * MX * 8] = o1;
+            });
         }
         __syncthreads();
 
-        // second convolution, residual, store: output rows 2 wave, 2 wave + 1
-#pragma unroll
-        for (int rr = 0; rr < 2; ++rr) {
-            const int r = 2 * wave + rr;
-            f32x4 a0 = {0.0f, 0.0f, 0.0f, 0.0f}, a1 = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for (int tap = 0; tap < 9; ++tap) {
-                const int dy = tap / 3, dx = tap - 3 * (tap / 3);
-                const uint4 b = s_mid[((r + dy) * MX + (n + dx)) * 5 + g];
-                a0 = mma(s_w[((9 + tap) * 2 + 0) * 64 + lane], b, a0);
-                a1 = mma(s_w[((9 + tap) * 2 + 1) * 64 + lane], b, a1);
-            }
-            const int y = y0 + r, x = x0 + n;
-            if (y < p.H && x < p.W) {
-                const uint16_t r0[4] = {(uint16_t)(resv[rr][0].x & 0xffffu), (uint16_t)(resv[rr][0].x >> 16),
-                                        (uint16_t)(resv[rr][0].y & 0xffffu), (uint16_t)(resv[rr][0].y >> 16)};
-                const uint16_t r1[4] = {(uint16_t)(resv[rr][1].x & 0xffffu), (uint16_t)(resv[rr][1].x >> 16),
-                                        (uint16_t)(resv[rr][1].y & 0xffffu), (uint16_t)(resv[rr][1].y >> 16)};
-                uint16_t o0[4], o1[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    o0[i] = f2bf(a0[i] + bf2f(r0[i]));
-                    o1[i] = f2bf(a1[i] + bf2f(r1[i]));
+        // second convolution, residual, store: rows rh TY / 2 .. of the tile
+        {
+            const int r0 = rh * (TY / 2), c = 16 * cb + n, x = x0 + c;
+            const bool in_x = c < TX && x < p.W;
+            uint2 res[3][2];                     // the un-normalised input, two rows ahead of its use
+            uint4 w[9][2];
+            load_frags(1, w);
+            conv_rows<TY / 2, MX>(s_mid + r0 * MX * 4, c, g, w,
+                                  [&](int ro) {
+                const int y = y0 + r0 + ro;
+                res[ro % 3][0] = res[ro % 3][1] = make_uint2(0u, 0u);
+                if (in_x && y < p.H) {
+                    const uint16_t *src = Fl + ((int64_t)y * p.W + x) * kC + 4 * g;
+                    res[ro % 3][0] = *reinterpret_cast<const uint2 *>(src);
+                    res[ro % 3][1] = *reinterpret_cast<const uint2 *>(src + 16);
                 }
-                uint16_t *dst = p.F_out + (((int64_t)l * p.H + y) * p.W + x) * kC;
-                *reinterpret_cast<uint2 *>(dst + 4 * g) =
-                    make_uint2(o0[0] | ((unsigned)o0[1] << 16), o0[2] | ((unsigned)o0[3] << 16));
-                *reinterpret_cast<uint2 *>(dst + 16 + 4 * g) =
-                    make_uint2(o1[0] | ((unsigned)o1[1] << 16), o1[2] | ((unsigned)o1[3] << 16));
-            }
+            },
+                                  [&](int ro, const f32x4 &a0, const f32x4 &a1) {
+                const int y = y0 + r0 + ro;
+                if (in_x && y < p.H) {
+                    uint16_t *dst = Ol + ((int64_t)y * p.W + x) * kC + 4 * g;
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const f32x4 &a = h ? a1 : a0;
+                        const uint2 u = res[ro % 3][h];
+                        *reinterpret_cast<uint2 *>(dst + 16 * h) =
+                            pack4(a[0] + bf2f((uint16_t)(u.x & 0xffffu)), a[1] + bf2f((uint16_t)(u.x >> 16)),
+                                  a[2] + bf2f((uint16_t)(u.y & 0xffffu)), a[3] + bf2f((uint16_t)(u.y >> 16)));
+                    }
+                }
+            });
         }
     }
 }
@@ -216,17 +271,25 @@ __global__ void __launch_bounds__(256) k_residual_conv(const ConvParams p) {
 hipError_t launch_residual_conv(const ConvParams &pin, int num_cu, bool frag_ready, hipStream_t s) {
     ConvParams p = pin;
     p.tiles_x = (p.W + TX - 1) / TX;
-    p.tiles_y = (p.H + TY - 1) / TY;
-    p.n_tiles = (int64_t)p.L * p.tiles_x * p.tiles_y;
+    const int64_t slots = 2 * (int64_t)(num_cu > 0 ? num_cu : 256);
+    // 16 rows per tile, or 8 where that makes for less time: rounds of the
+    // resident workgroups times a tile's cost, 9 for 8 rows (its halo is larger)
+    // and 16 for 16 (24 x 36x64: 13.9 against 15.7 us, 24 x 72x128: 25.8 against
+    // 28.1, 6 x 288x512: 80.5 against 67.3)
+    const int64_t n16 = (int64_t)p.L * p.tiles_x * ((p.H + 15) / 16);
+    const int64_t n8 = (int64_t)p.L * p.tiles_x * ((p.H + 7) / 8);
+    const bool small = 9 * ((n8 + slots - 1) / slots) < 16 * ((n16 + slots - 1) / slots);
+    p.tiles_y = (p.H + (small ? 7 : 15)) / (small ? 8 : 16);
+    p.n_tiles = small ? n8 : n16;
     hipError_t e;
     if (!frag_ready) {                           // else p.frag already holds them
         hipLaunchKernelGGL(k_conv_frag, dim3((NFRAG + 255) / 256), dim3(256), 0, s, p);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    int64_t blocks = 2 * (int64_t)(num_cu > 0 ? num_cu : 256);
-    if (blocks > p.n_tiles) blocks = p.n_tiles;
-    hipLaunchKernelGGL(k_residual_conv, dim3((unsigned)blocks), dim3(256), 0, s, p);
+    const unsigned blocks = (unsigned)(slots < p.n_tiles ? slots : p.n_tiles);
+    if (small) hipLaunchKernelGGL(k_residual_conv<8>, dim3(blocks), dim3(256), 0, s, p);
+    else hipLaunchKernelGGL(k_residual_conv<16>, dim3(blocks), dim3(256), 0, s, p);
     return hipGetLastError();
 }
 
