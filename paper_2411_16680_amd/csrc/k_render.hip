@@ -7,47 +7,151 @@
 //
 // One thread per output pixel, 16 x 16 pixel tiles (a wave covers 16 x 4), so
 // the neighbouring threads that share low-resolution logit taps and, at
-// similar depths, image taps sit in the same wave.  With V a multiple of 4
-// (template NV4 = V / 4) each layer first reads the four taps' V blend logits
-// as float4 vectors, upsamples all of them and takes their maximum, so the
-// per-view loop only exponentiates; other view counts run the softmax online
-// (running maximum, rescaled sums).  Neither the weights nor the per-view
-// samples are stored.
+// similar depths, image taps sit in the same wave.  With a view count known at
+// compile time each layer first reads the four taps' V blend logits in
+// vectors, upsamples all of them and takes their maximum, so the per-view code
+// only exponentiates; other view counts run the softmax online (running
+// maximum, rescaled sums).  Neither the weights nor the per-view samples are
+// stored.
+//
+// The vector unit bounds it: about 50 instructions per pixel, layer and view
+// and 140 more per pixel and layer, a third of them double (a position needs
+// that: a disparity is worth up to ~1e3 px), at three waves per SIMD.  So the
+// layers share what does not depend on the disparity (A (u, v, 1), three
+// doubles a view in registers: without it 382 us against 311), the projection
+// takes positions from the image's centre on (one comparison per axis), a wave
+// inside the image masks nothing, and texels enter the blend as halves
+// (add_sample).  1080p from 512 x 288, 6 layers, under the profiler: 8 views
+// 402 us before, 296 now (355 and 267 without it); 5 views, which ran online,
+// 331 and 240.  Did not help: the logit taps in LDS (296; fewer loads, as many
+// more instructions), a layer's logits read ahead (305), 128 registers for a
+// fourth wave (305, spills), 64 x 4 and 32 x 8 tiles (294).
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "uf_params.h"
 
 namespace qk {
 namespace {
 
-// RGBA8 image m as a buffer resource: a load at a byte offset outside the
-// image reads zero.  A tap outside the image is sent to kTapOOB, far past
+// RGBA8 images are read as buffer resources: a load at a byte offset outside
+// the image reads zero.  A tap outside the image is sent to kTapOOB, far past
 // the end (images are under 1 GiB), never to a negative offset: the compiler
 // may merge the loads of neighbouring taps or fold a constant into the
 // instruction's immediate offset, and a negative register offset would then
 // take a valid tap out of range with it.
 constexpr int kTapOOB = 0x40000000;
 
-__device__ inline __amdgpu_buffer_rsrc_t image_rsrc(const RenderParams &p, int m) {
-    const int bytes = p.iH[m] * p.iW[m] * 4;
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.img[m]), 0, bytes, 0x00020000);
+// What a layer needs of a view, in the 64 bytes of one scalar load: the
+// disparity's column of the projection, the image's centre hx, hy =
+// floor((size - 1) / 2), its width, the image, its bytes and a row's.
+struct RenderView {
+    double b[3];
+    double hx, hy, wd;
+    const void *img;
+    int bytes, pitch;
+};
+
+// The kernel's arguments (under 4 KiB): the views, with their projections taken
+// to texel positions counted from the image's centre (A: the columns of x, y
+// and 1) and the centre's byte offset, and the rest of RenderParams.
+struct RenderArgs {
+    RenderView v[kMaxViews];
+    int centre[kMaxViews];
+    double A[kMaxViews][9];
+    const float *depth_logit, *sigma_logit, *blend_logit;
+    float *rgb, *acc, *depth;
+    int V, L, h, w, H, W;
+    double rx, ry, band, inv_far;
+};
+static_assert(sizeof(RenderArgs) < 4096, "kernel arguments");
+
+__device__ inline __amdgpu_buffer_rsrc_t layer_rsrc(const float *p, int bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p), 0, bytes, 0x00020000);
 }
 
 __device__ inline unsigned load_texel(__amdgpu_buffer_rsrc_t r, int byte_off) {
     return __builtin_amdgcn_raw_buffer_load_b32(r, byte_off, 0, 0);
 }
 
-// Byte c of a packed texel as a float 0..255.
-__device__ inline float chan(unsigned t, int c) {
-    return (float)((t >> (8 * c)) & 0xffu);
-}
-
 __device__ inline float sigmoid_(float x) { return __builtin_amdgcn_rcpf(1.0f + __expf(-x)); }
 
-template <int NV4>
-__global__ void __launch_bounds__(256) k_render_ibr(const RenderParams p) {
+// One view's four texels (00, 10, 01, 11) and the position between them.
+struct Tex {
+    unsigned a[4];
+    float wx, wy;
+};
+
+// The texels around position (cx, cy), counted from the centre, of a view's
+// image; texels outside it, and all of them where pz says the point is behind
+// the camera, read zero.  Where the whole wave lies inside -- nearly always --
+// the two texels of a row come with one load.  |cx| < hx is inside (of an image
+// of even width the last column goes the general way too), and a position that
+// is not a number is not; wx and wy are clamped, so that such a position's are
+// numbers too (the clamp is a modifier of the conversion).
+__device__ __forceinline__ void issue_texels(const RenderView &v, int centre, double cx, double cy, double pz, Tex &t) {
+    const double xf = floor(cx), yf = floor(cy);
+    t.wx = __builtin_amdgcn_fmed3f((float)(cx - xf), 0.0f, 1.0f);
+    t.wy = __builtin_amdgcn_fmed3f((float)(cy - yf), 0.0f, 1.0f);
+    asm("" : "+v"(t.wx), "+v"(t.wy));                // (now: later would hold four doubles)
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(v.img), 0, v.bytes, 0x00020000);
+    const bool in = pz > 1e-6 && fabs(cx) < v.hx && fabs(cy) < v.hy;
+    int o = (int)((unsigned)(int)fma(yf, v.wd, xf) * 4u + (unsigned)centre);
+    asm("" : "+v"(o));                               // (no branch around it)
+    o = in ? o : kTapOOB;
+    const auto r0 = __builtin_amdgcn_raw_buffer_load_b64(rs, o, 0, 0);
+    const auto r1 = __builtin_amdgcn_raw_buffer_load_b64(rs, o, v.pitch, 0);
+    t.a[0] = r0[0];
+    t.a[1] = r0[1];
+    t.a[2] = r1[0];
+    t.a[3] = r1[1];
+    const unsigned long long all = __builtin_amdgcn_ballot_w64(pz > 1e-6) & __builtin_amdgcn_ballot_w64(fabs(cx) < v.hx) &
+                                   __builtin_amdgcn_ballot_w64(fabs(cy) < v.hy);
+    if (__builtin_expect(all != __builtin_amdgcn_ballot_w64(true), 0)) {
+        const double fx = cx + v.hx, fy = cy + v.hy;
+        const int iw = v.pitch >> 2, ih = v.bytes / v.pitch;
+        const bool ok = pz > 1e-6 && fx > -2.0 && fx < (double)(iw + 1) && fy > -2.0 && fy < (double)(ih + 1);
+        const int ix = ok ? (int)(xf + v.hx) : -4, iy = ok ? (int)(yf + v.hy) : -4;
+        const bool vx0 = (unsigned)ix < (unsigned)iw, vx1 = (unsigned)(ix + 1) < (unsigned)iw;
+        const bool vy0 = (unsigned)iy < (unsigned)ih, vy1 = (unsigned)(iy + 1) < (unsigned)ih;
+        const int q = (int)(((unsigned)iy * (unsigned)iw + (unsigned)ix) * 4u);
+        t.a[0] = load_texel(rs, (vx0 && vy0) ? q : kTapOOB);
+        t.a[1] = load_texel(rs, (vx1 && vy0) ? q + 4 : kTapOOB);
+        t.a[2] = load_texel(rs, (vx0 && vy1) ? q + v.pitch : kTapOOB);
+        t.a[3] = load_texel(rs, (vx1 && vy1) ? q + v.pitch + 4 : kTapOOB);
+    }
+}
+
+// Adds e times the bilinear sample to c, in units of 2^24.  A byte b in the
+// low end of a half is the number b 2^-24, exactly, and the mixed fma takes
+// halves and floats: one mask gives a texel's red and blue, one byte
+// permutation the green of two, where a conversion per channel took three.
+__device__ __forceinline__ void add_sample(const Tex &t, float e, float &c0, float &c1, float &c2) {
+    typedef _Float16 half2 __attribute__((ext_vector_type(2)));
+    const float f = e * t.wy, g = e - f;             // of the two rows
+    const float w1 = t.wx * g, w3 = t.wx * f;
+    const float w[4] = {g - w1, w1, f - w3, w3};
+#pragma unroll
+    for (int r = 0; r < 4; r += 2) {
+        const half2 rb0 = __builtin_bit_cast(half2, t.a[r] & 0x00ff00ffu);
+        const half2 rb1 = __builtin_bit_cast(half2, t.a[r + 1] & 0x00ff00ffu);
+        const half2 gg = __builtin_bit_cast(half2, __builtin_amdgcn_perm(t.a[r + 1], t.a[r], 0x0c050c01u));
+        c0 = fmaf(w[r], (float)rb0[0], c0);
+        c1 = fmaf(w[r], (float)gg[0], c1);
+        c2 = fmaf(w[r], (float)rb0[1], c2);
+        c0 = fmaf(w[r + 1], (float)rb1[0], c0);
+        c1 = fmaf(w[r + 1], (float)gg[1], c1);
+        c2 = fmaf(w[r + 1], (float)rb1[1], c2);
+    }
+}
+
+// NV views known at compile time (0: p.V, the softmax online).  Up to 8 views a
+// pixel's A (u, v, 1) of every view is kept over the layers (HOIST).
+template <int NV>
+__global__ void __launch_bounds__(256) k_render_ibr(const RenderArgs p) {
+    constexpr bool HOIST = NV > 0 && NV <= 8;
     // XCD-aware tile order: workgroups are dispatched round-robin over the
     // 8 XCDs, so workgroup i is given tile (i % 8) * per + i / 8 and each XCD
     // walks one contiguous band of 16-row tiles; with horizontal-ish
@@ -76,123 +180,109 @@ __global__ void __launch_bounds__(256) k_render_ibr(const RenderParams p) {
     const double lxd = sx - x0, lyd = sy - y0;
     const float lx = (float)lxd, ly = (float)lyd;
     const int64_t hw = (int64_t)p.h * p.w;
-    const int64_t t00 = (int64_t)y0 * p.w + x0, t10 = (int64_t)y0 * p.w + x1;
-    const int64_t t01 = (int64_t)y1 * p.w + x0, t11 = (int64_t)y1 * p.w + x1;
+    // (NV > 0 is taken where a layer's logits stay under 2 GiB)
+    using idx = std::conditional_t<(NV > 0), int, int64_t>;
+    const idx t00 = (idx)y0 * p.w + x0, t10 = (idx)y0 * p.w + x1;
+    const idx t01 = (idx)y1 * p.w + x0, t11 = (idx)y1 * p.w + x1;
+    auto at = [&](const float *q, idx i) {
+        if constexpr (NV > 0) return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(layer_rsrc(q, (int)(4 * hw)), 4 * i, 0, 0));
+        else return q[i];
+    };
     auto lerp_f = [&](float a00, float a10, float a01, float a11) {
         return (1.0f - ly) * ((1.0f - lx) * a00 + lx * a10) + ly * ((1.0f - lx) * a01 + lx * a11);
     };
 
-    const double u = (double)x + 0.5, v = (double)y + 0.5;
-    const int V = p.V, L = p.L;
+    const double u = (double)x + 0.5, vv = (double)y + 0.5;
+    const int V = NV > 0 ? NV : p.V, L = p.L;
+    const double rL = 1.0 / (double)L;
+    double base[HOIST ? 3 * NV : 1];               // A (u, v, 1)
+    if constexpr (HOIST) {
+#pragma unroll
+        for (int m = 0; m < NV; ++m)
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                base[3 * m + i] = fma(p.A[m][3 * i], u, fma(p.A[m][3 * i + 1], vv, p.A[m][3 * i + 2]));
+    }
     float Tr = 1.0f, out0 = 0.0f, out1 = 0.0f, out2 = 0.0f, dmap = 0.0f;
 
     for (int li = 0; li < L; ++li) {
+        const float *D = p.depth_logit + li * hw, *S = p.sigma_logit + li * hw;
+        const float alpha = sigmoid_(lerp_f(at(S, t00), at(S, t10), at(S, t01), at(S, t11)));
         // depth: the logit is interpolated in double, since an error in it is
         // magnified by the parallax (up to ~1e3 px per unit of disparity)
-        const float *D = p.depth_logit + li * hw;
-        const double xd = (1.0 - lyd) * ((1.0 - lxd) * (double)D[t00] + lxd * (double)D[t10]) +
-                          lyd * ((1.0 - lxd) * (double)D[t01] + lxd * (double)D[t11]);
-        const double delta = ((double)(L - li) - 0.5) / (double)L;
-        const double disp = (delta + (0.5 / (double)L) * (double)tanhf((float)xd)) * p.band + p.inv_far;
-        const float depth = (float)(1.0 / disp);
-        const float *S = p.sigma_logit + li * hw;
-        const float alpha = sigmoid_(lerp_f(S[t00], S[t10], S[t01], S[t11]));
+        const double xd = (1.0 - lyd) * ((1.0 - lxd) * (double)at(D, t00) + lxd * (double)at(D, t10)) +
+                          lyd * ((1.0 - lxd) * (double)at(D, t01) + lxd * (double)at(D, t11));
+        const double delta = ((double)(L - li) - 0.5) * rL;
+        const double disp = fma(fma(0.5 * rL, (double)tanhf((float)xd), delta), p.band, p.inv_far);
+        double rd = __builtin_amdgcn_rcp(disp);         // refined as 1 / pz below
+        rd = fma(rd, fma(-disp, rd, 1.0), rd);
+        const float depth = disp != 0.0 ? (float)rd : __builtin_inff();
 
         // one view's image, back-projected through this layer's depth: the
         // four texels' loads are issued here and blended later (blend_view),
         // so the next view's loads are in flight while this one is blended
-        struct Tex {
-            unsigned a[4];
-            float w[4];
-        };
-        auto issue_view = [&](int m, Tex &t) {
-            const double *A = p.cam[m];
-            const double pz = fma(A[6], u, fma(A[7], v, fma(A[11], disp, A[8])));
-            const double qx = fma(A[0], u, fma(A[1], v, fma(A[9], disp, A[2])));
-            const double qy = fma(A[3], u, fma(A[4], v, fma(A[10], disp, A[5])));
-            const int iw = p.iW[m], ih = p.iH[m];
+        auto issue_view = [&](int m, const RenderView &v, int centre, Tex &t) {
+            double pz, qx, qy;
+            if constexpr (HOIST) {
+                qx = fma(v.b[0], disp, base[3 * m]);
+                qy = fma(v.b[1], disp, base[3 * m + 1]);
+                pz = fma(v.b[2], disp, base[3 * m + 2]);
+            } else {
+                const double *A = p.A[m];
+                pz = fma(A[6], u, fma(A[7], vv, fma(v.b[2], disp, A[8])));
+                qx = fma(A[0], u, fma(A[1], vv, fma(v.b[0], disp, A[2])));
+                qy = fma(A[3], u, fma(A[4], vv, fma(v.b[1], disp, A[5])));
+            }
             // 1/pz: the hardware reciprocal refined by one Newton step (the
             // relative error squares, far below what the coordinates need)
             double rz = __builtin_amdgcn_rcp(pz);
             rz = fma(rz, fma(-pz, rz, 1.0), rz);
-            const double fxc = qx * rz - 0.5, fyc = qy * rz - 0.5;
-            const bool ok = (pz > 1e-6) && (fxc > -2.0) && (fxc < (double)(iw + 1)) &&
-                            (fyc > -2.0) && (fyc < (double)(ih + 1));
-            const double xf = floor(fxc), yf = floor(fyc);
-            const float wx = (float)(fxc - xf), wy = (float)(fyc - yf);
-            const int ix = ok ? (int)xf : -4, iy = ok ? (int)yf : -4;
-            const bool vx0 = (unsigned)ix < (unsigned)iw, vx1 = (unsigned)(ix + 1) < (unsigned)iw;
-            const bool vy0 = (unsigned)iy < (unsigned)ih, vy1 = (unsigned)(iy + 1) < (unsigned)ih;
-            t.w[0] = (vx0 && vy0) ? (1.0f - wx) * (1.0f - wy) : 0.0f;
-            t.w[1] = (vx1 && vy0) ? wx * (1.0f - wy) : 0.0f;
-            t.w[2] = (vx0 && vy1) ? (1.0f - wx) * wy : 0.0f;
-            t.w[3] = (vx1 && vy1) ? wx * wy : 0.0f;
-            const __amdgpu_buffer_rsrc_t rs = image_rsrc(p, m);
-            const int o = (iy * iw + ix) * 4;
-            t.a[0] = load_texel(rs, (vx0 && vy0) ? o : kTapOOB);
-            t.a[1] = load_texel(rs, (vx1 && vy0) ? o + 4 : kTapOOB);
-            t.a[2] = load_texel(rs, (vx0 && vy1) ? o + 4 * iw : kTapOOB);
-            t.a[3] = load_texel(rs, (vx1 && vy1) ? o + 4 * iw + 4 : kTapOOB);
+            issue_texels(v, centre, qx * rz, qy * rz, pz, t);
         };
-        // the bilinear sample of an issued view (texels 0..255)
-        auto blend_view = [&](const Tex &t, float &s0, float &s1, float &s2) {
-            s0 = t.w[0] * chan(t.a[0], 0) + t.w[1] * chan(t.a[1], 0) + t.w[2] * chan(t.a[2], 0) + t.w[3] * chan(t.a[3], 0);
-            s1 = t.w[0] * chan(t.a[0], 1) + t.w[1] * chan(t.a[1], 1) + t.w[2] * chan(t.a[2], 1) + t.w[3] * chan(t.a[3], 1);
-            s2 = t.w[0] * chan(t.a[0], 2) + t.w[1] * chan(t.a[1], 2) + t.w[2] * chan(t.a[2], 2) + t.w[3] * chan(t.a[3], 2);
-        };
-        auto sample_view = [&](int m, float &s0, float &s1, float &s2) {
-            Tex t;
-            issue_view(m, t);
-            blend_view(t, s0, s1, s2);
-        };
-
         // blend: softmax over the views of the upsampled logits
         const float *B = p.blend_logit + li * hw * V;
         float z = 0.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f;
-        if constexpr (NV4 > 0) {
-            // all views' logits first (16-byte loads: V = 4 NV4 floats per
-            // tap, and each tap's row starts on a 16-byte boundary), then
-            // their maximum, then the views
-            constexpr int NV = 4 * NV4;
-            const float4 *B00 = reinterpret_cast<const float4 *>(B + t00 * NV);
-            const float4 *B10 = reinterpret_cast<const float4 *>(B + t10 * NV);
-            const float4 *B01 = reinterpret_cast<const float4 *>(B + t01 * NV);
-            const float4 *B11 = reinterpret_cast<const float4 *>(B + t11 * NV);
+        if constexpr (NV > 0) {
+            // all views' logits first (in the widest loads that V floats per
+            // tap stay aligned to), then their maximum, then the views
+            constexpr int VW = NV % 4 == 0 ? 4 : NV % 2 == 0 ? 2 : 1;
+            typedef float vec __attribute__((ext_vector_type(VW)));
+            const __amdgpu_buffer_rsrc_t brs = layer_rsrc(B, (int)(4 * hw) * NV);
+            auto tap = [&](int i, int c) {
+                const int o = i * (4 * NV), k = c * (int)sizeof(vec);
+                if constexpr (VW == 4) return __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b128(brs, o, k, 0));
+                else if constexpr (VW == 2) return __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b64(brs, o, k, 0));
+                else return __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b32(brs, o, k, 0));
+            };
             float xb[NV];
 #pragma unroll
-            for (int c = 0; c < NV4; ++c) {
-                const float4 a = B00[c], b = B10[c], d = B01[c], e = B11[c];
-                xb[4 * c + 0] = lerp_f(a.x, b.x, d.x, e.x);
-                xb[4 * c + 1] = lerp_f(a.y, b.y, d.y, e.y);
-                xb[4 * c + 2] = lerp_f(a.z, b.z, d.z, e.z);
-                xb[4 * c + 3] = lerp_f(a.w, b.w, d.w, e.w);
+            for (int c = 0; c < NV / VW; ++c) {
+                const vec a = tap(t00, c), b = tap(t10, c), d = tap(t01, c), e = tap(t11, c);
+#pragma unroll
+                for (int i = 0; i < VW; ++i) xb[VW * c + i] = lerp_f(a[i], b[i], d[i], e[i]);
             }
             float mx = xb[0];
 #pragma unroll
             for (int m = 1; m < NV; ++m) mx = fmaxf(mx, xb[m]);
-            // the views two at a time, two texel buffers in turn: the loads
-            // of the next view are issued before this one is blended (not
-            // unrolled further: the loop body's live values would take the
-            // register file; the index is uniform)
-            Tex ta, tb;
-            issue_view(0, ta);
-#pragma unroll 1
-            for (int m = 0; m < NV; m += 2) {
-                float s0, s1, s2;
-                issue_view(m + 1, tb);               // NV is even
-                const float e0 = __expf(xb[m] - mx);
-                blend_view(ta, s0, s1, s2);
-                z += e0;
-                c0 = fmaf(e0, s0, c0);
-                c1 = fmaf(e0, s1, c1);
-                c2 = fmaf(e0, s2, c2);
-                if (m + 2 < NV) issue_view(m + 2, ta);
-                const float e1 = __expf(xb[m + 1] - mx);
-                blend_view(tb, s0, s1, s2);
-                z += e1;
-                c0 = fmaf(e1, s0, c0);
-                c1 = fmaf(e1, s1, c1);
-                c2 = fmaf(e1, s2, c2);
+            // two texel buffers in turn: the loads of the next view are issued
+            // before this one is blended
+            Tex t[2];
+            int first = 0;          // hidden: the views' records are read again in each
+            asm volatile("" : "+s"(first));     // layer, all at once they would take the scalar registers
+            issue_view(0, p.v[first], p.centre[first], t[0]);
+            RenderView rv = p.v[first + (NV > 1 ? 1 : 0)];
+            int rc = p.centre[first + (NV > 1 ? 1 : 0)];
+#pragma unroll
+            for (int m = 0; m < NV; ++m) {
+                if (m + 1 < NV) issue_view(m + 1, rv, rc, t[(m + 1) & 1]);
+                if (m + 2 < NV) rv = p.v[first + m + 2], rc = p.centre[first + m + 2];
+                const float e = __expf(xb[m] - mx);
+                add_sample(t[m & 1], e, c0, c1, c2);
+                z += e;
+                // each view blended before the next but one is issued: all
+                // views' texels at once would take the register file
+                asm volatile("" : "+v"(c0), "+v"(c1), "+v"(c2));
+                __builtin_amdgcn_sched_barrier(0);
             }
         } else {
             // online: running maximum, sums rescaled when it moves
@@ -205,15 +295,14 @@ __global__ void __launch_bounds__(256) k_render_ibr(const RenderParams p) {
                     mx = xb;
                 }
                 const float e = __expf(xb - mx);
-                float s0, s1, s2;
-                sample_view(m, s0, s1, s2);
+                Tex t;
+                issue_view(m, p.v[m], p.centre[m], t);
+                add_sample(t, e, c0, c1, c2);
                 z += e;
-                c0 = fmaf(e, s0, c0);
-                c1 = fmaf(e, s1, c1);
-                c2 = fmaf(e, s2, c2);
             }
         }
-        const float k = Tr * alpha * (1.0f / 255.0f) / z;   // beta = e / z; texels v / 255
+        // beta = e / z; texels v / 255, summed in units of 2^24
+        const float k = Tr * alpha * (16777216.0f / 255.0f) * __builtin_amdgcn_rcpf(z);
         out0 = fmaf(k, c0, out0);
         out1 = fmaf(k, c1, out1);
         out2 = fmaf(k, c2, out2);
@@ -233,16 +322,47 @@ __global__ void __launch_bounds__(256) k_render_ibr(const RenderParams p) {
 hipError_t launch_render_ibr(const RenderParams &p, hipStream_t s) {
     const int tiles = ((p.W + 15) / 16) * ((p.H + 15) / 16);
     const dim3 g(tiles), b(256);
-    // the vector path reads 16 bytes at a time: V a multiple of 4 and the
-    // logits 16-byte aligned (the C-ABI asks only for 4)
-    const bool vec = p.V % 4 == 0 && (reinterpret_cast<uintptr_t>(p.blend_logit) & 15) == 0;
-    switch (vec ? p.V / 4 : 0) {
-    case 1: hipLaunchKernelGGL(k_render_ibr<1>, g, b, 0, s, p); break;
-    case 2: hipLaunchKernelGGL(k_render_ibr<2>, g, b, 0, s, p); break;
-    case 3: hipLaunchKernelGGL(k_render_ibr<3>, g, b, 0, s, p); break;
-    case 4: hipLaunchKernelGGL(k_render_ibr<4>, g, b, 0, s, p); break;
-    default: hipLaunchKernelGGL(k_render_ibr<0>, g, b, 0, s, p); break;
+    RenderArgs a = {};
+    for (int m = 0; m < p.V; ++m) {
+        RenderView &v = a.v[m];
+        const double *c = p.cam[m];
+        v.hx = (p.iW[m] - 1) / 2;
+        v.hy = (p.iH[m] - 1) / 2;
+        a.centre[m] = 4 * ((p.iH[m] - 1) / 2 * p.iW[m] + (p.iW[m] - 1) / 2);
+        for (int i = 0; i < 3; ++i) {
+            a.A[m][i] = c[i] - (v.hx + 0.5) * c[6 + i];
+            a.A[m][3 + i] = c[3 + i] - (v.hy + 0.5) * c[6 + i];
+            a.A[m][6 + i] = c[6 + i];
+        }
+        v.b[0] = c[9] - (v.hx + 0.5) * c[11];
+        v.b[1] = c[10] - (v.hy + 0.5) * c[11];
+        v.b[2] = c[11];
+        v.wd = p.iW[m];
+        v.img = p.img[m];
+        v.pitch = 4 * p.iW[m];
+        v.bytes = p.iH[m] * v.pitch;
     }
+    a.depth_logit = p.depth_logit;
+    a.sigma_logit = p.sigma_logit;
+    a.blend_logit = p.blend_logit;
+    a.rgb = p.rgb;
+    a.acc = p.acc;
+    a.depth = p.depth;
+    a.V = p.V; a.L = p.L; a.h = p.h; a.w = p.w; a.H = p.H; a.W = p.W;
+    a.rx = p.rx; a.ry = p.ry; a.band = p.band; a.inv_far = p.inv_far;
+    // view counts known at compile time read their logits in vectors, which the
+    // logits' address has to allow (the C-ABI asks only for 4 bytes), at 32-bit
+    // offsets
+    const uintptr_t at = reinterpret_cast<uintptr_t>(p.blend_logit);
+    const bool vec = (at & (p.V % 4 == 0 ? 15 : p.V % 2 == 0 ? 7 : 3)) == 0 &&
+                     (int64_t)p.h * p.w * p.V < ((int64_t)1 << 29);
+#define QK_RENDER(NV) case NV: hipLaunchKernelGGL((k_render_ibr<NV>), g, b, 0, s, a); break
+    switch (vec ? p.V : 0) {
+    QK_RENDER(1); QK_RENDER(2); QK_RENDER(3); QK_RENDER(4); QK_RENDER(5); QK_RENDER(6); QK_RENDER(7); QK_RENDER(8);
+    QK_RENDER(12); QK_RENDER(16);
+    default: hipLaunchKernelGGL((k_render_ibr<0>), g, b, 0, s, a); break;
+    }
+#undef QK_RENDER
     return hipGetLastError();
 }
 
