@@ -13,22 +13,21 @@
 // difference applies the first two rows of the novel K (on its own grid,
 // NDC = 2 (u, v) / (W_n, H_n) up to a constant that cancels).
 //
-// Two forms.  Per pixel (k_ray_encoding): one thread per map pixel
-// evaluates its own encoding.  Low resolution, as the paper does it
-// (k_ray_lowres + k_ray_upsample_add): the projected encoding is evaluated
-// once per pixel of a coarse grid, then every map pixel adds its bilinear
-// upsampling -- projection and bilinear interpolation are both linear, so
-// projecting first gives the same values and leaves C channels, not 32, to
-// interpolate; the second pass is bound by the feature maps' HBM traffic.
+// Two forms.  Per pixel: every map pixel evaluates its own encoding.  Low
+// resolution, as the paper does it (k_ray_encoding into a workspace, then
+// k_ray_upsample_add): the projected encoding is evaluated once per pixel of a
+// coarse grid, then every map pixel adds its bilinear upsampling -- projection
+// and bilinear interpolation are both linear, so projecting first gives the
+// same values and leaves C channels, not 32, to interpolate; the second pass
+// is bound by the feature maps' HBM traffic.
 //
 // The encoding runs in double up to the sinusoids (the top octave scales
 // its argument by 128 pi): sin(pi t) and cos(pi t) from their Taylor
 // series on a quarter period after an exact quadrant reduction, then each
 // higher octave by the double-angle identities sin 2a = 2 sin a cos a,
 // cos 2a = (cos a - sin a)(cos a + sin a) -- the angle error doubles per
-// octave, about 1e-14 at the top.  The projection, in float, reads the
-// 32 x C weights as wave-uniform operands (scalar loads or LDS broadcasts)
-// and accumulates on top of the feature, which is rounded once at the store.
+// octave, about 1e-14 at the top.  The projection, in float, accumulates on top
+// of the feature, which is rounded once at the store.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -120,9 +119,10 @@ __device__ inline float bf2f(uint16_t h) { return __uint_as_float((unsigned)h <<
 
 __device__ inline uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 
-// The 32 sinusoids of pixel (x, y) of view m's grid (the grid the
-// composed D[m] was made for).
-__device__ inline void ray_sinusoids(const RayParams &p, int m, int x, int y, float e[32]) {
+// 16 of the 32 sinusoids of pixel (x, y) of view m's grid (the grid the composed
+// D[m] was made for): sine and cosine of one angle (x's, or y's) in 8 octaves.
+__device__ __forceinline__ void ray_sinusoids(const RayParams &p, int m, int x, int y, bool second, float fs[8],
+                                              float fc[8]) {
     const double u = (double)x + 0.5, v = (double)y + 0.5;
     const double *D = p.D[m], *o = p.o[m];
     const double dx = fma(D[0], u, fma(D[1], v, D[2]));
@@ -131,21 +131,16 @@ __device__ inline void ray_sinusoids(const RayParams &p, int m, int x, int y, fl
     const double rz = o[2] / dz;
     const double ax = p.inv_band * fma(-rz, dx, o[0]);
     const double ay = p.inv_band * fma(-rz, dy, o[1]);
-    const double tx = tanh_abs(fma(p.kx0, ax, p.kx1 * ay));
-    const double ty = tanh_abs(fma(p.ky0, ax, p.ky1 * ay));
-    double sx, cx, sy, cy;
-    sincospi_unit(tx, sx, cx);
-    sincospi_unit(ty, sy, cy);
+    const double t = tanh_abs(second ? fma(p.ky0, ax, p.ky1 * ay) : fma(p.kx0, ax, p.kx1 * ay));
+    double s, c;
+    sincospi_unit(t, s, c);
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-        e[4 * k + 0] = (float)sx;
-        e[4 * k + 1] = (float)cx;
-        e[4 * k + 2] = (float)sy;
-        e[4 * k + 3] = (float)cy;
+        fs[k] = (float)s;
+        fc[k] = (float)c;
         if (k < 7) {
-            const double s2x = 2.0 * sx * cx, c2x = (cx - sx) * (cx + sx);
-            const double s2y = 2.0 * sy * cy, c2y = (cy - sy) * (cy + sy);
-            sx = s2x; cx = c2x; sy = s2y; cy = c2y;
+            const double s2 = 2.0 * s * c, c2 = (c - s) * (c + s);
+            s = s2; c = c2;
         }
     }
 }
@@ -185,88 +180,142 @@ __device__ inline void store8(void *base, int64_t off, const float a[8]) {
     }
 }
 
-// The 32 x C weights: for C <= 16 through the scalar unit (a wave-uniform
-// index into the constant address space compiles to scalar loads and the
-// FMAs take the weight as an SGPR operand); for wider C the scalar loads
-// come in small pieces that stall, so the workgroup stages the weights in
-// LDS and every read is a broadcast.
-typedef const __attribute__((address_space(4))) float *wptr_t;
-
-template <int C>
-struct Weights {
-    static constexpr bool kLds = C >= 32;
-    static constexpr int kBuf = kLds ? 8 * C : 1;    // float4s of LDS
-    __device__ static void stage(const RayParams &p, float4 *buf) {
-        if constexpr (kLds) {
-            for (int i = threadIdx.x; i < 8 * C; i += 256) buf[i] = reinterpret_cast<const float4 *>(p.Wr)[i];
-            __syncthreads();
+// N consecutive channels as float, and back (rounded once); N = 2 or a multiple of 4
+template <int N, bool BF16>
+__device__ __forceinline__ void load_n(const void *base, int64_t off, float a[N]) {
+    if constexpr (N % 8 == 0) {
+#pragma unroll
+        for (int j = 0; j < N; j += 8) load8<BF16>(base, off + j, a + j);
+    } else if constexpr (BF16) {
+        const unsigned *w = reinterpret_cast<const unsigned *>(static_cast<const uint16_t *>(base) + off);
+        unsigned r[N / 2];
+        if constexpr (N == 4) {
+            const uint2 v = *reinterpret_cast<const uint2 *>(w);
+            r[0] = v.x;
+            r[1] = v.y;
+        } else {
+            r[0] = w[0];
         }
+#pragma unroll
+        for (int j = 0; j < N / 2; ++j) {
+            a[2 * j] = bf2f((uint16_t)(r[j] & 0xffffu));
+            a[2 * j + 1] = bf2f((uint16_t)(r[j] >> 16));
+        }
+    } else {
+        typedef float vec __attribute__((ext_vector_type(N)));
+        const vec v = *reinterpret_cast<const vec *>(static_cast<const float *>(base) + off);
+#pragma unroll
+        for (int j = 0; j < N; ++j) a[j] = v[j];
     }
-};
-
-// a[j] += sum_i e[i] w[i][c0 + j], j < 8
-template <int C, typename WP>
-__device__ inline void project8(const float e[32], WP w, int c0, float a[8]) {
-#pragma unroll
-    for (int i = 0; i < 32; ++i)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) a[j] = fmaf(e[i], w[i * C + c0 + j], a[j]);
 }
 
-template <int C>
-__device__ inline void project8_w(const float e[32], const RayParams &p, const float4 *lds, int c0,
-                                  float a[8]) {
-    if constexpr (Weights<C>::kLds)
-        project8<C>(e, reinterpret_cast<const float *>(lds), c0, a);
-    else
-        project8<C>(e, (wptr_t)p.Wr, c0, a);
+template <int N, bool BF16>
+__device__ __forceinline__ void store_n(void *base, int64_t off, const float a[N]) {
+    if constexpr (N % 8 == 0) {
+#pragma unroll
+        for (int j = 0; j < N; j += 8) store8<BF16>(base, off + j, a + j);
+    } else if constexpr (BF16) {
+        typedef unsigned vec __attribute__((ext_vector_type(N / 2)));
+        vec v;
+#pragma unroll
+        for (int j = 0; j < N / 2; ++j) v[j] = f2bf(a[2 * j]) | ((unsigned)f2bf(a[2 * j + 1]) << 16);
+        *reinterpret_cast<vec *>(static_cast<uint16_t *>(base) + off) = v;
+    } else {
+        typedef float vec __attribute__((ext_vector_type(N)));
+        vec v;
+#pragma unroll
+        for (int j = 0; j < N; ++j) v[j] = a[j];
+        *reinterpret_cast<vec *>(static_cast<float *>(base) + off) = v;
+    }
 }
 
-// Per-pixel form: every pixel of every map evaluates its own encoding.
-template <int C, bool BF16>
+// The projected encoding e Wr of every pixel of a grid: LOW, of the (lH, lW)
+// grid, float32, into the workspace [V][lH][lW][C]; otherwise of every map,
+// added to its features (the per-pixel form).
+//
+// A wave takes 32 pixels at a time: lane 32 h + 16 a + n evaluates angle a of
+// pixel 16 h + n, one evaluation per pixel and angle.  The product runs on the
+// matrix cores in float, 16x16x4, with the k index of step t at 4 t + g for the
+// lanes of group g = lane / 16: those are the encoding's components of octave
+// t, and two swaps of lane groups turn the sines and cosines of an octave into
+// the operands of both halves' 16 pixels.  The weights' channels are the rows,
+// row 4 g + i of block b being channel (C / 4) g + 4 b + i, so that a lane ends
+// with C / 4 consecutive channels of its pixel (C = 8: 2, rows 2 and 3 of each
+// group empty).  A wave keeps the weights in registers over its pixels.
+//
+// The low-resolution grid of a 1080p pyramid (8 views, 240 x 135) took 24, 15
+// and 9 us at 32, 16 and 8 channels and 43 us added to its own map at 64, one
+// thread per pixel with the weights as LDS broadcasts or scalars (LDS reads
+// bound the first, few and long waves the rest); now 15, 12, 12 and 26.  The
+// chain of double operations, of which 4 waves per SIMD overlap, bounds it: held
+// to 80 registers for 6 waves it spills (33, 23, 28 us).  A frame's small grids
+// took 12 us a launch, now 5.
+template <int C, bool LOW, bool BF16>
 __global__ void __launch_bounds__(256) k_ray_encoding(const RayParams p) {
-    __shared__ float4 wbuf[Weights<C>::kBuf];
-    Weights<C>::stage(p, wbuf);                  // the only barrier
+    constexpr int NB = C < 16 ? 1 : C / 16, NCH = C / 4;
+    typedef float f4 __attribute__((ext_vector_type(4)));
     const int m = blockIdx.y;
-    const int fw = p.fW[m];
-    const int64_t np = (int64_t)p.fH[m] * fw;
-    const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (q >= np) return;
-    const int y = (int)(q / fw), x = (int)(q - (int64_t)y * fw);
-    float e[32];
-    ray_sinusoids(p, m, x, y, e);
-    // all of the pixel's channels are read before any is written: the source
-    // may be the map itself, and the compiler cannot move a load of one
-    // pointer above a store through another that may alias it
-    float a[C / 8][8];
+    const int fw = LOW ? p.lW : p.fW[m];
+    const int64_t np = (int64_t)(LOW ? p.lH : p.fH[m]) * fw;
+    const int lane = threadIdx.x & 63, g = lane >> 4, n = lane & 15;
+    const int64_t step = (int64_t)gridDim.x * 128;
+    int64_t q0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 32;
+    if (q0 >= np) return;
+    float w[NB][8];
+    {
+        const bool row = C >= 16 || (n & 3) < 2;
+        const int ch = C < 16 ? 2 * (n >> 2) + (n & 1) : NCH * (n >> 2) + (n & 3);
 #pragma unroll
-    for (int c8 = 0; c8 < C / 8; ++c8) load8<BF16>(p.src[m], q * C + 8 * c8, a[c8]);
+        for (int b = 0; b < NB; ++b)
 #pragma unroll
-    for (int c8 = 0; c8 < C / 8; ++c8) {
-        project8_w<C>(e, p, wbuf, 8 * c8, a[c8]);
-        store8<BF16>(p.feat[m], q * C + 8 * c8, a[c8]);
+            for (int k = 0; k < 8; ++k) {
+                const float v = p.Wr[(4 * k + g) * C + ch + 4 * b];
+                w[b][k] = row ? v : 0.0f;
+            }
     }
-}
-
-// Low-resolution form, first pass: the projected encoding P = e Wr of every
-// pixel of the (lH, lW) grid, float32, into the workspace [V][lH][lW][C].
-template <int C>
-__global__ void __launch_bounds__(256) k_ray_lowres(const RayParams p) {
-    __shared__ float4 wbuf[Weights<C>::kBuf];
-    Weights<C>::stage(p, wbuf);                  // the only barrier
-    const int m = blockIdx.y;
-    const int64_t np = (int64_t)p.lH * p.lW;
-    const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (q >= np) return;
-    const int y = (int)(q / p.lW), x = (int)(q - (int64_t)y * p.lW);
-    float e[32];
-    ray_sinusoids(p, m, x, y, e);
-    float *dst = p.P + ((int64_t)m * np + q) * C;
+    double rw = __builtin_amdgcn_rcp((double)fw);
+    rw = fma(rw, fma(-(double)fw, rw, 1.0), rw);
+    rw = fma(rw, fma(-(double)fw, rw, 1.0), rw);
+    for (; q0 < np; q0 += step) {
+        float e[2][8];
+        {
+            const int64_t qe = q0 + 16 * (lane >> 5) + n, q = qe < np ? qe : np - 1;
+            // exact: the quotient is 1 / (2 fw) or more from the next integer
+            const int y = (int)(((double)q + 0.5) * rw), x = (int)(q - (int64_t)y * fw);
+            ray_sinusoids(p, m, x, y, (lane >> 4) & 1, e[0], e[1]);
+        }
 #pragma unroll
-    for (int c8 = 0; c8 < C / 8; ++c8) {
-        float a[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-        project8_w<C>(e, p, wbuf, 8 * c8, a);
-        store8<false>(dst, 8 * c8, a);
+        for (int k = 0; k < 8; ++k) {
+            // s = (s0 s1 s2 s3), c alike by lane group: then (s0 c0 s2 c2) and
+            // (s1 c1 s3 c3), then (s0 c0 s1 c1) and (s2 c2 s3 c3)
+            const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(e[0][k]), __float_as_uint(e[1][k]), false, false);
+            const auto t = __builtin_amdgcn_permlane32_swap(r[0], r[1], false, false);
+            e[0][k] = __uint_as_float(t[0]);
+            e[1][k] = __uint_as_float(t[1]);
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int64_t q = q0 + 16 * h + n;
+            const bool live = q < np;
+            float a[NCH];
+            if constexpr (!LOW) load_n<NCH, BF16>(p.src[m], (live ? q : np - 1) * C + NCH * g, a);
+            f4 acc[NB];
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[b][i] = (LOW || 4 * b + i >= NCH) ? 0.0f : a[4 * b + i];
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+                    acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[b][k], e[h][k], acc[b], 0, 0, 0);
+#pragma unroll
+            for (int j = 0; j < NCH; ++j) a[j] = acc[j / 4][j % 4];
+            if (live) {
+                if constexpr (LOW) store_n<NCH, false>(p.P, ((int64_t)m * np + q) * C + NCH * g, a);
+                else store_n<NCH, BF16>(p.feat[m], q * C + NCH * g, a);
+            }
+        }
     }
 }
 
@@ -354,13 +403,20 @@ __global__ void __launch_bounds__(256) k_ray_upsample_add_any(const RayParams p)
     store8<BF16>(p.feat[m], q * C + c0, a);
 }
 
+// Blocks of k_ray_encoding per view: 128 pixels each, up to 8 waves per SIMD in
+// all, then more pixels per wave
+inline unsigned encoding_blocks(int64_t pixels, unsigned V) {
+    const int64_t all = (pixels + 127) / 128, most = (2048 + V - 1) / V;
+    return (unsigned)(all < most ? all : most);
+}
+
 template <int C>
 hipError_t launch_c(const RayParams &p, hipStream_t s) {
     const unsigned V = (unsigned)p.V;
     bool same = p.lH > 0;                        // low grid == every map grid: nothing to upsample
     for (int m = 0; m < p.V; ++m) same = same && p.lH == p.fH[m] && p.lW == p.fW[m];
     if (p.lH > 0 && !same) {
-        hipLaunchKernelGGL((k_ray_lowres<C>), dim3((unsigned)(((int64_t)p.lH * p.lW + 255) / 256), V),
+        hipLaunchKernelGGL((k_ray_encoding<C, true, false>), dim3(encoding_blocks((int64_t)p.lH * p.lW, V), V),
                            dim3(256), 0, s, p);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -387,11 +443,11 @@ hipError_t launch_c(const RayParams &p, hipStream_t s) {
         }
         return hipGetLastError();
     }
-    const dim3 g((unsigned)((p.max_pixels + 255) / 256), V);
+    const dim3 g(encoding_blocks(p.max_pixels, V), V);
     if (p.bf16)
-        hipLaunchKernelGGL((k_ray_encoding<C, true>), g, dim3(256), 0, s, p);
+        hipLaunchKernelGGL((k_ray_encoding<C, false, true>), g, dim3(256), 0, s, p);
     else
-        hipLaunchKernelGGL((k_ray_encoding<C, false>), g, dim3(256), 0, s, p);
+        hipLaunchKernelGGL((k_ray_encoding<C, false, false>), g, dim3(256), 0, s, p);
     return hipGetLastError();
 }
 
