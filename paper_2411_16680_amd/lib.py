@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 from typing import Dict, List, Optional, Sequence
 
 import numpy as np
@@ -42,6 +43,9 @@ class QuarkError(RuntimeError):
     def __init__(self, status: int, msg: str):
         super().__init__(f"{STATUS_NAMES.get(status, status)}: {msg}")
         self.status = status
+
+
+_SIZE = struct.Struct("=II")         # a camera's width and height (32 bits, wrapped as ctypes does)
 
 
 class qk_camera(ctypes.Structure):
@@ -207,45 +211,52 @@ def version() -> str:
 # marshalling helpers
 # --------------------------------------------------------------------------
 
+# Marshalling is most of what a small call takes on the host (3 views of a tiny
+# level: 18 of 27 us), so a call's cameras go over as bytes, in the structure's
+# layout, instead of number by number.
+def _camera_bytes(cam) -> bytes:
+    return (np.asarray(cam.K, dtype=np.float64).reshape(9).tobytes()
+            + np.asarray(cam.E, dtype=np.float64).reshape(16).tobytes()
+            + _SIZE.pack(int(cam.width) & 0xFFFFFFFF, int(cam.height) & 0xFFFFFFFF))
+
+
 def make_camera(cam) -> qk_camera:
-    c = qk_camera()
-    K = np.ascontiguousarray(cam.K, dtype=np.float64).reshape(9)
-    E = np.ascontiguousarray(cam.E, dtype=np.float64).reshape(16)
-    for i in range(9):
-        c.K[i] = float(K[i])
-    for i in range(16):
-        c.E[i] = float(E[i])
-    c.width, c.height = int(cam.width), int(cam.height)
-    return c
+    return qk_camera.from_buffer_copy(_camera_bytes(cam))
+
+
+def _cameras(cams):
+    return (qk_camera * len(cams)).from_buffer_copy(b"".join([_camera_bytes(c) for c in cams]))
 
 
 def _ptr(t) -> Optional[int]:
-    return None if t is None else int(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _fmap(f) -> "qk_feature_map":
     """One view's feature map [H][W][C] (its dtype and C as the tensor has
     them; the library checks them against the call's precision and
     weights)."""
-    return qk_feature_map(_ptr(f), _dtype_code(f), int(f.shape[0]), int(f.shape[1]),
-                          int(f.shape[2]) if len(f.shape) > 2 else 0)
+    shape = f.shape
+    return qk_feature_map(f.data_ptr(), _dtype_code(f), shape[0], shape[1],
+                          shape[2] if len(shape) > 2 else 0)
+
+
+_DTYPE_CODES: Dict = {}
 
 
 def _dtype_code(t) -> int:
-    import torch
-    if t.dtype == torch.bfloat16:
-        return QK_BF16
-    if t.dtype == torch.float32:
-        return QK_F32
-    return 99
+    if not _DTYPE_CODES:
+        import torch
+        _DTYPE_CODES.update({torch.bfloat16: QK_BF16, torch.float32: QK_F32})
+    return _DTYPE_CODES.get(t.dtype, 99)
 
 
 def make_ldm(F, depth, alpha) -> qk_ldm:
     """F: [L][H][W][C] (float32 or bfloat16) or None; depth, alpha: [L][H][W] float32
     (either may be None where the call allows it; the grid comes from the others)."""
     ref = depth if depth is not None else alpha
-    L, H, W = (int(s) for s in (ref.shape if ref is not None else F.shape[:3]))
-    C = int(F.shape[-1]) if F is not None else 0
+    L, H, W = ref.shape if ref is not None else F.shape[:3]
+    C = F.shape[-1] if F is not None else 0
     return qk_ldm(_ptr(F), _ptr(depth), _ptr(alpha), L, H, W, C,
                   _dtype_code(F) if F is not None else QK_F32)
 
@@ -261,8 +272,10 @@ def make_weights(w: Dict, heads: int = 1, head_dim: Optional[int] = None) -> qk_
 
 
 def _stream_handle(stream) -> Optional[int]:
-    import torch
     if stream is None:
+        import torch
+        if torch.cuda.is_initialized():      # the current stream's handle, without the stream object
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         stream = torch.cuda.current_stream()
     return int(stream.cuda_stream)
 
@@ -299,9 +312,8 @@ class Context:
 def _uf_args(in_cams, feats, novel, near, far, weights, precision, attn_form, mode, ldm_in,
              ldm_out, rgb_out, acc_out, blend_out=None):
     V = len(in_cams)
-    cams = (qk_camera * V)(*[make_camera(c) for c in in_cams])
-    fm = (qk_feature_map * V)(*[_fmap(f)
-                                 for f in feats])
+    cams = _cameras(in_cams)
+    fm = (qk_feature_map * V)(*[_fmap(f) for f in feats])
     nov = make_camera(novel)
     wts = weights if isinstance(weights, qk_weights) else make_weights(weights)
     lin = ldm_in if isinstance(ldm_in, qk_ldm) else make_ldm(*ldm_in)
@@ -357,7 +369,7 @@ class Request:
     def __init__(self, in_cams, feats, novel, near, far, weights, ldm_in, ldm_out, *,
                  mode="residual", rgb_out=None, acc_out=None, blend_logit_out=None):
         V = len(in_cams)
-        self.cams = (qk_camera * V)(*[make_camera(c) for c in in_cams])
+        self.cams = _cameras(in_cams)
         self.fm = (qk_feature_map * V)(*[_fmap(f) for f in feats])
         self.nov = make_camera(novel)
         self.wts = weights if isinstance(weights, qk_weights) else make_weights(weights)
@@ -400,9 +412,8 @@ def make_weight_grads(dw: Dict) -> qk_weight_grads:
 def _bwd_args(in_cams, feats, novel, near, far, weights, mode, ldm_in, ldm_out, d_rgb, d_out,
               d_in, d_feats, d_weights):
     V = len(in_cams)
-    cams = (qk_camera * V)(*[make_camera(c) for c in in_cams])
-    fm = (qk_feature_map * V)(*[_fmap(f)
-                                 for f in feats])
+    cams = _cameras(in_cams)
+    fm = (qk_feature_map * V)(*[_fmap(f) for f in feats])
     nov = make_camera(novel)
     wts = weights if isinstance(weights, qk_weights) else make_weights(weights)
     lin = ldm_in if isinstance(ldm_in, qk_ldm) else make_ldm(*ldm_in)
@@ -487,7 +498,7 @@ def composite_backward_check(color, alpha, d_rgb, d_alpha, d_color=None, d_acc=N
 
 def _render_args(in_cams, images, novel, near, far, logits, H, W, rgb_out, acc_out, depth_out):
     V = len(in_cams)
-    cams = (qk_camera * V)(*[make_camera(c) for c in in_cams])
+    cams = _cameras(in_cams)
     imgs = (qk_image * V)(*[qk_image(_ptr(im), int(im.shape[0]), int(im.shape[1]))
                             for im in images])
     dl, sl, bl = logits
@@ -522,7 +533,7 @@ def render_ibr_check(in_cams, images, novel, near, far, logits, H, W, rgb_out, *
 
 def _views_args(in_cams, novel, depth, alpha, color, rgb_outs, acc_outs):
     V = len(in_cams)
-    cams = (qk_camera * V)(*[make_camera(c) for c in in_cams])
+    cams = _cameras(in_cams)
     L, H, W = (int(s) for s in depth.shape)
     ld = qk_ldm_decoded(_ptr(depth), _ptr(alpha), _ptr(color), L, H, W)
     accs = [None] * V if acc_outs is None else list(acc_outs)
@@ -583,7 +594,7 @@ def layer_collapse_check(F_in, W1, W2, F_out) -> int:
 
 def _ray_args(in_cams, novel, near, far, Wr, feats, low_hw, src=None):
     V = len(in_cams)
-    cams = (qk_camera * V)(*[make_camera(c) for c in in_cams])
+    cams = _cameras(in_cams)
     srcs = [None] * len(feats) if src is None else list(src)
     if len(srcs) != len(feats):
         raise ValueError("src needs one map per feature map")
@@ -678,7 +689,7 @@ def ldm_logits_check(F, w_sigma, w_depth, depth_logit, sigma_logit) -> int:
 def camera_tables(in_cams, feat_hw: Sequence, novel, H: int, W: int) -> np.ndarray:
     """qk_camera_tables: per-view [12] = A (3x3 row-major) then b, in double."""
     V = len(in_cams)
-    cams = (qk_camera * V)(*[make_camera(c) for c in in_cams])
+    cams = _cameras(in_cams)
     hw = np.ascontiguousarray(feat_hw, dtype=np.int32).reshape(V, 2)
     out = np.zeros((V, 12))
     nov = make_camera(novel)
