@@ -600,9 +600,16 @@ __device__ __forceinline__ int xcd_tile(int i, int nt) {
     return (xcd < rem) ? xcd * (q + 1) + loc : rem * (q + 1) + (xcd - rem) * q + loc;
 }
 
-template <int C, bool BF16, bool FOLD, bool F8, int HD, int VAR, int ROWS = 1>
+// SPLIT: the four waves of a workgroup share the pixels of one wave and take a
+// quarter of the layers each.  The colours and alphas of all layers wait in LDS
+// (kSplitPixels of them, 16 KB) for the composite, which the first wave then
+// takes layer by layer with the same operations in the same order.
+constexpr int kSplitPixels = 1024;
+
+template <int C, bool BF16, bool FOLD, bool F8, int HD, int VAR, int ROWS = 1, bool SPLIT = false>
 __global__ void __launch_bounds__(256 * ROWS)
-__attribute__((amdgpu_waves_per_eu(ROWS > 1 ? 2
+__attribute__((amdgpu_waves_per_eu(SPLIT ? (C == 64 ? 1 : BF16 ? 3 : 2)          // LDS holds no more
+                                   : ROWS > 1 ? 2
                                    : (FOLD && HD != C) ? 2
                                    : (!BF16 && VAR == kBlend) ? 1    // its extra stores spill at 3
                                    : Occupancy<C, BF16, FOLD || kReassoc<C, BF16, FOLD, HD>>::waves)))
@@ -672,6 +679,7 @@ k_update_fuse(const UFArgs<VAR == kBatch> args) {
     __shared__ Coord scam[(GR > 1 && !PADTAB) ? kMaxViews * 12 : 1];
     __shared__ int sfwh[(GR > 1 && !PADTAB) ? kMaxViews * 2 : 1];
     constexpr int THREADS = 256 * ROWS;
+    __shared__ float4 slayer[SPLIT ? kSplitPixels : 1];   // colour and alpha of every layer's pixels
     __shared__ float sF[4 * ROWS][PIX * P];
     __shared__ float sO[4 * ROWS][PIX * P];   // o tile; for C = 8 also the tap exchange
     // word w of the padded table: pad row w / 4 (rows run through the four
@@ -777,9 +785,10 @@ k_update_fuse(const UFArgs<VAR == kBatch> args) {
     const int rest = tile / p.chunks;
     const int xb = rest % p.x_blocks;
     const int y = ROWS > 1 ? rest / p.x_blocks * ROWS + (wave >> 2) : rest / p.x_blocks;
-    const int x0w = xb * (4 * PIX) + (ROWS > 1 ? wave & 3 : wave) * PIX;   // first pixel of this wave
-    if (x0w >= p.W || (ROWS > 1 && y >= p.H)) return;  // no later barrier: safe to leave
-    const int l_begin = chunk * p.layers_per_chunk;
+    // first pixel of this wave
+    const int x0w = SPLIT ? xb * PIX : xb * (4 * PIX) + (ROWS > 1 ? wave & 3 : wave) * PIX;
+    if (!SPLIT && (x0w >= p.W || (ROWS > 1 && y >= p.H))) return;  // no later barrier: safe to leave
+    const int l_begin = (SPLIT ? wave : chunk) * p.layers_per_chunk;
     const int l_end = min(p.L, l_begin + p.layers_per_chunk);
 
     // operand role of this lane: pixel column n of sub-tile sg, channels
@@ -1321,7 +1330,10 @@ k_update_fuse(const UFArgs<VAR == kBatch> args) {
                 }
                 p.depth_out[pe] = dn;
                 p.alpha_out[pe] = an;
-                if (do_comp) {
+                if constexpr (SPLIT) {
+                    slayer[li * PIX + 16 * s + n] =
+                        make_float4(sigmoidf_(X[td][2]), sigmoidf_(X[td][3]), sigmoidf_(head4), an);
+                } else if (do_comp) {
                     const float w = Tr[td] * an;
                     cr[td][0] = fmaf(w, sigmoidf_(X[td][2]), cr[td][0]);
                     cr[td][1] = fmaf(w, sigmoidf_(X[td][3]), cr[td][1]);
@@ -1330,6 +1342,22 @@ k_update_fuse(const UFArgs<VAR == kBatch> args) {
                 }
             }
         }
+    }
+
+    if constexpr (SPLIT) {
+        // the composite, layer by layer as one wave takes them
+        __syncthreads();
+        if (wave != 0) return;
+        for (int li = 0; li < p.L; ++li)
+#pragma unroll
+            for (int td = 0; td < ND; ++td) {
+                const float4 b = slayer[li * PIX + ((G > 1) ? 16 * (2 * td + g / 2) : 0) + n];
+                const float w = Tr[td] * b.w;
+                cr[td][0] = fmaf(w, b.x, cr[td][0]);
+                cr[td][1] = fmaf(w, b.y, cr[td][1]);
+                cr[td][2] = fmaf(w, b.z, cr[td][2]);
+                Tr[td] *= (1.0f - b.w);
+            }
     }
 
     if (do_comp) {
@@ -1379,10 +1407,43 @@ struct UFLaunch {
     const UFBatch *batch;
 };
 
+// Whether a composited level's layers are split over a workgroup's waves (SPLIT):
+// a wave then takes a quarter of the layers of 16 G pixels instead of all of
+// them, so that a small level, whose time is one wave's chain of layers, is up
+// to 3 times shorter.  A workgroup does a quarter of the work for the same
+// preparation of weights, so a level that fills the chip loses by it: the split
+// workgroups have to run at once (3 on a CU in bfloat16 and 2 in float32, 1 at
+// C = 64) and, of few layers, fewer; from 10 layers on two rounds of them still
+// gain.  Measured with 4 views, split workgroups and layers, us split against not:
+// bfloat16, C = 32 folded: 192, 2: 8.3 / 11.3; 576, 5: 13.6 / 19.9; 1212, 5: 22 /
+// 22; 1212, 12: 34 / 50.  float32, C = 32: 192, 2: 11.1 / 15.0; 576, 2: 14 / 15.6,
+// 5: 30 / 27, 12: 44 / 56; 1212, 12: 67 / 75, 5: 37 / 38; C = 16: 1080, 9: 68 / 64,
+// 12: 71 / 82.  C = 64, float32: 192, 2: 24 / 32; 576, 2: 70 / 34, 12: 141 / 127.
+// A 64 x 48 level of 4 layers and 2 views (C = 16, float32): 12.7 / 21.8; 128 x 72, 24
+// layers, 8 views, 4 heads, bfloat16: 55 / 138.
+template <int C, bool BF16>
+static bool splits(const UFParams &p) {
+    constexpr int PIX = Shape<C>::PIX, AT_ONCE = C == 64 ? 256 : BF16 ? 768 : 512;
+    if (p.rgb == nullptr || p.chunks != 1 || p.L < 2 || p.L * PIX > kSplitPixels) return false;
+    const int64_t tiles = (int64_t)((p.W + PIX - 1) / PIX) * p.H;
+    const int most = C < 64 && p.L >= 10 ? 1280 : 128 * p.L < AT_ONCE ? 128 * p.L : AT_ONCE;
+    return tiles <= most;
+}
+
 // One level.
 template <int C, bool BF16, bool FOLD, bool F8, int HD, int VAR>
 static hipError_t launch_level(const UFParams &p, hipStream_t s) {
     UFArgs<false> a{p};
+    if constexpr (VAR == kPlain && !F8) {
+        if (splits<C, BF16>(p)) {
+            a.p.x_blocks = (p.W + Shape<C>::PIX - 1) / Shape<C>::PIX;
+            a.p.layers_per_chunk = (p.L + 3) / 4;
+            a.p.n_tiles = a.p.x_blocks * p.H;
+            hipLaunchKernelGGL((k_update_fuse<C, BF16, FOLD, F8, HD, VAR, 1, true>), dim3(a.p.n_tiles), dim3(256),
+                               0, s, a);
+            return hipGetLastError();
+        }
+    }
     if constexpr (C == 64 && kReassoc<C, BF16, FOLD, HD>) {
         const int rows2 = p.x_blocks * ((p.H + 1) / 2) * p.chunks;   // tiles of two rows
         if (rows2 >= 256) {
