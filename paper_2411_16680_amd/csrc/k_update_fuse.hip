@@ -704,10 +704,13 @@ k_update_fuse(const UFArgs<VAR == kBatch> args) {
     // ---- weight fragments from the float32 master weights, once per
     // workgroup.  Fragment lane (c, k) holds element [k-slot 8k..8k+7][c] of
     // W (the A operand of the transposed products).  Every projection is
-    // block-diagonal over the G sub-tiles.
-    for (int e = tid; e < FR::N * 64; e += THREADS) {
-        const int f = e >> 6, ln = e & 63;
-        const int nn = ln & 15, gg = ln >> 4;
+    // block-diagonal over the G sub-tiles.  A lane's 8 elements are a fixed
+    // step apart, so a wave asks for several fragments' before it waits for
+    // the first (one fragment at a time is a wait on L2 each: a 48 x 32 level of 2
+    // layers, C = 64 in bfloat16, took 25.7 us, now 14.9).
+    constexpr int NW = THREADS / 64, AHEAD = FR::N > 3 * NW ? 4 : (FR::N + NW - 1) / NW;
+    const int ln = tid & 63, nn = ln & 15, gg = ln >> 4;
+    auto load_frag = [&](int f, float vals[8]) {    // f is uniform over the wave
         // kinds: 0 Q, 1 K, 2 V, 3 O, 4 decode (no K/V slots in the
         // one-to-many form: the O slots follow Q); reassociated form: 5 W_k
         // on the query, 6 W_v on the output
@@ -721,47 +724,68 @@ k_update_fuse(const UFArgs<VAR == kBatch> args) {
         const int ntile = (kind == 4) ? ND : NT;
         const int kc = fi / ntile, t = fi % ntile;
         const int ng = 16 * t + nn;               // output channel row of this lane
+        const int kap = 32 * kc + 8 * gg;         // K slots kap + i: sub-tile kap / C, channel kap % C + i
         const float *Wm = kind == 0 ? (FOLD ? p.Wqk + (size_t)head * C * C : p.Wq)
                         : (kind == 1 || (RE && kind == 5)) ? p.Wk
                         : (kind == 2 || (RE && kind == 6)) ? p.Wv
                         : (FOLD ? p.Wvo : p.Wo);
-        float vals[8];
+        // element i: src[i * step] where `in`, else zero
+        const float *src;
+        int step = C;
+        bool in;
+        if (TAPK && (kind == 1 || kind == 2)) {
+            // K slot kap + i = tap gg + 4 kc x channel i; output rows
+            // 8t..8t+7 of the tile hold row-group t of a pair
+            in = nn / 8 == t;
+            if constexpr (OTM) {                    // the blended sample itself
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int kap = 32 * kc + 8 * gg + i;   // K slot: sub-tile kap / C, channel kap % C
-            float w = 0.0f;
-            if (TAPK && (kind == 1 || kind == 2)) {
-                // K slot kap = tap (kap / 8) x channel (kap % 8); output rows
-                // 8t..8t+7 of the tile hold row-group t of a pair
-                if (nn / 8 == t) {
-                    if (OTM) w = (kap % 8 == nn % 8) ? 1.0f : 0.0f;      // the blended sample itself
-                    else w = Wm[(kap % 8) * C + (nn % 8)];
-                }
-            } else if (HQ > 1 && kind == 3) {
-                // output projection over the heads' concatenation: K slot kap
-                // is channel kap % C of head kap / C
-                w = (Wm + (size_t)(kap / C) * C * C)[(kap % C) * C + ng];
-            } else if (kind < 4 || (RE && kind == 6)) {
-                if (kap / C == ng / C) w = Wm[(kap % C) * C + (ng % C)];
-            } else if (RE && kind == 5) {           // transposed: W_k q
-                if (kap / C == ng / C) w = Wm[(ng % C) * C + (kap % C)];
-            } else {                                // decode heads: sigma, depth, r, g, b
-                const int s = (G == 1) ? 0 : ng / 8;
-                const int j = (G == 1) ? ng : ng % 8;
-                if (kap / C == s && j < 5) {
-                    const int c = kap % C;
-                    w = (j == 0) ? p.w_sigma[c] : (j == 1) ? p.w_depth[c] : p.W_color[c * 3 + (j - 2)];
-                }
+                for (int i = 0; i < 8; ++i) vals[i] = in && i == nn % 8 ? 1.0f : 0.0f;
+                return;
             }
-            vals[i] = w;
+            src = Wm + nn % 8;
+        } else if (HQ > 1 && kind == 3) {
+            // output projection over the heads' concatenation: K slot kap
+            // is channel kap % C of head kap / C
+            src = Wm + (size_t)(kap / C) * C * C + (kap % C) * C + ng;
+            in = true;
+        } else if (kind < 4 || (RE && kind == 6)) {
+            src = Wm + (kap % C) * C + (ng % C);
+            in = kap / C == ng / C;
+        } else if (RE && kind == 5) {               // transposed: W_k q
+            src = Wm + (ng % C) * C + (kap % C);
+            step = 1;
+            in = kap / C == ng / C;
+        } else {                                    // decode heads: sigma, depth, r, g, b
+            const int j = (G == 1) ? ng : ng % 8;
+            in = kap / C == ((G == 1) ? 0 : ng / 8) && j < 5;
+            step = j < 2 ? 1 : 3;
+            src = j == 0 ? p.w_sigma + kap % C : j == 1 ? p.w_depth + kap % C : p.W_color + (kap % C) * 3 + (j - 2);
         }
+        src = in ? src : p.w_sigma;
+        step = in ? step : 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) vals[i] = src[i * step];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) vals[i] = in ? vals[i] : 0.0f;
+    };
+    auto put_frag = [&](int f, const float vals[8]) {
         if constexpr (F8) {
-            if (kind < 4) {
+            if (f < FR::OFF_D) {
+                const int kind = f < FR::OFF_K ? 0 : f < FR::OFF_V ? 1 : f < FR::OFF_O ? 2 : 3;
                 *reinterpret_cast<MA *>(&sfrag[f][ln]) = MM::make(vals, 1.0f / f8s[2 + kind]);
-                continue;
+                return;
             }
         }
         sfrag[f][ln] = OP::make(vals);
+    };
+    for (int f0 = __builtin_amdgcn_readfirstlane(tid >> 6); f0 < FR::N; f0 += AHEAD * NW) {
+        float vals[AHEAD][8];
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u)
+            if (f0 + u * NW < FR::N) load_frag(f0 + u * NW, vals[u]);
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u)
+            if (f0 + u * NW < FR::N) put_frag(f0 + u * NW, vals[u]);
     }
     if constexpr (PADTAB) {
         for (int e = tid; e < p.V * 12; e += 256) *padw(e) = p.cam[e / 12][e % 12];
@@ -1413,21 +1437,20 @@ struct UFLaunch {
 // to 3 times shorter.  A workgroup does a quarter of the work for the same
 // preparation of weights, so a level that fills the chip loses by it: the split
 // workgroups have to run at once (3 on a CU in bfloat16 and 2 in float32, 1 at
-// C = 64) and, of few layers, fewer; from 10 layers on two rounds of them still
-// gain.  Measured with 4 views, split workgroups and layers, us split against not:
-// bfloat16, C = 32 folded: 192, 2: 8.3 / 11.3; 576, 5: 13.6 / 19.9; 1212, 5: 22 /
-// 22; 1212, 12: 34 / 50.  float32, C = 32: 192, 2: 11.1 / 15.0; 576, 2: 14 / 15.6,
-// 5: 30 / 27, 12: 44 / 56; 1212, 12: 67 / 75, 5: 37 / 38; C = 16: 1080, 9: 68 / 64,
-// 12: 71 / 82.  C = 64, float32: 192, 2: 24 / 32; 576, 2: 70 / 34, 12: 141 / 127.
-// A 64 x 48 level of 4 layers and 2 views (C = 16, float32): 12.7 / 21.8; 128 x 72, 24
-// layers, 8 views, 4 heads, bfloat16: 55 / 138.
+// C = 64), or in two rounds from 7 layers on.  Measured with 4 views, split
+// workgroups and layers, us split against not: bfloat16, C = 32 folded: 576, 2:
+// 6.8 / 9.1; 1212, 2: 11.2 / 10.3, 5: 18 / 20, 7: 19 / 27, 12: 29 / 46; 3600, 7:
+// 47 / 42.  float32, C = 16: 288, 2: 9.9 / 13.2; 606, 2: 15.6 / 13.6, 5: 26 / 27, 7:
+// 27 / 36; 1080, 5: 40 / 36, 7: 43 / 48, 12: 60 / 78; 1800, 7: 62 / 60.  C = 64,
+// bfloat16: 96, 2: 10.7 / 14.9; 576, 2: 31 / 16, 12: 63 / 64.  A 64 x 48 level of 4
+// layers and 2 views (C = 16, float32): 13 / 22; 128 x 72, 24 layers, 8 views, 4
+// heads, bfloat16: 49 / 138 (138 with the slower preparation of weights too).
 template <int C, bool BF16>
 static bool splits(const UFParams &p) {
     constexpr int PIX = Shape<C>::PIX, AT_ONCE = C == 64 ? 256 : BF16 ? 768 : 512;
     if (p.rgb == nullptr || p.chunks != 1 || p.L < 2 || p.L * PIX > kSplitPixels) return false;
     const int64_t tiles = (int64_t)((p.W + PIX - 1) / PIX) * p.H;
-    const int most = C < 64 && p.L >= 10 ? 1280 : 128 * p.L < AT_ONCE ? 128 * p.L : AT_ONCE;
-    return tiles <= most;
+    return tiles <= (C < 64 && p.L >= 7 ? 2 * AT_ONCE : AT_ONCE);
 }
 
 // One level.

@@ -63,9 +63,9 @@ def test_split_step(ctx, case, prec):
             assert torch.equal(x, y)
 
 
-@pytest.mark.parametrize("H", [128, 129])
+@pytest.mark.parametrize("H", [256, 257])
 def test_last_level_that_is_split(ctx, H):
-    """2 layers, C = 32: 128 L = 256 tiles of 16 pixels and one row more."""
+    """2 layers, C = 32, float32: 512 tiles of 16 pixels and one row more."""
     sc = _scene(32, 2, H, 32, 2, 1, "f32", 90)
     lvl = sc.levels[0]
     dl = runner.level_to_device(lvl)
