@@ -27,7 +27,7 @@
 // What bounds it: with the fragments in LDS every product read 1.5 operands and
 // the LDS pipe was busy throughout; now it is vector work (GELU, normalisation,
 // ~55 % busy) beside the matrix cores (~25 %).  16 layers of 480x270: 193 -> 134
-// us (570 TFLOP/s), the same bits.  Both kernels' fragments in registers (144)
+// us (570 TFLOP/s), the same bits.  The tile's height is chosen per call (launcher).  Both kernels' fragments in registers (144)
 // spilled and took 298 us; the next tile's input read ahead changed nothing, two
 // workgroups per CU overlap each other's staging.
 #include <hip/hip_runtime.h>
@@ -159,11 +159,12 @@ __global__ void __launch_bounds__(256, 2) k_residual_conv(const ConvParams p) {
     uint2 *mid2 = reinterpret_cast<uint2 *>(s_mid);
 
     // each XCD (workgroups are dispatched round-robin over the 8) takes one
-    // contiguous range of tiles: neighbours share their halos in its L2
-    const int nr = min(8, (int)gridDim.x), r = (int)blockIdx.x % nr;
-    const int64_t t_end = p.n_tiles * (r + 1) / nr;
-    const int t_step = ((int)gridDim.x - r + nr - 1) / nr;
-    for (int64_t t = p.n_tiles * r / nr + (int)blockIdx.x / nr; t < t_end; t += t_step) {
+    // contiguous range of tiles, as many as its share of the workgroups: neighbours
+    // share their halos in its L2, and no workgroup has a tile more than it must
+    const int nb = (int)gridDim.x, r = (int)blockIdx.x & 7, q8 = nb >> 3, rem = nb & 7;
+    const int before = r * q8 + min(r, rem), mine = q8 + (r < rem);
+    const int64_t t_end = p.n_tiles * (before + mine) / nb;
+    for (int64_t t = p.n_tiles * before / nb + ((int)blockIdx.x >> 3); t < t_end; t += mine) {
         const int l = (int)(t / per_layer);
         const int rem = (int)(t - (int64_t)l * per_layer);
         const int ty = rem / p.tiles_x, tx = rem - ty * p.tiles_x;
@@ -272,15 +273,23 @@ hipError_t launch_residual_conv(const ConvParams &pin, int num_cu, bool frag_rea
     ConvParams p = pin;
     p.tiles_x = (p.W + TX - 1) / TX;
     const int64_t slots = 2 * (int64_t)(num_cu > 0 ? num_cu : 256);
-    // 16 rows per tile, or 8 where that makes for less time: rounds of the
-    // resident workgroups times a tile's cost, 9 for 8 rows (its halo is larger)
-    // and 16 for 16 (24 x 36x64: 13.9 against 15.7 us, 24 x 72x128: 25.8 against
-    // 28.1, 6 x 288x512: 80.5 against 67.3)
-    const int64_t n16 = (int64_t)p.L * p.tiles_x * ((p.H + 15) / 16);
-    const int64_t n8 = (int64_t)p.L * p.tiles_x * ((p.H + 7) / 8);
-    const bool small = 9 * ((n8 + slots - 1) / slots) < 16 * ((n16 + slots - 1) / slots);
-    p.tiles_y = (p.H + (small ? 7 : 15)) / (small ? 8 : 16);
-    p.n_tiles = small ? n8 : n16;
+    // The tile's height: a compute unit's time is about 4 us and 1/3 us per tile
+    // and row that the tile stages (TY + 4), so the height with the fewest such
+    // rows per compute unit, the taller of equals.  Measured, us at 2 / 4 / 8 / 16
+    // rows: 2 x 40x64: 5.5 / 6.4 / 7.9 / 11.4; 8 x 64x100: 11.5 / 8.5 / 8.8 / 11.8;
+    // 1 x 288x512: 25 / 21 / 16 / 17; 16 x 135x240: 77 / 52 / 41 / 37.  10 and 12 rows
+    // for where 8 make just more than a tile per unit: 5 x 72x154: 9.3 at 10, 10.4 at
+    // 12, 11.0 at 8; 1 x 288x512: 14.1 at 12.
+    const int64_t cus = num_cu > 0 ? num_cu : 256;
+    int ty = 16;
+    int64_t best = INT64_MAX;
+    for (int h : {16, 12, 10, 8, 4, 2}) {
+        const int64_t n = (int64_t)p.L * p.tiles_x * ((p.H + h - 1) / h);
+        const int64_t cost = (n + cus - 1) / cus * (h + 4);
+        if (cost < best) best = cost, ty = h;
+    }
+    p.tiles_y = (p.H + ty - 1) / ty;
+    p.n_tiles = (int64_t)p.L * p.tiles_x * p.tiles_y;
     hipError_t e;
     if (!frag_ready) {                           // else p.frag already holds them
         hipLaunchKernelGGL(k_conv_frag, dim3((NFRAG + 255) / 256), dim3(256), 0, s, p);
@@ -288,8 +297,15 @@ hipError_t launch_residual_conv(const ConvParams &pin, int num_cu, bool frag_rea
         if (e != hipSuccess) return e;
     }
     const unsigned blocks = (unsigned)(slots < p.n_tiles ? slots : p.n_tiles);
-    if (small) hipLaunchKernelGGL(k_residual_conv<8>, dim3(blocks), dim3(256), 0, s, p);
-    else hipLaunchKernelGGL(k_residual_conv<16>, dim3(blocks), dim3(256), 0, s, p);
+    const dim3 gr(blocks), bl(256);
+    switch (ty) {
+    case 2: hipLaunchKernelGGL(k_residual_conv<2>, gr, bl, 0, s, p); break;
+    case 4: hipLaunchKernelGGL(k_residual_conv<4>, gr, bl, 0, s, p); break;
+    case 8: hipLaunchKernelGGL(k_residual_conv<8>, gr, bl, 0, s, p); break;
+    case 10: hipLaunchKernelGGL(k_residual_conv<10>, gr, bl, 0, s, p); break;
+    case 12: hipLaunchKernelGGL(k_residual_conv<12>, gr, bl, 0, s, p); break;
+    default: hipLaunchKernelGGL(k_residual_conv<16>, gr, bl, 0, s, p); break;
+    }
     return hipGetLastError();
 }
 
