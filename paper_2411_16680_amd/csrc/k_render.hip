@@ -22,7 +22,7 @@
 // takes positions from the image's centre on (one comparison per axis), a wave
 // inside the image masks nothing, and texels enter the blend as halves
 // (add_sample).  1080p from 512 x 288, 6 layers, under the profiler: 8 views
-// 402 us before, 296 now (355 and 267 without it); 5 views, which ran online,
+// 402 us before, 296 now (355 and 267 to 287 without it); 5 views, which ran online,
 // 331 and 240.  Did not help: the logit taps in LDS (296; fewer loads, as many
 // more instructions), a layer's logits read ahead (305), 128 registers for a
 // fourth wave (305, spills), 64 x 4 and 32 x 8 tiles (294).
