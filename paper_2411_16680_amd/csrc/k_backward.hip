@@ -39,6 +39,7 @@
 
 #include "uf_params.h"
 #include "vbin.h"
+#include "view_order.h"
 
 namespace qk {
 namespace {
@@ -378,15 +379,6 @@ __device__ __forceinline__ void outer_rows(const float *a, const float *b, int n
                                                    b[(4 * s + g) * kRow<C> + c], acc, 0, 0, 0);
 }
 
-// Calls f(integral_constant<int, K>) for K = B .. N - 1.
-template <int B, int N, typename F>
-__device__ __forceinline__ void static_for(F &&f) {
-    if constexpr (B < N) {
-        f(std::integral_constant<int, B>{});
-        static_for<B + 1, N>(f);
-    }
-}
-
 // How the samples' gradients reach the maps: float atomics (32-bit byte
 // offsets, or for maps of 2 GiB and more 64-bit addresses), or rows of ds in
 // memory for the sorted scatter -- with up to kKeep views the taps of the first
@@ -513,25 +505,17 @@ k_uf_backward(const BwdParams p) {
                     if (k < p.V) step(kept[k], k);
                 });
             } else {
-                Taps ta, tb;
-                proj(0);
-                issue_taps<C, WIDE, 0>(p, 0, mine, chunk, ta);
-                for (int m0 = 0; m0 < p.V; m0 += LPP) {
-                    static_for<0, LPP>([&](auto kk) {
-                        constexpr int k = decltype(kk)::value;
-                        Taps &cur = k % 2 == 0 ? ta : tb, &nxt = k % 2 == 0 ? tb : ta;
-                        const int mn = min(m0 + k + 1, p.V - 1);
-                        if constexpr (k + 1 < LPP) {
-                            issue_taps<C, WIDE, k + 1>(p, mn, mine, chunk, nxt);
-                        } else {
-                            if (m0 + LPP < p.V) proj(m0 + LPP);
-                            issue_taps<C, WIDE, 0>(p, mn, mine, chunk, nxt);
-                        }
+                Taps buf[2];
+                views_in_order<LPP>(
+                    p.V, proj,
+                    [&](auto kk, int m, auto slot) {
+                        issue_taps<C, WIDE, decltype(kk)::value>(p, m, mine, chunk, buf[decltype(slot)::value]);
+                    },
+                    [&](int m, auto slot) {
                         __builtin_amdgcn_sched_barrier(0);
-                        if (m0 + k < p.V) step(cur, m0 + k);
+                        step(buf[decltype(slot)::value], m);
                         __builtin_amdgcn_sched_barrier(0);
                     });
-                }
             }
         };
 
