@@ -159,9 +159,7 @@ typedef struct qk_context qk_context;
  * workspaces that grow on demand and live until qk_context_destroy: the
  * folded weights of the one-to-many form (2 C C_feat floats per request),
  * the e4m3 scales (8 floats), the backward pass's scratch (16 bytes per
- * layer-pixel when d_rgb is given, plus 5 KiB per backward workgroup, plus,
- * where it is 4 GiB or less, fits the cap and can be had, 4 C + 4 bytes per
- * layer-pixel and view for larger problems), the
+ * layer-pixel when d_rgb is given, plus 5 KiB per backward workgroup), the
  * render to input views' records (4 bytes per layer-pixel-view) or
  * projected planes, the low-resolution ray encodings, the residual block's
  * weight fragments and the batched launch's parameter table.  Growing one
@@ -169,7 +167,12 @@ typedef struct qk_context qk_context;
  * their total (0: no cap): a call whose workspace would pass the cap
  * returns QK_ENOMEM, the message naming the bytes it needed (launches of
  * the same call before the failing growth may have been enqueued; they
- * write only the context's workspace).  A context may be used from one host
+ * write only the context's workspace).  For larger problems the backward
+ * pass also takes about 4 C + 4 bytes per layer-pixel and view, where that is
+ * 4 GiB or less, fits the cap and can be had, and works without otherwise
+ * (slower): it never asks under stream capture, nor again for a size the
+ * device had no memory for, and gives this part up to a growth above that
+ * needs the room, unless a captured call uses it.  A context may be used from one host
  * thread at a time; calls that share it on different streams race on its
  * workspaces.  Errors: QK_EINVAL (out == NULL, no such device), QK_EHIP. */
 QK_API qk_status qk_context_create(int device, size_t workspace_bytes, qk_context **out);

@@ -44,6 +44,10 @@ struct qk_context {
     size_t wfold_elems = 0;
     float *bws = nullptr;        // backward workspace: composite adjoint + partials
     size_t bws_elems = 0;
+    float *sws = nullptr;        // the backward's sorted scatter, which it can do without
+    size_t sws_elems = 0;
+    size_t sws_refused = SIZE_MAX;   // floats of it the device had no memory for
+    bool sws_captured = false;   // a captured call uses it: it stays where it is
     float *f8 = nullptr;         // e4m3 scales [7] + running maximum [1]
     size_t f8_elems = 0;
     float *vws = nullptr;        // projected planes of the render to input views
@@ -377,31 +381,88 @@ qk_status check_backward(int32_t V, const qk_camera *in_cams, const qk_feature_m
     return QK_OK;
 }
 
-// Grow a context buffer to at least `need` floats (synchronising the stream
-// before a buffer in use is replaced).
+// Whether `more` further bytes pass the cap on the workspaces.
+bool past_cap(const qk_context *ctx, size_t more) {
+    return ctx->ws_cap != 0 && ctx->ws_bytes + more > ctx->ws_cap;
+}
+
+// Frees a context buffer after the stream's work.
+qk_status release(qk_context *ctx, float **buf, size_t *have, hipStream_t stream) {
+    if (!*buf) return QK_OK;
+    hipError_t se = hipStreamSynchronize(stream);
+    if (se != hipSuccess) return fail(QK_EHIP, "hipStreamSynchronize: %s", hipGetErrorString(se));
+    (void)hipFree(*buf);
+    *buf = nullptr;
+    ctx->ws_bytes -= *have * sizeof(float);
+    *have = 0;
+    return QK_OK;
+}
+
+// `elems` floats within the context's cap on their total.  Where the cap or the
+// device's memory does not leave them, the sorted scatter's workspace is given
+// up for them (and under a cap asked for again only while it fits beside them).
+qk_status allocate(qk_context *ctx, size_t elems, hipStream_t stream, bool give_up, float **out) {
+    const size_t bytes = elems * sizeof(float);
+    *out = nullptr;
+    give_up = give_up && ctx->sws != nullptr && !ctx->sws_captured;
+    if (give_up && past_cap(ctx, bytes) && !past_cap(ctx, bytes - std::min(bytes, ctx->sws_elems * sizeof(float)))) {
+        qk_status st = release(ctx, &ctx->sws, &ctx->sws_elems, stream);
+        if (st != QK_OK) return st;
+    }
+    if (past_cap(ctx, bytes))
+        return fail(QK_ENOMEM, "workspace of %zu bytes in all would pass the context's cap of %zu",
+                    ctx->ws_bytes + bytes, ctx->ws_cap);
+    float *buf = nullptr;
+    hipError_t e = hipMalloc(&buf, bytes);
+    if (e != hipSuccess && give_up && ctx->sws != nullptr) {
+        (void)hipGetLastError();             // not the call's error yet
+        ctx->sws_refused = std::min(ctx->sws_refused, ctx->sws_elems);
+        qk_status st = release(ctx, &ctx->sws, &ctx->sws_elems, stream);
+        if (st != QK_OK) return st;
+        e = hipMalloc(&buf, bytes);
+    }
+    if (e != hipSuccess) return fail(QK_ENOMEM, "workspace of %zu floats", elems);
+    ctx->ws_bytes += bytes;
+    *out = buf;
+    return QK_OK;
+}
+
 // Grow one of the context's device workspaces to `need` floats (never
-// shrinks), within the context's cap on their total.
+// shrinks), synchronising the stream before a buffer in use is replaced.
 qk_status grow(qk_context *ctx, float **buf, size_t *have, size_t need, hipStream_t stream) {
     if (*have >= need) return QK_OK;
-    const size_t total = ctx->ws_bytes - *have * sizeof(float) + need * sizeof(float);
-    if (ctx->ws_cap != 0 && total > ctx->ws_cap)
+    const size_t held = *have * sizeof(float), more = need * sizeof(float) - held;
+    const size_t spare = buf == &ctx->sws || ctx->sws_captured ? 0 : ctx->sws_elems * sizeof(float);
+    if (past_cap(ctx, more) && past_cap(ctx, more - std::min(more, spare)))
         return fail(QK_ENOMEM, "workspace of %zu bytes in all would pass the context's cap of %zu",
-                    total, ctx->ws_cap);
-    if (*buf) {
-        hipError_t se = hipStreamSynchronize(stream);
-        if (se != hipSuccess) return fail(QK_EHIP, "hipStreamSynchronize: %s", hipGetErrorString(se));
-        (void)hipFree(*buf);
-        *buf = nullptr;
-        ctx->ws_bytes -= *have * sizeof(float);
-        *have = 0;
+                    ctx->ws_bytes + more, ctx->ws_cap);
+    qk_status st = release(ctx, buf, have, stream);
+    if (st == QK_OK) st = allocate(ctx, need, stream, buf != &ctx->sws, buf);
+    if (st == QK_OK) *have = need;
+    return st;
+}
+
+// Whether the sorted scatter's workspace of `need` floats is there or can be had.
+// A size the device refused is not asked for again, and nothing is while the
+// stream is captured: such calls neither allocate nor wait.
+bool have_sorted(qk_context *ctx, size_t need, hipStream_t stream) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusActive;
+    bool capture = true;
+    if (hipStreamIsCapturing(stream, &status) == hipSuccess) capture = status != hipStreamCaptureStatusNone;
+    else (void)hipGetLastError();
+    if (ctx->sws_elems >= need) {
+        ctx->sws_captured = ctx->sws_captured || capture;
+        return true;
     }
-    if (hipMalloc(buf, need * sizeof(float)) != hipSuccess) {
-        *buf = nullptr;
-        return fail(QK_ENOMEM, "workspace of %zu floats", need);
+    if (capture || ctx->sws_captured || need >= ctx->sws_refused ||
+        past_cap(ctx, (need - ctx->sws_elems) * sizeof(float)))
+        return false;
+    const qk_status st = grow(ctx, &ctx->sws, &ctx->sws_elems, need, stream);
+    if (st == QK_ENOMEM) {
+        (void)hipGetLastError();             // a failed allocation is not the call's error
+        ctx->sws_refused = need;
     }
-    *have = need;
-    ctx->ws_bytes += need * sizeof(float);
-    return QK_OK;
+    return st == QK_OK;
 }
 
 // Derived weights (qk_context_weights_static): the folded attention weights
@@ -420,16 +481,12 @@ float *derived_find(qk_context *ctx, int kind, const void *const key[4], const i
 // A new entry of `elems` floats, counted against the workspace cap; *out is
 // NULL (and the status QK_OK) when the context keeps no more entries.
 qk_status derived_add(qk_context *ctx, int kind, const void *const key[4], const int32_t dims[4],
-                      size_t elems, float **out) {
+                      size_t elems, hipStream_t stream, float **out) {
     *out = nullptr;
     if (ctx->derived.size() >= kDerivedMax) return QK_OK;
-    const size_t total = ctx->ws_bytes + elems * sizeof(float);
-    if (ctx->ws_cap != 0 && total > ctx->ws_cap)
-        return fail(QK_ENOMEM, "workspace of %zu bytes in all would pass the context's cap of %zu",
-                    total, ctx->ws_cap);
     float *buf = nullptr;
-    if (hipMalloc(&buf, elems * sizeof(float)) != hipSuccess)
-        return fail(QK_ENOMEM, "derived weights of %zu floats", elems);
+    qk_status st = allocate(ctx, elems, stream, true, &buf);
+    if (st != QK_OK) return st;
     qk_context::Derived d;
     d.kind = kind;
     std::copy(key, key + 4, d.key);
@@ -437,7 +494,6 @@ qk_status derived_add(qk_context *ctx, int kind, const void *const key[4], const
     d.buf = buf;
     d.elems = elems;
     ctx->derived.push_back(d);
-    ctx->ws_bytes += elems * sizeof(float);
     *out = buf;
     return QK_OK;
 }
@@ -471,7 +527,7 @@ qk_status fold_weights(qk_context *ctx, const qk_weights *w, float *dst, hipStre
         wf = derived_find(ctx, kDerivedFold, key, dims);
         fresh = wf == nullptr;
         if (fresh) {
-            qk_status st = derived_add(ctx, kDerivedFold, key, dims, 2 * per, &wf);
+            qk_status st = derived_add(ctx, kDerivedFold, key, dims, 2 * per, stream, &wf);
             if (st != QK_OK) return st;
         }
     }
@@ -734,13 +790,14 @@ qk_status qk_context_create(int device, size_t workspace_bytes, qk_context **out
 }
 
 qk_status qk_context_destroy(qk_context *ctx) {
-    if (ctx && (ctx->wfold || ctx->bws || ctx->f8 || ctx->vws || ctx->cfrag || ctx->rws ||
+    if (ctx && (ctx->wfold || ctx->bws || ctx->sws || ctx->f8 || ctx->vws || ctx->cfrag || ctx->rws ||
                 ctx->bdesc || ctx->bhost || ctx->bevent || !ctx->derived.empty())) {
         int cur = -1;
         if (hipGetDevice(&cur) == hipSuccess && cur != ctx->device) (void)hipSetDevice(ctx->device);
         (void)derived_clear(ctx);
         if (ctx->wfold) (void)hipFree(ctx->wfold);
         if (ctx->bws) (void)hipFree(ctx->bws);
+        if (ctx->sws) (void)hipFree(ctx->sws);
         if (ctx->f8) (void)hipFree(ctx->f8);
         if (ctx->vws) (void)hipFree(ctx->vws);
         if (ctx->cfrag) (void)hipFree(ctx->cfrag);
@@ -1236,7 +1293,8 @@ qk_status qk_update_fuse_backward(qk_context *ctx, void *hip_stream, int32_t V,
     hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
     const size_t n_comp = d_rgb ? 4 * (size_t)p.N : 0;
     const size_t n_part = (size_t)p.blocks * qk::kGradTiles * qk::kGradTileElems;
-    const size_t n_base = (n_comp + n_part + 3) & ~(size_t)3;
+    st = grow(ctx, &ctx->bws, &ctx->bws_elems, n_comp + n_part, stream);
+    if (st != QK_OK) return st;
     // The sorted scatter of the feature-map gradients where its workspace (the
     // samples' gradients and the bins) is at most 4 GiB, fits the cap and can be
     // had; float atomics otherwise.
@@ -1246,17 +1304,9 @@ qk_status qk_update_fuse_backward(qk_context *ctx, void *hip_stream, int32_t V,
     for (int m = 0; m < V; ++m) tiles_f += qk::scatter_tiles(feats[m].H, feats[m].W);
     const size_t n_sort = (size_t)records * in->C + (size_t)qk::scatter_bin_words(tiles_f, records);
     sorted = sorted && tiles_f < ((int64_t)1 << 28) && n_sort <= ((size_t)1 << 30);
-    if (sorted && ctx->bws_elems < n_base + n_sort && ctx->ws_cap != 0)
-        sorted = ctx->ws_bytes - ctx->bws_elems * sizeof(float) + (n_base + n_sort) * sizeof(float) <= ctx->ws_cap;
-    st = grow(ctx, &ctx->bws, &ctx->bws_elems, n_base + (sorted ? n_sort : 0), stream);
-    if (st == QK_ENOMEM && sorted) {
-        (void)hipGetLastError();             // a failed allocation is not the call's error
-        sorted = false;
-        st = grow(ctx, &ctx->bws, &ctx->bws_elems, n_base, stream);
-    }
-    if (st != QK_OK) return st;
+    sorted = sorted && have_sorted(ctx, n_sort, stream);
     if (sorted) {
-        p.ds = ctx->bws + n_base;
+        p.ds = ctx->sws;
         p.bins = reinterpret_cast<uint32_t *>(p.ds + (size_t)records * in->C);
         if (V <= qk::kBwdKeep)
             p.blocks = (int32_t)std::min<int64_t>(p.blocks, qk::kBwdWavesKeep * (int64_t)ctx->num_cu);
@@ -1465,7 +1515,7 @@ qk_status qk_residual_conv(qk_context *ctx, void *hip_stream, const qk_ldm *in, 
         frag = derived_find(ctx, kDerivedConv, key, dims);
         fresh = frag == nullptr;
         if (fresh) {
-            st = derived_add(ctx, kDerivedConv, key, dims, kFragFloats, &frag);
+            st = derived_add(ctx, kDerivedConv, key, dims, kFragFloats, stream, &frag);
             if (st != QK_OK) return st;
         }
     }
