@@ -1291,25 +1291,26 @@ qk_status qk_update_fuse_backward(qk_context *ctx, void *hip_stream, int32_t V,
     if (cur != ctx->device && hipSetDevice(ctx->device) != hipSuccess)
         return fail(QK_EHIP, "hipSetDevice(%d) failed", ctx->device);
     hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
-    const size_t n_comp = d_rgb ? 4 * (size_t)p.N : 0;
-    const size_t n_part = (size_t)p.blocks * qk::kGradTiles * qk::kGradTileElems;
-    st = grow(ctx, &ctx->bws, &ctx->bws_elems, n_comp + n_part, stream);
-    if (st != QK_OK) return st;
     // The sorted scatter of the feature-map gradients where its workspace (the
     // samples' gradients and the bins) is at most 4 GiB, fits the cap and can be
-    // had; float atomics otherwise.
+    // had; float atomics otherwise.  The workgroups follow from the sizes alone:
+    // each sums its share of the weight gradients, which are the same bits whatever
+    // memory is left.
     const int64_t records = V * p.N;
     int64_t tiles_f = 0;
     bool sorted = !p.wide && records * in->C >= kScatterMin && records < ((int64_t)1 << 31);
     for (int m = 0; m < V; ++m) tiles_f += qk::scatter_tiles(feats[m].H, feats[m].W);
     const size_t n_sort = (size_t)records * in->C + (size_t)qk::scatter_bin_words(tiles_f, records);
     sorted = sorted && tiles_f < ((int64_t)1 << 28) && n_sort <= ((size_t)1 << 30);
-    sorted = sorted && have_sorted(ctx, n_sort, stream);
-    if (sorted) {
+    const size_t n_comp = d_rgb ? 4 * (size_t)p.N : 0;
+    const size_t n_part = (size_t)p.blocks * qk::kGradTiles * qk::kGradTileElems;   // for any number of views
+    if (sorted && V <= qk::kBwdKeep)
+        p.blocks = (int32_t)std::min<int64_t>(p.blocks, qk::kBwdWavesKeep * (int64_t)ctx->num_cu);
+    st = grow(ctx, &ctx->bws, &ctx->bws_elems, n_comp + n_part, stream);
+    if (st != QK_OK) return st;
+    if (sorted && have_sorted(ctx, n_sort, stream)) {
         p.ds = ctx->sws;
         p.bins = reinterpret_cast<uint32_t *>(p.ds + (size_t)records * in->C);
-        if (V <= qk::kBwdKeep)
-            p.blocks = (int32_t)std::min<int64_t>(p.blocks, qk::kBwdWavesKeep * (int64_t)ctx->num_cu);
     }
     p.partials = ctx->bws;
     p.comp = d_rgb ? ctx->bws + n_part : nullptr;

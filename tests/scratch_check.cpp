@@ -134,6 +134,7 @@ int main() {
     CHECK(qk_context_create(0, 0, &ctx) == QK_OK);
     CHECK(backward(ctx, V, L) == QK_OK);
     CHECK(g_bwd.ds != nullptr);
+    const int blocks = g_bwd.blocks;
     CHECK(backward(ctx, V, L) == QK_OK && g_bwd.ds != nullptr);
     CHECK(g_allocs == 0 && g_frees == 0 && g_syncs == 0);
     // under capture a larger problem than ever takes the way that needs no allocation
@@ -147,11 +148,11 @@ int main() {
     CHECK(g_live == 0);
 
     // memory for the small workspace alone: refused once, then neither asked for
-    // nor waited for
+    // nor waited for; the same workgroups, so the same weight gradients
     g_memory = rows;
     CHECK(qk_context_create(0, 0, &ctx) == QK_OK);
     CHECK(backward(ctx, V, L) == QK_OK);
-    CHECK(g_bwd.ds == nullptr);
+    CHECK(g_bwd.ds == nullptr && g_bwd.blocks == blocks);
     CHECK(backward(ctx, V, L) == QK_OK && g_bwd.ds == nullptr);
     CHECK(g_allocs == 0 && g_frees == 0 && g_syncs == 0);
     g_capturing = true;
@@ -166,7 +167,7 @@ int main() {
     CHECK(qk_context_create(0, rows + ((size_t)48 << 20), &ctx) == QK_OK);
     CHECK(backward(ctx, V, L) == QK_OK && g_bwd.ds != nullptr);
     CHECK(views(ctx, 8, 1024, 2048) == QK_OK);  // 64 MiB of records
-    CHECK(backward(ctx, V, L) == QK_OK && g_bwd.ds == nullptr);
+    CHECK(backward(ctx, V, L) == QK_OK && g_bwd.ds == nullptr && g_bwd.blocks == blocks);
     CHECK(g_allocs == 0 && g_frees == 0 && g_syncs == 0);
     CHECK(views(ctx, 8, 1024, 2048) == QK_OK && g_allocs == 0);
     CHECK(views(ctx, 16, 2048, 4096) == QK_ENOMEM);      // 512 MiB: past the cap in any case

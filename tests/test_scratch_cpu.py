@@ -1,7 +1,7 @@
 """The context's workspaces at their limits (CPU, the C-ABI linked with a
 stand-in for the HIP runtime): the backward's optional scratch is refused once
-and not asked for again, never under capture, and is given back to a call that
-has to have the room."""
+and not asked for again, never under capture, is given back to a call that has
+to have the room, and does not change the weight gradients' workgroups."""
 
 import os
 import shutil

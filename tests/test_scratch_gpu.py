@@ -46,3 +46,19 @@ def test_workspace_is_given_up_under_a_cap(level):
     for g in (a, b):
         for x, y in zip(g["feats"], c["feats"]):
             assert np.max(np.abs(x - y)) <= 1e-5 * np.max(np.abs(y))
+
+
+@pytest.mark.parametrize("C,V,H,W,L", [(16, 4, 131, 251, 8), (16, 5, 125, 203, 8), (8, 3, 243, 401, 7),
+                                       (8, 6, 190, 301, 6)])
+def test_weight_gradients_whatever_memory_is_left(C, V, H, W, L):
+    """Each is a sum in a fixed order, also where the maps' gradients take the
+    other way: the same bits."""
+    sc = synth.make_custom(V=V, H=H, W=W, C=C, L=L, seed=91)
+    lvl = sc.levels[0]
+    ups = tb._upstream(lvl, 7)
+    tb._say("weights", C, V)
+    small = lib.Context(0, workspace_bytes=16 * L * H * W + (8 << 20))
+    a = tb._run_backward(lib.Context(0), sc, lvl, mode="residual", **ups)
+    b = tb._run_backward(small, sc, lvl, mode="residual", **ups)
+    for k in tb.NAMES:
+        assert np.array_equal(a[k], b[k]), k
