@@ -708,12 +708,12 @@ k_uf_backward(const BwdParams p) {
                 const float4 ds = make_float4(fmaf(pm, dob.x, da * qv.x), fmaf(pm, dob.y, da * qv.y),
                                               fmaf(pm, dob.z, da * qv.z), fmaf(pm, dob.w, da * qv.w));
                 const float fx = T.p.fx, fy = T.p.fy, ex = 1.f - fx, ey = 1.f - fy;
-                // along x: (1 - fy)(t10 - t00) + fy (t11 - t01), along y alike,
-                // as dot products of ds with the four taps
-                const float g00 = dot4(ds, T.t[0]), g10 = dot4(ds, T.t[1]);
-                const float g01 = dot4(ds, T.t[2]), g11 = dot4(ds, T.t[3]);
-                const float gX = fmaf(ey, g10 - g00, fy * (g11 - g01));
-                const float gY = fmaf(ex, g01 - g00, fx * (g11 - g10));
+                // along x: ds . ((1 - fy)(t10 - t00) + fy (t11 - t01)), along y
+                // alike.  The taps are differenced before the products: what
+                // neighbouring texels have in common, nearly all of a smooth
+                // map, would cancel only after it had been rounded.
+                const float gX = fmaf(ey, dot4(ds, T.t[1] - T.t[0]), fy * dot4(ds, T.t[3] - T.t[2]));
+                const float gY = fmaf(ex, dot4(ds, T.t[2] - T.t[0]), fx * dot4(ds, T.t[3] - T.t[1]));
                 ddv = fmaf(gX, T.p.dx, fmaf(gY, T.p.dy, ddv));
                 if constexpr (SORT) {                        // scattered afterwards
                     if (live_ld)
