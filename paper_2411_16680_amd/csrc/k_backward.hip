@@ -171,18 +171,27 @@ __global__ void __launch_bounds__(kBlock) k_composite_backward(const CompBwdPara
 // through the wave's own LDS rows; no barrier is needed for a slice that one
 // wave writes and reads in order.
 // ---------------------------------------------------------------------------
-__device__ inline float rcp(float x) { return __builtin_amdgcn_rcpf(x); }   // about 1 ulp
+// 1 / x in double to its last bits: recip_d and a second Newton step
+__device__ inline double recip2_d(double x) {
+    const double r = recip_d(x);
+    return fma(r, fma(-x, r, 1.0), r);
+}
+// 1 / x and 1 / sqrt(x) to within a hair of half a unit in the last place: the
+// hardware estimate and a Newton step, for x of ordinary size.  (The estimates
+// alone, about 1 ulp each, showed in the gradients' errors.)
+__device__ inline float rcp1(float x) {
+    const float r = __builtin_amdgcn_rcpf(x);
+    return fmaf(r, fmaf(-x, r, 1.0f), r);
+}
+__device__ inline float rsq1(float x) {
+    const float r = __builtin_amdgcn_rsqf(x);
+    return fmaf(0.5f * r, fmaf(-x * r, r, 1.0f), r);
+}
 // sigma'(x) = sigma(x) sigma(-x) = e / (1 + e)^2 with e = e^-|x|: no
 // cancellation when sigma(x) is near one
 __device__ inline float dsigm(float x) {
-    const float e = __expf(-fabsf(x)), r = rcp(1.0f + e);
+    const float e = __expf(-fabsf(x)), r = rcp1(1.0f + e);
     return e * r * r;
-}
-// tanh x and its derivative 4 e / (1 + e)^2, with e = e^-2|x|
-__device__ inline void tanh_grad(float x, float &th, float &dth) {
-    const float e = __expf(-2.0f * fabsf(x)), r = rcp(1.0f + e);
-    th = copysignf((1.0f - e) * r, x);
-    dth = 4.0f * e * r * r;
 }
 
 constexpr int kTapOob = (int)0x80000000; // past any map under 2 GiB
@@ -233,7 +242,7 @@ __device__ __forceinline__ void project(const double *A, int fw, int fh, double 
     const double pz = fma(A[6], uc, fma(A[7], vc, fma(A[11], invd, A[8])));
     const double qx = fma(A[0], uc, fma(A[1], vc, fma(A[9], invd, A[2])));
     const double qy = fma(A[3], uc, fma(A[4], vc, fma(A[10], invd, A[5])));
-    const double rz = recip_d(pz);
+    const double rz = recip2_d(pz);
     const double X = qx * rz - 0.5, Y = qy * rz - 0.5;
     const bool ok = live && (pz > 1e-6) && (fabs(X) < 1e7) && (fabs(Y) < 1e7);
     // d p / d d = -b / d^2;  d(q / pz) / d d = (dq pz - q dpz) / pz^2
@@ -479,7 +488,7 @@ k_uf_backward(const BwdParams p) {
         const uint32_t ec_ld = (uint32_t)(live_ld ? e_ld : N - 1);
         const uint32_t rem = ec_ld - (uint32_t)(li * npix), yy = fast_div(rem, p.div_w);
         const double uc = (double)(rem - yy * p.div_w.d) + 0.5, vc = (double)yy + 0.5;
-        const double invd = recip_d((double)depth_ld);
+        const double invd = recip2_d((double)depth_ld);
         ViewProj mine;
         auto proj = [&](int m0) {
             const int m = min(m0 + chunk, p.V - 1);
@@ -538,7 +547,7 @@ k_uf_backward(const BwdParams p) {
         for (int t = 0; t < MT; ++t) {
             const float ss = row_sum(fmaf(f[t][0], f[t][0], fmaf(f[t][1], f[t][1],
                                      fmaf(f[t][2], f[t][2], f[t][3] * f[t][3]))));
-            ir[t] = __builtin_amdgcn_rsqf(ss * (1.0f / (float)C) + 1e-6f);
+            ir[t] = rsq1(ss * (1.0f / (float)C) + 1e-6f);
         }
         auto normalised = [&](f32x4 (&x)[MT]) {
 #pragma unroll
@@ -592,7 +601,7 @@ k_uf_backward(const BwdParams p) {
                 ob.z = fmaf(pw, s.z, ob.z);
                 ob.w = fmaf(pw, s.w, ob.w);
             });
-            iz = rcp(z);
+            iz = rcp1(z);
             *reinterpret_cast<float4 *>(row_ld + 4 * chunk) = make_float4(ob.x * iz, ob.y * iz, ob.z * iz, ob.w * iz);
             wave_order();
         }
@@ -605,9 +614,10 @@ k_uf_backward(const BwdParams p) {
             rows_load<C>(A, n, g, ob);
             zero4(o);
             product<false>(s_w[kMatV], n, g, ob, o);
-#pragma unroll
-            for (int t = 0; t < MT; ++t) fp[t] = f[t];
+            zero4(fp);                            // summed before f joins: fewer roundings at its size
             product<false>(s_w[kMatO], n, g, o, fp);
+#pragma unroll
+            for (int t = 0; t < MT; ++t) fp[t] += f[t];
             zero4(x);
             product<false>(s_w[kMatH], n, g, fp, x);
             wave_order();
@@ -624,24 +634,23 @@ k_uf_backward(const BwdParams p) {
                 float h[5];                       // d x_sigma, d x_depth, d x_color
 #pragma unroll
                 for (int j = 0; j < 3; ++j) h[2 + j] = dco[j] * dsigm(xc[j]);
-                float th, dth;
-                tanh_grad(xd, th, dth);
+                const float th = tanhf(xd), dth = fmaf(-th, th, 1.0f);
                 if (p.mode == 0) {
                     const float a_in = a_px, ac = fminf(fmaxf(a_in, 1e-6f), 1.0f - 1e-6f);
-                    h[0] = dal * dsigm(logf(ac * rcp(1.0f - ac)) + xs);
-                    if (a_in > 1e-6f && a_in < 1.0f - 1e-6f) da_in = h[0] * rcp(a_in * (1.0f - a_in));
-                    const float invd = rcp(d_px), disp = fmaf(kap, th, invd);
+                    h[0] = dal * dsigm(logf(ac / (1.0f - ac)) + xs);
+                    if (a_in > 1e-6f && a_in < 1.0f - 1e-6f) da_in = h[0] / (a_in * (1.0f - a_in));
+                    const float disp = fmaf(kap, th, 1.0f / d_px);
                     h[1] = 0.f;
                     if (disp > p.inv_far && disp < p.inv_near) {
-                        const float dn = rcp(disp);
+                        const float dn = rcp1(disp);
                         const float ddisp = -ddn * dn * dn;
-                        dd_in = -ddisp * invd * invd;
+                        dd_in = -ddisp / (d_px * d_px);
                         h[1] = ddisp * kap * dth;
                     }
                 } else {
                     h[0] = dal * dsigm(xs);
-                    const float delta = ((float)(p.L - li) - 0.5f) * rcp((float)p.L);
-                    const float dn = rcp(fmaf(delta + half_l * th, band, p.inv_far));
+                    const float delta = ((float)(p.L - li) - 0.5f) / (float)p.L;
+                    const float dn = rcp1(fmaf(delta + half_l * th, band, p.inv_far));
                     h[1] = -ddn * dn * dn * kap * dth;
                 }
                 if (live) p.d_alpha[e_px] = da_in;
@@ -656,9 +665,13 @@ k_uf_backward(const BwdParams p) {
             wave_order();
             outer_rows<C>(B, A, n, g, gH);
             rows_load<C>(A, n, g, x);             // h
-            if (p.dF_out) load_vec(p.dF_out, dfp);
-            else zero4(dfp);
+            zero4(dfp);
             product<true>(s_w[kMatH], n, g, x, dfp);
+            if (p.dF_out) {
+                load_vec(p.dF_out, x);
+#pragma unroll
+                for (int t = 0; t < MT; ++t) dfp[t] += x[t];
+            }
             f32x4 dov[MT], dob[MT];
             zero4(dov);
             product<true>(s_w[kMatO], n, g, dfp, dov);

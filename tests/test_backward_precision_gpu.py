@@ -1,0 +1,41 @@
+"""The backward in full float32: divisions and square roots as exact as IEEE ones,
+sums rounded at their own size before a larger term joins.
+
+Relative error of dLoss/dF (the norm's, against the FP64 oracle).  Its main part
+is dLoss/dF' plus the decode heads' five products with sigma'(x) and tanh'(x) of
+the updated feature's two 16-term products: some 40 roundings at the size of what
+they are added to, each 2.4e-8 of it in the root mean square (a rounding of up to
+2^-24, over mantissas spread evenly): 1.5e-7.  Estimates of a unit in the last
+place in the place of divisions, and products accumulated onto the feature and
+onto dLoss/dF' themselves, gave 1.6e-7 to 2.0e-7."""
+
+import numpy as np
+import pytest
+
+import test_backward_gpu as tb
+from paper_2411_16680_amd import lib, synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return lib.Context(0)
+
+
+@pytest.mark.parametrize("V", [1, 2, 4])
+@pytest.mark.parametrize("C", [8, 16])
+def test_feature_gradient(ctx, C, V):
+    err = []
+    for seed in range(4):
+        sc = synth.make_custom(V=V, H=48, W=72, C=C, L=4, seed=200 + seed, arc=0.3, radius=2.0)
+        lvl = sc.levels[0]
+        ups = tb._upstream(lvl, seed)
+        gpu = tb._run_backward(ctx, sc, lvl, mode="paper", **ups)
+        ref = tb._oracle(sc, lvl, ups, lib.MODE["paper"])
+        err.append(np.linalg.norm(gpu["F"] - ref["F"]) / np.linalg.norm(ref["F"]))
+    tb._say("precision", C, V, f"{np.median(err):.2e}")
+    assert np.median(err) <= 1.5e-7
