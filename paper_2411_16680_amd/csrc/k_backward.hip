@@ -919,6 +919,10 @@ static void scatter_params(const BwdParams &p, ViewsParams &v, ScatterParams &sp
     v.div_hw = make_fast_div((uint32_t)(p.H * p.W));
     v.div_w = make_fast_div((uint32_t)p.W);
     sp.ds = p.ds;
+    const int64_t records = p.V * p.N;
+    sp.listed = v.total + 1;
+    sp.list = reinterpret_cast<uint2 *>(p.bins + scatter_list_at(tiles, records));
+    sp.list_cap = (uint32_t)scatter_list_cap(records);
 }
 
 hipError_t launch_update_fuse_backward(const BwdParams &p, hipStream_t s) {

@@ -4,10 +4,15 @@
 // map their bilinear footprint falls in (k_views.hip's passes), and one
 // workgroup per tile writes each of its pixels once,
 //   dI(x, y) = sum over the records of the four cells around it of w_tap ds.
-// No atomics on the maps, and nothing is cleared first.
+// No atomics on the maps, and nothing is cleared first.  A tile's workgroup takes
+// its first kScatterOwn records; where more crowd there (a map much smaller than
+// the level, a view that sees it from afar) it lists the rest in pieces as large,
+// which a second launch spreads over the chip and adds.
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
+
+#include <algorithm>
 
 #include "uf_params.h"
 #include "vbin.h"
@@ -20,31 +25,50 @@ constexpr int kCw = kTw + 1, kCh = kTh + 1, kCells = kCw * kCh;   // cells whose
 constexpr int kThreads = 256;
 constexpr int kBatch = 1280, kPer = kBatch / kThreads;            // records sorted at a time
 
-// A workgroup sorts its tile's records by cell (top left tap) in LDS, a batch
-// at a time; then C lanes, one per channel, own two pixel columns and walk
-// down the rows of the three columns of cells that reach them, summing in
-// registers.  A record's row of ds is read one and a half times on average.
+struct ScatterLds {
+    int cnt[kCells + 1];                 // counts, then a cell's first record
+    int sum[kThreads / 64];
+    float4 w[kBatch];                    // tap weights 00, 10, 01, 11
+    uint32_t q[kBatch];                  // byte offset of the row of ds
+};
+
+// A tile of a view's map, its place and records.
+struct Tile {
+    int m, x0, y0;
+    VbinRanges ranges;
+    __device__ Tile(const ViewsParams &p, int t) {
+        m = 0;
+        for (int i = 1; i < p.V; ++i) m = (t >= p.tbase[i]) ? i : m;
+        const int ntx = p.ntx[m], lt = t - p.tbase[m];
+        const int ty = lt / ntx, tx = lt - ty * ntx;
+        x0 = tx * kTw;
+        y0 = ty * kTh;
+        ranges = vbin_ranges(p, t, tx, ty, ntx, p.nty[m]);
+    }
+};
+
+// A workgroup sorts records first .. last - 1 of a tile by cell (top left tap) in
+// LDS, a batch at a time; then C lanes, one per channel, own two pixel columns and
+// walk down the rows of the three columns of cells that reach them, summing in
+// registers.  A record's row of ds is read one and a half times on average.  The
+// first batch of a tile writes its pixels and later ones add to them; ADD: other
+// workgroups add to the same pixels.
 // 16.6 M records of 64 bytes (960x540, L = 8, C = 16, V = 4): 0.48 ms, 2.2 TB/s
 // of rows, bound by the latency of the short lists (8 records a cell there).
 // Tiles are 4 rows high so that such a tile is one batch at six workgroups per
 // CU: 8 rows in two batches took 0.55 ms, in one batch of 2560 0.68 ms; with a
 // pixel's own four lists per C lanes, every row read four times, 1.07 ms.
-template <int C>
-__global__ void __launch_bounds__(kThreads) k_scatter_tiles(const ViewsParams p, const ScatterParams sp) {
+template <int C, bool ADD>
+__device__ __forceinline__ void scatter_records(const ViewsParams &p, const ScatterParams &sp, const Tile &tile,
+                                                uint32_t first, uint32_t last, ScatterLds &lds) {
     constexpr int RG = kThreads / C / (kTw / 2); // groups of rows
     constexpr int RH = kTh / RG;                 // pixel rows of a group
-    __shared__ int s_cnt[kCells + 1];            // counts, then a cell's first record
-    __shared__ int s_sum[kThreads / 64];
-    __shared__ float4 s_w[kBatch];               // tap weights 00, 10, 01, 11
-    __shared__ uint32_t s_q[kBatch];             // byte offset of the row of ds
-    const int t = xcd_order(blockIdx.x, gridDim.x);
-    int m = 0;
-    for (int i = 1; i < p.V; ++i) m = (t >= p.tbase[i]) ? i : m;
-    const int ntx = p.ntx[m], nty = p.nty[m], lt = t - p.tbase[m];
-    const int ty = lt / ntx, tx = lt - ty * ntx;
-    const int x0 = tx * kTw, y0 = ty * kTh;
-    const VbinRanges ranges = vbin_ranges(p, t, tx, ty, ntx, nty);
-    const uint32_t total = ranges.cum[5];
+    auto &s_cnt = lds.cnt;
+    auto &s_sum = lds.sum;
+    auto &s_w = lds.w;
+    auto &s_q = lds.q;
+    const int m = tile.m, x0 = tile.x0, y0 = tile.y0;
+    const VbinRanges &ranges = tile.ranges;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int ch = tid % C, col = tid / C % (kTw / 2), row0 = tid / C / (kTw / 2) * RH;
     const __amdgpu_buffer_rsrc_t ds = __builtin_amdgcn_make_buffer_rsrc(
@@ -53,7 +77,7 @@ __global__ void __launch_bounds__(kThreads) k_scatter_tiles(const ViewsParams p,
     float *out = sp.dfeat[m];
 
     // (a tile without records is one empty batch: its pixels are zero)
-    for (uint32_t b0 = 0; b0 == 0 || b0 < total; b0 += kBatch) {
+    for (uint32_t b0 = first; b0 == 0 || b0 < last; b0 += kBatch) {
         for (int i = tid; i <= kCells; i += kThreads) s_cnt[i] = 0;
         __syncthreads();
         int cell[kPer], rank[kPer], q[kPer];
@@ -62,7 +86,7 @@ __global__ void __launch_bounds__(kThreads) k_scatter_tiles(const ViewsParams p,
         for (int k = 0; k < kPer; ++k) {
             const uint32_t i = b0 + k * kThreads + tid;
             cell[k] = -1;
-            q[k] = i < total ? p.rec[ranges.at(i)] : -1;
+            q[k] = i < last ? p.rec[ranges.at(i)] : -1;
         }
 #pragma unroll
         for (int k = 0; k < kPer; ++k) {
@@ -143,8 +167,13 @@ __global__ void __launch_bounds__(kThreads) k_scatter_tiles(const ViewsParams p,
             const int x = x0 + 2 * col, y = y0 + r - 1;
             if (r > row0 && y < vh) {            // row r - 1 is complete for this batch
                 float *dst = out + ((int64_t)y * vw + x) * C + ch;
-                if (x < vw) dst[0] = b0 == 0 ? a0 : dst[0] + a0;
-                if (x + 1 < vw) dst[C] = b0 == 0 ? b0v : dst[C] + b0v;
+                if constexpr (ADD) {
+                    if (x < vw && a0 != 0.0f) unsafeAtomicAdd(dst, a0);
+                    if (x + 1 < vw && b0v != 0.0f) unsafeAtomicAdd(dst + C, b0v);
+                } else {
+                    if (x < vw) dst[0] = b0 == 0 ? a0 : dst[0] + a0;
+                    if (x + 1 < vw) dst[C] = b0 == 0 ? b0v : dst[C] + b0v;
+                }
             }
             a0 = a1;
             b0v = b1;
@@ -154,12 +183,49 @@ __global__ void __launch_bounds__(kThreads) k_scatter_tiles(const ViewsParams p,
     }
 }
 
+template <int C>
+__global__ void __launch_bounds__(kThreads) k_scatter_tiles(const ViewsParams p, const ScatterParams sp) {
+    __shared__ ScatterLds lds;
+    __shared__ uint32_t s_at;
+    const int t = xcd_order(blockIdx.x, gridDim.x);
+    const Tile tile(p, t);
+    const uint32_t total = tile.ranges.cum[5];
+    if (total > kScatterOwn) {                   // list what is left
+        const uint32_t n = (total - 1) / kScatterOwn;
+        if (threadIdx.x == 0) s_at = atomicAdd(sp.listed, n);
+        __syncthreads();
+        const uint32_t at = s_at;
+        for (uint32_t i = threadIdx.x; i < n; i += kThreads)
+            if (at + i < sp.list_cap) sp.list[at + i] = make_uint2((uint32_t)t, (i + 1) * kScatterOwn);
+    }
+    scatter_records<C, false>(p, sp, tile, 0, min(total, (uint32_t)kScatterOwn), lds);
+}
+
+// The pieces that k_scatter_tiles listed.  4 views of 131x251, 8 layers, C = 16 (the
+// whole adjoint): maps of 4 x 32 5.91 -> 0.57 ms (float atomics 0.69), focal lengths
+// a hundredth 31 -> 0.79 (9 to 12); the launch takes 3 us where no tile is crowded.
+// Pieces of 5120 records: 0.77 and 1.35 ms.
+template <int C>
+__global__ void __launch_bounds__(kThreads) k_scatter_rest(const ViewsParams p, const ScatterParams sp) {
+    __shared__ ScatterLds lds;
+    const uint32_t n = min(*sp.listed, sp.list_cap);
+    for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) {
+        const uint2 piece = sp.list[i];
+        const Tile tile(p, (int)piece.x);
+        scatter_records<C, true>(p, sp, tile, piece.y, min(tile.ranges.cum[5], piece.y + kScatterOwn), lds);
+    }
+}
+
 }  // namespace
 
 hipError_t launch_scatter(const ViewsParams &p, const ScatterParams &sp, int C, hipStream_t s) {
-    const dim3 g((unsigned)p.tbase[p.V]), b(kThreads);
+    const dim3 g((unsigned)p.tbase[p.V]), r(std::min<uint32_t>(sp.list_cap, 6 * 256)), b(kThreads);
     if (C == 8) hipLaunchKernelGGL(k_scatter_tiles<8>, g, b, 0, s, p, sp);
     else hipLaunchKernelGGL(k_scatter_tiles<16>, g, b, 0, s, p, sp);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if (C == 8) hipLaunchKernelGGL(k_scatter_rest<8>, r, b, 0, s, p, sp);
+    else hipLaunchKernelGGL(k_scatter_rest<16>, r, b, 0, s, p, sp);
     return hipGetLastError();
 }
 

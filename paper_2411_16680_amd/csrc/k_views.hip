@@ -212,7 +212,9 @@ __device__ inline void vbin_chunk(const ViewsParams &p, int &m, int64_t &q0) {
 
 __global__ void __launch_bounds__(256) k_vbin_zero(const ViewsParams p) {
     const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i <= p.nbins) p.cursor[i] = 0u;          // cursor[nbins] is the records' total
+    // cursor[nbins] is the records' total, then the scatter's count of listed pieces
+    // (nbins is a multiple of 4, so the last block reaches both)
+    if (i < p.nbins + 4) p.cursor[i] = 0u;
 }
 
 // KPT layer-pixels per thread.  What bounds both passes is the rate of global

@@ -230,18 +230,27 @@ struct ViewsParams {
 namespace qk {
 
 // Sorted scatter of the feature-map gradients: tiles of 32 x kScatterTh map
-// pixels, binned like the render to the views (words of its workspace: bin
-// cursors, total, tile starts, records).
+// pixels, binned like the render to the views.  Its workspace, in words: bin
+// cursors, four for the total and the pieces listed, tile starts, records, and the
+// list of the pieces of kScatterOwn records that are more than a tile's own.
 constexpr int kScatterTh = 4;
+constexpr uint32_t kScatterOwn = 2560;
 struct ScatterParams {
     const float *ds;                // [V][N][C]
     float *dfeat[kMaxViews];        // [fH][fW][C], written
+    uint32_t *listed;               // pieces listed
+    uint2 *list;                    // [list_cap] a piece's tile and first record
+    uint32_t list_cap;              // the tiles read a record at most four times in all
 };
 inline int64_t scatter_tiles(int32_t fH, int32_t fW) {
     return (int64_t)((fW + 31) / 32) * ((fH + kScatterTh - 1) / kScatterTh);
 }
+inline int64_t scatter_list_cap(int64_t records) { return 4 * records / kScatterOwn + 1; }
+inline int64_t scatter_list_at(int64_t tiles, int64_t records) {
+    return 4 * tiles + 4 + ((tiles + 3) & ~(int64_t)3) + ((records + 3) & ~(int64_t)3);
+}
 inline int64_t scatter_bin_words(int64_t tiles, int64_t records) {
-    return 4 * tiles + 4 + ((tiles + 3) & ~(int64_t)3) + records;
+    return scatter_list_at(tiles, records) + 2 * scatter_list_cap(records);
 }
 
 }  // namespace qk
