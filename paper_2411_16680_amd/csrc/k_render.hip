@@ -68,8 +68,8 @@ struct RenderArgs {
 };
 static_assert(sizeof(RenderArgs) < 4096, "kernel arguments");
 
-__device__ inline __amdgpu_buffer_rsrc_t layer_rsrc(const float *p, int bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p), 0, bytes, 0x00020000);
+__device__ inline __amdgpu_buffer_rsrc_t layer_rsrc(const float *p, int64_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p), 0, (int)min(bytes, (int64_t)0x7fffffff), 0x00020000);
 }
 
 __device__ inline unsigned load_texel(__amdgpu_buffer_rsrc_t r, int byte_off) {
@@ -186,12 +186,19 @@ __global__ void __launch_bounds__(256) k_render_ibr(const RenderArgs p) {
     const double lxd = sx - x0, lyd = sy - y0;
     const float lx = (float)lxd, ly = (float)lyd;
     const int64_t hw = (int64_t)p.h * p.w;
-    // (NV > 0 is taken where a layer's logits stay under 2 GiB)
+    // Offsets count from the tile's first row of logits, in 32 bits where NV > 0 (the
+    // launcher sees to it that a tile's rows are that close; a layer's need not be)
+    int first_row = 0;
+    if constexpr (NV > 0) {
+        const double s0 = ((double)(tile / tiles_x * p.rows) + 0.5) * p.ry - 0.5;
+        first_row = __builtin_amdgcn_readfirstlane(min(max((int)s0, 0), p.h - 1));
+    }
+    const int64_t row_at = (int64_t)first_row * p.w, left = hw - row_at;
     using idx = std::conditional_t<(NV > 0), int, int64_t>;
-    const idx t00 = (idx)y0 * p.w + x0, t10 = (idx)y0 * p.w + x1;
-    const idx t01 = (idx)y1 * p.w + x0, t11 = (idx)y1 * p.w + x1;
+    const idx t00 = (idx)(y0 - first_row) * p.w + x0, t10 = (idx)(y0 - first_row) * p.w + x1;
+    const idx t01 = (idx)(y1 - first_row) * p.w + x0, t11 = (idx)(y1 - first_row) * p.w + x1;
     auto at = [&](const float *q, idx i) {
-        if constexpr (NV > 0) return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(layer_rsrc(q, (int)(4 * hw)), 4 * i, 0, 0));
+        if constexpr (NV > 0) return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(layer_rsrc(q, 4 * left), 4 * i, 0, 0));
         else return q[i];
     };
     auto lerp_f = [&](float a00, float a10, float a01, float a11) {
@@ -212,7 +219,7 @@ __global__ void __launch_bounds__(256) k_render_ibr(const RenderArgs p) {
     float Tr = 1.0f, out0 = 0.0f, out1 = 0.0f, out2 = 0.0f, dmap = 0.0f;
 
     for (int li = 0; li < L; ++li) {
-        const float *D = p.depth_logit + li * hw, *S = p.sigma_logit + li * hw;
+        const float *D = p.depth_logit + li * hw + row_at, *S = p.sigma_logit + li * hw + row_at;
         const float alpha = sigmoid_(lerp_f(at(S, t00), at(S, t10), at(S, t01), at(S, t11)));
         // depth: the logit is interpolated in double, since an error in it is
         // magnified by the parallax (up to ~1e3 px per unit of disparity)
@@ -259,14 +266,14 @@ __global__ void __launch_bounds__(256) k_render_ibr(const RenderArgs p) {
             return r;
         };
         // blend: softmax over the views of the upsampled logits
-        const float *B = p.blend_logit + li * hw * V;
+        const float *B = p.blend_logit + (li * hw + row_at) * V;
         float z = 0.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f;
         if constexpr (NV > 0) {
             // all views' logits first (in the widest loads that V floats per
             // tap stay aligned to), then their maximum, then the views
             constexpr int VW = NV % 4 == 0 ? 4 : NV % 2 == 0 ? 2 : 1;
             typedef float vec __attribute__((ext_vector_type(VW)));
-            const __amdgpu_buffer_rsrc_t brs = layer_rsrc(B, (int)(4 * hw) * NV);
+            const __amdgpu_buffer_rsrc_t brs = layer_rsrc(B, 4 * left * NV);
             auto tap = [&](int i, int c) {
                 const int o = i * (4 * NV), k = c * (int)sizeof(vec);
                 if constexpr (VW == 4) return __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b128(brs, o, k, 0));
@@ -377,12 +384,7 @@ hipError_t launch_render_ibr(const RenderParams &p, hipStream_t s) {
     a.depth = p.depth;
     a.V = p.V; a.L = p.L; a.h = p.h; a.w = p.w; a.H = p.H; a.W = p.W;
     a.rx = p.rx; a.ry = p.ry; a.band = p.band; a.inv_far = p.inv_far;
-    // view counts known at compile time read their logits in vectors, which the
-    // logits' address has to allow (the C-ABI asks only for 4 bytes), at 32-bit
-    // offsets
-    const uintptr_t at = reinterpret_cast<uintptr_t>(p.blend_logit);
-    const bool vec = (at & (p.V % 4 == 0 ? 15 : p.V % 2 == 0 ? 7 : 3)) == 0 &&
-                     (int64_t)p.h * p.w * p.V < ((int64_t)1 << 29);
+    const bool vec = render_vectors(p.V, p.h, p.w, p.H, a.rows, reinterpret_cast<uintptr_t>(p.blend_logit));
 #define QK_RENDER(NV) case NV: hipLaunchKernelGGL((k_render_ibr<NV>), g, b, 0, s, a); break
     switch (vec ? p.V : 0) {
     QK_RENDER(1); QK_RENDER(2); QK_RENDER(3); QK_RENDER(4); QK_RENDER(5); QK_RENDER(6); QK_RENDER(7); QK_RENDER(8);

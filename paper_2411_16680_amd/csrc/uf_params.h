@@ -191,6 +191,15 @@ struct RenderParams {
     double band, inv_far;           // 1/near - 1/far, 1/far
 };
 
+// Whether a view count with a kernel of its own can read the blend logits in
+// vectors: their address has to allow it (the C-ABI asks only for 4 bytes), and the
+// logits that a tile of `rows` output rows reads, counted from its first one,
+// have to lie within 2 GiB of each other (32-bit offsets).
+inline bool render_vectors(int32_t V, int32_t h, int32_t w, int32_t H, int32_t rows, uintptr_t logits) {
+    const int64_t most = (int64_t)rows * h / H + 3, span = most < h ? most : h;
+    return (logits & (V % 4 == 0 ? 15 : V % 2 == 0 ? 7 : 3)) == 0 && span * w < ((int64_t)1 << 29) / V;
+}
+
 }  // namespace qk
 
 namespace qk {
