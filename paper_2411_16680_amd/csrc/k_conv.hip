@@ -42,7 +42,7 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kC = 32, TX = 30, MX = TX + 2, IX = TX + 4;
+constexpr int kC = 32, TX = kConvTileCols, MX = TX + 2, IX = TX + 4;
 constexpr int NFRAG = 2 * 9 * 2 * 64;            // [conv][tap][half of C_out][lane]
 
 // Place of 16-byte chunk q of column c in an LDS row (64 bytes a pixel): the
@@ -273,21 +273,7 @@ hipError_t launch_residual_conv(const ConvParams &pin, int num_cu, bool frag_rea
     ConvParams p = pin;
     p.tiles_x = (p.W + TX - 1) / TX;
     const int64_t slots = 2 * (int64_t)(num_cu > 0 ? num_cu : 256);
-    // The tile's height: a compute unit's time is about 4 us and 1/3 us per tile
-    // and row that the tile stages (TY + 4), so the height with the fewest such
-    // rows per compute unit, the taller of equals.  Measured, us at 2 / 4 / 8 / 16
-    // rows: 2 x 40x64: 5.5 / 6.4 / 7.9 / 11.4; 8 x 64x100: 11.5 / 8.5 / 8.8 / 11.8;
-    // 1 x 288x512: 25 / 21 / 16 / 17; 16 x 135x240: 77 / 52 / 41 / 37.  10 and 12 rows
-    // for where 8 make just more than a tile per unit: 5 x 72x154: 9.3 at 10, 10.4 at
-    // 12, 11.0 at 8; 1 x 288x512: 14.1 at 12.
-    const int64_t cus = num_cu > 0 ? num_cu : 256;
-    int ty = 16;
-    int64_t best = INT64_MAX;
-    for (int h : {16, 12, 10, 8, 4, 2}) {
-        const int64_t n = (int64_t)p.L * p.tiles_x * ((p.H + h - 1) / h);
-        const int64_t cost = (n + cus - 1) / cus * (h + 4);
-        if (cost < best) best = cost, ty = h;
-    }
+    const int ty = conv_tile_rows(p.L, p.H, p.W, num_cu > 0 ? num_cu : 256);
     p.tiles_y = (p.H + ty - 1) / ty;
     p.n_tiles = (int64_t)p.L * p.tiles_x * p.tiles_y;
     hipError_t e;
@@ -301,6 +287,7 @@ hipError_t launch_residual_conv(const ConvParams &pin, int num_cu, bool frag_rea
     switch (ty) {
     case 2: hipLaunchKernelGGL(k_residual_conv<2>, gr, bl, 0, s, p); break;
     case 4: hipLaunchKernelGGL(k_residual_conv<4>, gr, bl, 0, s, p); break;
+    case 6: hipLaunchKernelGGL(k_residual_conv<6>, gr, bl, 0, s, p); break;
     case 8: hipLaunchKernelGGL(k_residual_conv<8>, gr, bl, 0, s, p); break;
     case 10: hipLaunchKernelGGL(k_residual_conv<10>, gr, bl, 0, s, p); break;
     case 12: hipLaunchKernelGGL(k_residual_conv<12>, gr, bl, 0, s, p); break;

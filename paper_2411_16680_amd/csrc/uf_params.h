@@ -278,6 +278,28 @@ struct ConvParams {
     int64_t n_tiles;
 };
 
+// The residual block's tiles: 30 columns, and the height by what a call has to do.  A
+// compute unit's time is about 4 us and 1/3 us per tile and row that the tile
+// stages (its rows + 4), so the height with the fewest such rows per compute unit,
+// the taller of equals.  A unit's first two tiles are resident together and
+// overlap by 1.3 to 1.7 us: 4 or 5 rows less.  Measured, us at 2 / 4 / 6 / 8 / 10 / 12 /
+// 16 rows: 4 x 45x80: 6.2 / 6.3 / 7.0 / 7.9 / 8.7 / 9.6 / 11.4; 12 x 36x64: 9.2 / 7.6 / 7.2
+// / 8.2 / 8.9 / 9.8 / 11.6; 24 x 36x64: 14.8 / 11.3 / 9.2 / 10.5 / 11.8 / 10.3 / 12.2; 5 x
+// 72x154: 13.0 / 11.3 / 9.2 / 10.6 / 9.5 / 10.2 / 11.9; 24 x 45x80: 17.3 / 14.3 / 13.4 /
+// 11.0 / 12.2 / 13.4 / 12.4; 1 x 288x512: 26.3 / 20.3 / 17.5 / 16.6 / 18.3 / 14.5 / 17.2.
+constexpr int kConvTileCols = 30;
+inline int conv_tile_rows(int32_t L, int32_t H, int32_t W, int64_t cus) {
+    const int64_t tiles_x = (W + kConvTileCols - 1) / kConvTileCols;
+    int rows = 16;
+    int64_t best = INT64_MAX;
+    for (int h : {16, 12, 10, 8, 6, 4, 2}) {
+        const int64_t n = L * tiles_x * ((H + h - 1) / h), per = (n + cus - 1) / cus;
+        const int64_t cost = per * (h + 4) - (per != 2 ? 0 : h > 2 ? 5 : 4);
+        if (cost < best) best = cost, rows = h;
+    }
+    return rows;
+}
+
 }  // namespace qk
 
 namespace qk {
