@@ -119,28 +119,57 @@ __device__ inline float bf2f(uint16_t h) { return __uint_as_float((unsigned)h <<
 
 __device__ inline uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 
-// 16 of the 32 sinusoids of pixel (x, y) of view m's grid (the grid the composed
-// D[m] was made for): sine and cosine of one angle (x's, or y's) in 8 octaves.
-__device__ __forceinline__ void ray_sinusoids(const RayParams &p, int m, int x, int y, bool second, float fs[8],
-                                              float fc[8]) {
+// The two angles' arguments (before tanh) of pixel (x, y) of view m's grid (the grid
+// the composed D[m] was made for).
+__device__ __forceinline__ void ray_difference(const RayParams &p, int m, int x, int y, double &ax, double &ay) {
     const double u = (double)x + 0.5, v = (double)y + 0.5;
     const double *D = p.D[m], *o = p.o[m];
     const double dx = fma(D[0], u, fma(D[1], v, D[2]));
     const double dy = fma(D[3], u, fma(D[4], v, D[5]));
     const double dz = fma(D[6], u, fma(D[7], v, D[8]));
     const double rz = o[2] / dz;
-    const double ax = p.inv_band * fma(-rz, dx, o[0]);
-    const double ay = p.inv_band * fma(-rz, dy, o[1]);
-    const double t = tanh_abs(second ? fma(p.ky0, ax, p.ky1 * ay) : fma(p.kx0, ax, p.kx1 * ay));
-    double s, c;
-    sincospi_unit(t, s, c);
+    ax = p.inv_band * fma(-rz, dx, o[0]);
+    ay = p.inv_band * fma(-rz, dy, o[1]);
+}
+
+// the next octave: sin 2a, cos 2a
+__device__ __forceinline__ void next_octave(double &s, double &c) {
+    const double s2 = 2.0 * s * c, c2 = (c - s) * (c + s);
+    s = s2;
+    c = c2;
+}
+
+// 16 of the 32 sinusoids of a pixel: sine and cosine of one angle (x's, or y's) in 8
+// octaves.
+__device__ __forceinline__ void ray_sinusoids(const RayParams &p, int m, int x, int y, bool second, float fs[8],
+                                              float fc[8]) {
+    double ax, ay, s, c;
+    ray_difference(p, m, x, y, ax, ay);
+    sincospi_unit(tanh_abs(second ? fma(p.ky0, ax, p.ky1 * ay) : fma(p.kx0, ax, p.kx1 * ay)), s, c);
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
         fs[k] = (float)s;
         fc[k] = (float)c;
+        if (k < 7) next_octave(s, c);
+    }
+}
+
+// All 32, the two angles' chains side by side.
+__device__ __forceinline__ void ray_sinusoids(const RayParams &p, int m, int x, int y, float e[32]) {
+    double ax, ay, sx, cx, sy, cy;
+    ray_difference(p, m, x, y, ax, ay);
+    const double tx = tanh_abs(fma(p.kx0, ax, p.kx1 * ay)), ty = tanh_abs(fma(p.ky0, ax, p.ky1 * ay));
+    sincospi_unit(tx, sx, cx);
+    sincospi_unit(ty, sy, cy);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        e[4 * k] = (float)sx;
+        e[4 * k + 1] = (float)cx;
+        e[4 * k + 2] = (float)sy;
+        e[4 * k + 3] = (float)cy;
         if (k < 7) {
-            const double s2 = 2.0 * s * c, c2 = (c - s) * (c + s);
-            s = s2; c = c2;
+            next_octave(sx, cx);
+            next_octave(sy, cy);
         }
     }
 }
@@ -319,6 +348,36 @@ __global__ void __launch_bounds__(256) k_ray_encoding(const RayParams p) {
     }
 }
 
+// The same with a pixel per thread and the weights as scalars, for few channels: a
+// pixel's ray and its division are worked out once for both angles, and 8 channels
+// leave half of the matrix cores' rows empty.  The products' order differs, so the
+// last bits may.
+template <int C, bool LOW, bool BF16>
+__global__ void __launch_bounds__(256) k_ray_pixels(const RayParams p) {
+    const int m = blockIdx.y;
+    const int fw = LOW ? p.lW : p.fW[m];
+    const int64_t np = (int64_t)(LOW ? p.lH : p.fH[m]) * fw;
+    const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (q >= np) return;
+    const int y = (int)(q / fw), x = (int)(q - (int64_t)y * fw);
+    float e[32];
+    ray_sinusoids(p, m, x, y, e);
+    // all of the pixel's channels are read before any is written: the source may be
+    // the map itself
+    float a[C];
+#pragma unroll
+    for (int j = 0; j < C; ++j) a[j] = 0.0f;
+    if constexpr (!LOW) load_n<C, BF16>(p.src[m], q * C, a);
+    typedef const __attribute__((address_space(4))) float *scalars;   // uniform reads: scalar loads
+    const scalars w = (scalars)p.Wr;
+#pragma unroll
+    for (int i = 0; i < 32; ++i)
+#pragma unroll
+        for (int j = 0; j < C; ++j) a[j] = fmaf(e[i], w[i * C + j], a[j]);
+    if constexpr (LOW) store_n<C, false>(p.P, ((int64_t)m * np + q) * C, a);
+    else store_n<C, BF16>(p.feat[m], q * C, a);
+}
+
 // Low-resolution form, second pass, for a low-resolution grid no finer than
 // the map (lH <= fH, lW <= fW): a workgroup takes a segment of 256 / (C/8)
 // pixels of one map row, one thread per (pixel, 8 channels).  Bilinear
@@ -410,14 +469,31 @@ inline unsigned encoding_blocks(int64_t pixels, unsigned V) {
     return (unsigned)(all < most ? all : most);
 }
 
+// The encoding of a grid of `pixels` in each view.  8 channels, and 16 of a bfloat16
+// map, take a pixel per thread from where that is the faster, us against the matrix
+// cores: 8 views of 90x160, 135x240, 360x640 and 1080x1920, 8 channels: 4.8 / 5.9, 6.7
+// / 9.8, 31 / 49, 228 / 400 (a low-resolution grid of 90x120 8.6 / 8.6, 135x240 16.3 /
+// 18.3); 16 in bfloat16: 6.3 / 6.1, 9.3 / 9.9, 41 / 49, 348 / 448.  2 views of 90x160: 4.4 /
+// 3.5 and 5.8 / 3.4.  16 in float32 never: 506 / 478 at the largest, 5.6 / 3.5 there.
+template <int C, bool LOW, bool BF16>
+void launch_encoding(const RayParams &p, int64_t pixels, unsigned V, hipStream_t s) {
+    if constexpr (C == 8 || (C == 16 && BF16)) {
+        constexpr int64_t kFrom = C == 16 ? 200000 : LOW ? 86000 : 75000;
+        if (pixels * V >= kFrom) {
+            hipLaunchKernelGGL((k_ray_pixels<C, LOW, BF16>), dim3((unsigned)((pixels + 255) / 256), V), dim3(256), 0, s, p);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((k_ray_encoding<C, LOW, BF16>), dim3(encoding_blocks(pixels, V), V), dim3(256), 0, s, p);
+}
+
 template <int C>
 hipError_t launch_c(const RayParams &p, hipStream_t s) {
     const unsigned V = (unsigned)p.V;
     bool same = p.lH > 0;                        // low grid == every map grid: nothing to upsample
     for (int m = 0; m < p.V; ++m) same = same && p.lH == p.fH[m] && p.lW == p.fW[m];
     if (p.lH > 0 && !same) {
-        hipLaunchKernelGGL((k_ray_encoding<C, true, false>), dim3(encoding_blocks((int64_t)p.lH * p.lW, V), V),
-                           dim3(256), 0, s, p);
+        launch_encoding<C, true, false>(p, (int64_t)p.lH * p.lW, V, s);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         bool coarse = true;                      // the grid is no finer than any map
@@ -443,11 +519,8 @@ hipError_t launch_c(const RayParams &p, hipStream_t s) {
         }
         return hipGetLastError();
     }
-    const dim3 g(encoding_blocks(p.max_pixels, V), V);
-    if (p.bf16)
-        hipLaunchKernelGGL((k_ray_encoding<C, false, true>), g, dim3(256), 0, s, p);
-    else
-        hipLaunchKernelGGL((k_ray_encoding<C, false, false>), g, dim3(256), 0, s, p);
+    if (p.bf16) launch_encoding<C, false, true>(p, p.max_pixels, V, s);
+    else launch_encoding<C, false, false>(p, p.max_pixels, V, s);
     return hipGetLastError();
 }
 
