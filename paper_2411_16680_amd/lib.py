@@ -275,7 +275,10 @@ def _stream_handle(stream) -> Optional[int]:
     if stream is None:
         import torch
         if torch.cuda.is_initialized():      # the current stream's handle, without the stream object
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+            raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+            device = getattr(torch._C, "_cuda_getDevice", None)
+            if raw is not None and device is not None:     # not part of torch's public interface
+                return raw(device())
         stream = torch.cuda.current_stream()
     return int(stream.cuda_stream)
 
