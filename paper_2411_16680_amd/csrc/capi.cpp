@@ -1299,7 +1299,11 @@ qk_status qk_update_fuse_backward(qk_context *ctx, void *hip_stream, int32_t V,
     const int64_t records = V * p.N;
     int64_t tiles_f = 0;
     bool sorted = !p.wide && records * in->C >= kScatterMin && records < ((int64_t)1 << 31);
-    for (int m = 0; m < V; ++m) tiles_f += qk::scatter_tiles(feats[m].H, feats[m].W);
+    for (int m = 0; m < V; ++m) {
+        tiles_f += qk::scatter_tiles(feats[m].H, feats[m].W);
+        // a sample farther out counts as outside the map: not so in the binning
+        sorted = sorted && std::max(feats[m].H, feats[m].W) <= 10000000;
+    }
     const size_t n_sort = (size_t)records * in->C + (size_t)qk::scatter_bin_words(tiles_f, records);
     sorted = sorted && tiles_f < ((int64_t)1 << 28) && n_sort <= ((size_t)1 << 30);
     const size_t n_comp = d_rgb ? 4 * (size_t)p.N : 0;

@@ -93,14 +93,14 @@ static qk_camera camera(double tx, int w, int h) {
 
 // One backward of V views, L layers of 128 x 256, 16 channels; calls made of the
 // allocator and waits are counted afresh.
-static qk_status backward(qk_context *ctx, int V, int L, int map_w = 256) {
+static qk_status backward(qk_context *ctx, int V, int L, int map_w = 256, int map_h = 128) {
     const int H = 128, W = 256, C = 16;
     qk_camera cams[16], nov = camera(0.05, W, H);
     qk_feature_map fm[16];
     float *df[16];
     for (int m = 0; m < V; ++m) {
         cams[m] = camera(0.1 * m, W, H);
-        fm[m] = {P(0x100000000 + 0x10000000 * (uintptr_t)m), QK_F32, H, map_w, C};
+        fm[m] = {P(0x100000000 + 0x10000000 * (uintptr_t)m), QK_F32, map_h, map_w, C};
         df[m] = P(0x200000000 + 0x10000000 * (uintptr_t)m);
     }
     qk_weights w = {P(0x1000), P(0x2000), P(0x3000), P(0x4000), P(0x5000), P(0x6000), P(0x7000), C, C, 1, C};
@@ -196,6 +196,15 @@ int main() {
     CHECK(backward(ctx, V, L) == QK_OK && g_allocs == 0 && g_frees == 0 && g_syncs == 0);
     CHECK(qk_context_destroy(ctx) == QK_OK);
     CHECK(g_live == 0);
+
+    // samples count up to 10^7 texels from a map's corner: the binning knows no such
+    // limit, so larger maps take the atomics
+    g_memory = (size_t)1 << 40;
+    CHECK(qk_context_create(0, 0, &ctx) == QK_OK);
+    CHECK(backward(ctx, V, L, 10000000, 1) == QK_OK && g_bwd.ds != nullptr && !g_bwd.wide);
+    CHECK(backward(ctx, V, L, 10000001, 1) == QK_OK && g_bwd.ds == nullptr && !g_bwd.wide);
+    CHECK(backward(ctx, V, L, 1, 10000001) == QK_OK && g_bwd.ds == nullptr && !g_bwd.wide);
+    CHECK(qk_context_destroy(ctx) == QK_OK);
 
     std::printf("%d failures\n", fails);
     return fails != 0;
