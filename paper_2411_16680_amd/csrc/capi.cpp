@@ -291,10 +291,14 @@ qk_status check_update_fuse(int32_t V, const qk_camera *in_cams, const qk_featur
 
 
 // Sample-gradient floats (C per layer-pixel and view) from which the sorted
-// scatter is used: below, its four extra launches cost more than the atomics
-// (C = 16, V = 4: 0.26 M layer-pixels 495 against 680 us a step, 0.13 M 457
-// against 498, 0.06 M 463 against 445).
-constexpr int64_t kScatterMin = 16000000;
+// scatter is used; below, its five launches more cost more than the atomics.  A
+// training step launched call by call, C = 16, V = 4, us sorted against atomics: 4.1 M
+// floats 463 / 445, 8.3 M 457 / 498, 16.6 M 495 / 680; the adjoint alone, replayed from
+// a graph: C = 16, V = 2 / 4 / 8: 2.4 M 80 / 73, 73 / 82, 59 / 66 (2.1 M), 4.7 M 97 / 111,
+// 88 / 124, 88 / 132, 8.4 to 9.4 M 139 / 167, 109 / 201, 107 / 214; C = 8: 4.2 to 4.7 M
+// 112 / 136, 92 / 143, 93 / 144.  So the line lies between where whole steps and
+// where the kernels alone cross.
+constexpr int64_t kScatterMin = 6000000;
 
 bool supported_backward_c(int C) { return C == 8 || C == 16; }
 
@@ -1426,9 +1430,10 @@ qk_status qk_render_to_views(qk_context *ctx, void *hip_stream, int32_t V,
     qk::ViewsParams p;
     std::memset(&p, 0, sizeof(p));
     // The binned form holds all layers of a tile in 32 KiB of LDS (tiles of
-    // 32 x th pixels, 32 bytes per pixel and layer: th = 8 for L <= 4,
-    // halved as L doubles) and indexes records and view coordinates in 32
-    // and 16 bits; other calls take the planes form.
+    // 32 x th pixels, 32 bytes per pixel and layer: th = 32 for one layer, 8
+    // for three or four, 1 from 17 on; at one row 33 to 128 layers take more,
+    // up to 128 KiB) and indexes records and view coordinates in 32 and 16
+    // bits; other calls take the planes form.
     const int64_t nrec = (int64_t)V * ldm->L * ldm->H * ldm->W;
     bool small_views = true;
     for (int m = 0; m < V; ++m) small_views = small_views && views[m].W < 65535 && views[m].H < 65535;
