@@ -187,11 +187,12 @@ __device__ inline float rsq1(float x) {
     const float r = __builtin_amdgcn_rsqf(x);
     return fmaf(0.5f * r, fmaf(-x * r, r, 1.0f), r);
 }
-// sigma'(x) = sigma(x) sigma(-x) = e / (1 + e)^2 with e = e^-|x|: no
-// cancellation when sigma(x) is near one
+// sigma'(x) = sigma(x) sigma(-x): no cancellation when sigma(x) is near one.  (As e /
+// (1 + e)^2 with one exponential its error showed in dLoss/dF.)  Beyond 80, where
+// it is below 2e-35, held there: the estimates' step takes no infinity.
 __device__ inline float dsigm(float x) {
-    const float e = __expf(-fabsf(x)), r = rcp1(1.0f + e);
-    return e * r * r;
+    const float y = fabsf(x) > 80.0f ? 80.0f : x;
+    return rcp1(1.0f + __expf(-y)) * rcp1(1.0f + __expf(y));
 }
 
 constexpr int kTapOob = (int)0x80000000; // past any map under 2 GiB

@@ -39,3 +39,20 @@ def test_feature_gradient(ctx, C, V):
         err.append(np.linalg.norm(gpu["F"] - ref["F"]) / np.linalg.norm(ref["F"]))
     tb._say("precision", C, V, f"{np.median(err):.2e}")
     assert np.median(err) <= 1.5e-7
+
+
+@pytest.mark.parametrize("mode", ["residual", "paper"])
+@pytest.mark.parametrize("C", [8, 16])
+def test_saturated_heads(ctx, C, mode):
+    """Decode logits of a few hundred, where an exponential leaves float32: finite, and
+    within test_backward_gpu's bars."""
+    sc = synth.make_custom(V=3, H=40, W=56, C=C, L=4, seed=300 + C)
+    lvl = sc.levels[0]
+    for k in ("w_sigma", "W_color"):
+        lvl.weights[k] = (lvl.weights[k] * 150.0).astype(np.float32)
+    ups = tb._upstream(lvl, 2)
+    gpu = tb._run_backward(ctx, sc, lvl, mode=mode, **ups)
+    ref = tb._oracle(sc, lvl, ups, lib.MODE[mode])
+    for k in tb.NAMES:
+        assert np.all(np.isfinite(gpu[k])), k
+    tb._assert_close(tb._errors(gpu, ref), f"saturated C={C} {mode}")
