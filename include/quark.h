@@ -159,7 +159,7 @@ typedef struct qk_context qk_context;
  * workspaces that grow on demand and live until qk_context_destroy: the
  * folded weights of the one-to-many form (2 C C_feat floats per request),
  * the e4m3 scales (8 floats), the backward pass's scratch (16 bytes per
- * layer-pixel when d_rgb is given, plus 5 KiB per backward workgroup), the
+ * layer-pixel when d_rgb is given, plus 10 KiB per backward workgroup), the
  * render to input views' records (4 bytes per layer-pixel-view) or
  * projected planes, the low-resolution ray encodings, the residual block's
  * weight fragments and the batched launch's parameter table.  Growing one

@@ -1287,8 +1287,8 @@ qk_status qk_update_fuse_backward(qk_context *ctx, void *hip_stream, int32_t V,
     // persistent workgroups of four waves, 256 / C pixels of a layer each at a
     // time, as many as are resident together, or fewer for small LDMs
     const int64_t wave_pix = 256 / in->C;
-    const int64_t tiles = ((((int64_t)in->H * in->W + wave_pix - 1) / wave_pix) * in->L + 3) / 4;
-    p.blocks = (int32_t)std::max<int64_t>(1, std::min<int64_t>(tiles, qk::kBwdWaves * (int64_t)ctx->num_cu));
+    const int64_t items = (((int64_t)in->H * in->W + wave_pix - 1) / wave_pix) * in->L;
+    p.blocks = (int32_t)std::max<int64_t>(1, std::min<int64_t>((items + 3) / 4, qk::kBwdWaves * (int64_t)ctx->num_cu));
 
     int cur = -1;
     if (hipGetDevice(&cur) != hipSuccess) return fail(QK_EHIP, "hipGetDevice failed");
@@ -1311,9 +1311,10 @@ qk_status qk_update_fuse_backward(qk_context *ctx, void *hip_stream, int32_t V,
     const size_t n_sort = (size_t)records * in->C + (size_t)qk::scatter_bin_words(tiles_f, records);
     sorted = sorted && tiles_f < ((int64_t)1 << 28) && n_sort <= ((size_t)1 << 30);
     const size_t n_comp = d_rgb ? 4 * (size_t)p.N : 0;
-    const size_t n_part = (size_t)p.blocks * qk::kGradTiles * qk::kGradTileElems;   // for any number of views
+    const size_t n_part = 2 * (size_t)p.blocks * qk::kGradTiles * qk::kGradTileElems;   // for any number of views
     if (sorted && V <= qk::kBwdKeep)
         p.blocks = (int32_t)std::min<int64_t>(p.blocks, qk::kBwdWavesKeep * (int64_t)ctx->num_cu);
+    p.parts = items >= qk::kBwdHalve * 4 * (int64_t)p.blocks ? 2 : 1;
     st = grow(ctx, &ctx->bws, &ctx->bws_elems, n_comp + n_part, stream);
     if (st != QK_OK) return st;
     if (sorted && have_sorted(ctx, n_sort, stream)) {

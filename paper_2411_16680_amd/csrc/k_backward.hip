@@ -448,7 +448,8 @@ k_uf_backward(const BwdParams p) {
     const int nr = min(8, (int)gridDim.x), r = (int)blockIdx.x % nr;
     const int32_t item_end = (int32_t)((int64_t)items * (r + 1) / nr);
     const int32_t item_step = ((int)gridDim.x - r + nr - 1) / nr * kWaves;
-    const int32_t item0 = (int32_t)((int64_t)items * r / nr) + (int)blockIdx.x / nr * kWaves + wave;
+    const int32_t item_first = (int32_t)((int64_t)items * r / nr), item_half = item_first + (item_end - item_first) / 2;
+    const int32_t item0 = item_first + (int)blockIdx.x / nr * kWaves + wave;
     // the depth of this lane's pixel (load layout) of an item, read one item
     // ahead: the projections wait on it, and the taps on them
     auto item_depth = [&](int32_t item) {
@@ -456,7 +457,11 @@ k_uf_backward(const BwdParams p) {
         return p.depth_in[min(li * npix + q0 * PPT + lp, (li + 1) * npix - 1)];
     };
     float depth_next = item0 < item_end ? item_depth(item0) : 1.0f;
-    for (int32_t item = item0; item < item_end; item += item_step) {
+    int32_t item = item0;
+#pragma unroll 1
+    for (int part = 0; part < p.parts; ++part) {
+    const int32_t part_end = part + 1 < p.parts ? item_half : item_end;
+    for (; item < part_end; item += item_step) {
         const float depth_ld = depth_next;
         if (item + item_step < item_end) depth_next = item_depth(item + item_step);
         const int32_t q0 = (int32_t)fast_div((uint32_t)item, p.div_l), li = item - q0 * p.L;
@@ -811,26 +816,30 @@ k_uf_backward(const BwdParams p) {
         }
     }
 
-    // ---- workgroup partial of every weight-gradient tile.  The D layout of
-    //      a 16 x 16 tile: lane l holds column l % 16, rows 4 (l / 16) + i.
+    // ---- workgroup partial of every weight-gradient tile, where the items are many
+    //      after each half of them: a wave's sums are float, and their roundings
+    //      grow with their length.  The D layout of a 16 x 16 tile: lane l holds column l % 16, rows
+    //      4 (l / 16) + i.
     __syncthreads();
     float *red = &s_a[0][0];                            // kWaves x 256 floats used
-    const f32x4 *acc[kGradTiles] = {&gQ, &gK, &gV, &gO, &gH};
-    float *part = p.partials + (size_t)blockIdx.x * kGradTiles * kGradTileElems;
+    f32x4 *acc[kGradTiles] = {&gQ, &gK, &gV, &gO, &gH};
+    float *out = p.partials + ((size_t)blockIdx.x * p.parts + part) * kGradTiles * kGradTileElems;
 #pragma unroll
     for (int t = 0; t < kGradTiles; ++t) {
         const int col = lane & 15, row0 = 4 * (lane >> 4);
 #pragma unroll
         for (int i = 0; i < 4; ++i) red[wave * 256 + (row0 + i) * 16 + col] = (*acc[t])[i];
+        *acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
         __syncthreads();
         {
             const int idx = threadIdx.x;               // 256 entries, one per thread
             float s = 0.f;
 #pragma unroll
             for (int w = 0; w < kWaves; ++w) s += red[w * 256 + idx];
-            part[t * kGradTileElems + idx] = s;
+            out[t * kGradTileElems + idx] = s;
         }
         __syncthreads();
+    }
     }
 }
 
@@ -846,16 +855,17 @@ __global__ void __launch_bounds__(kBlock) k_reduce_wgrad(const BwdParams p) {
     // a wait: 739 partials took 15.2 us, now 5.7), added in order
     const float *at = p.partials + (size_t)t * kGradTileElems + rc;
     constexpr size_t kStep = (size_t)kGradTiles * kGradTileElems;
+    const int n = p.blocks * p.parts;
     double s = 0.0;
     int b = part;
-    for (; b + 7 * 16 < p.blocks; b += 8 * 16) {
+    for (; b + 7 * 16 < n; b += 8 * 16) {
         float v[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) v[i] = at[(b + 16 * i) * kStep];
 #pragma unroll
         for (int i = 0; i < 8; ++i) s += (double)v[i];
     }
-    for (; b < p.blocks; b += 16) s += (double)at[b * kStep];
+    for (; b < n; b += 16) s += (double)at[b * kStep];
     red[e16][part] = s;
     __syncthreads();
     if (part != 0) return;

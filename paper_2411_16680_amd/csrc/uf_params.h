@@ -109,6 +109,9 @@ constexpr int kGradTileElems = 256;
 // Workgroups per compute unit (waves per SIMD) of its persistent kernel: three,
 // or two where the taps of up to kBwdKeep views stay in registers.
 constexpr int kBwdKeep = 4, kBwdWaves = 3, kBwdWavesKeep = 2;
+// A workgroup writes its weight gradients' partial sums once, or from kBwdHalve items
+// a wave on after each half of its items (a part more takes 5 us).
+constexpr int kBwdHalve = 32;
 
 // Adjoint of one float32 Update & Fuse step (and of the composite).
 struct BwdParams {
@@ -133,6 +136,7 @@ struct BwdParams {
     int32_t V, L, H, W, C;
     int64_t N;          // L * H * W
     int32_t blocks;     // workgroups of the per-layer-pixel kernel
+    int32_t parts;      // partial sums of each
     FastDiv div_w, div_l;    // by W and by L
     int32_t wide;       // a feature map of 2 GiB or more
     float *ds;          // [V][N][C] sample gradients of the sorted scatter, or NULL (atomics)

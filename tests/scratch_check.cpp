@@ -197,6 +197,16 @@ int main() {
     CHECK(qk_context_destroy(ctx) == QK_OK);
     CHECK(g_live == 0);
 
+    // long sums of the weight gradients are written in two parts, whatever memory is
+    // left, and the workspace holds them for any number of views
+    CHECK(qk_context_create(0, 0, &ctx) == QK_OK);
+    CHECK(backward(ctx, V, 31) == QK_OK && g_bwd.parts == 1);      // 31 items a wave
+    CHECK(backward(ctx, V, 32) == QK_OK && g_bwd.parts == 2 && g_bwd.blocks == blocks);
+    CHECK(backward(ctx, V + 2, 47) == QK_OK && g_bwd.parts == 1);  // 768 workgroups
+    CHECK(backward(ctx, V + 2, 48) == QK_OK && g_bwd.parts == 2);
+    CHECK(g_bwd.comp - g_bwd.partials == (ptrdiff_t)2 * g_bwd.blocks * qk::kGradTiles * qk::kGradTileElems);
+    CHECK(qk_context_destroy(ctx) == QK_OK);
+
     // samples count up to 10^7 texels from a map's corner: the binning knows no such
     // limit, so larger maps take the atomics
     g_memory = (size_t)1 << 40;
