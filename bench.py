@@ -578,7 +578,7 @@ def time_ray(ctx, reps: int = 20):
     big = max(out["lowres"]["per_level"], key=lambda r: r["algorithmic_bytes_per_call"])
     out["roofline"] = {"bound": "hbm", "achieved": big["GB_s"], "peak": HBM_PEAK_GBS,
                        "unit": "GB/s", "frac": big["GB_s"] / HBM_PEAK_GBS,
-                       "kernel": f"k_ray_encoding<{big['C']}, low> + k_ray_upsample_add<{big['C']},bf16> "
+                       "kernel": f"{'k_ray_pixels' if big['C'] == 8 else 'k_ray_encoding'}<{big['C']}, low> + k_ray_upsample_add<{big['C']},bf16> "
                                  f"({big['grid']}, V=8, one call)",
                        "algorithmic_bytes_per_call": big["algorithmic_bytes_per_call"],
                        "avg_call_ms": big["avg_call_ms"],

@@ -513,7 +513,8 @@ QK_API qk_status qk_render_ibr_check(int32_t V, const qk_camera *in_cams, const 
  * Workspace, in the context (grown on demand like the others): up to 128
  * layers, one 4-byte record (the layer-pixel's index) per layer-pixel-view
  * whose footprint meets the view (at most V L H W words) plus 5 counters per
- * tile of 32 x th view pixels (th = 8 for L = 4, halved as L doubles);
+ * tile of 32 x th view pixels (th = 32 / L rounded down to a power of two, at
+ * least 1);
  * beyond, the projected planes, sum over views of L Hm Wm 4 floats.
  * Errors (nothing enqueued): QK_EINVAL (NULL or misaligned buffer, bad
  * camera), QK_ESHAPE (non-positive dims, V out of range), QK_EUNSUPPORTED

@@ -399,14 +399,14 @@ constexpr int kKeep = kBwdKeep;
 // What bounds it (960x540, L = 8, C = 16, V = 4, i.i.d. depths).  The float
 // atomics alone take 3.5 ms: they execute at the memory side, ~19 rows of C
 // floats per ns however they are grouped, so from kScatterMin on the gradients
-// go through the sort (0.65 ms, k_scatter.hip).  What is left was, with a pixel
-// per lane, 2.1 ms of 64-line gathers, LDS reads of the weights and 4700 vector
-// instructions per 64 pixels; quads of lanes per tap row, the products on the
-// matrix cores, 16 pixels at a time (few enough registers to keep the taps of
-// four views for the second pass, at two waves per SIMD) and one e^-|x| per
-// logistic leave 0.93 ms: latency at that occupancy (VALU 37 % busy; gathering
-// again at three waves per SIMD 1.10 ms, four waves spill).  The whole adjoint
-// 4.0 -> 1.75 ms.
+// go through the sort (0.69 ms with its binning, k_scatter.hip).  What is left
+// was, with a pixel per lane, 2.1 ms of 64-line gathers, LDS reads of the weights
+// and 4700 vector instructions per 64 pixels; quads of lanes per tap row, the
+// products on the matrix cores and 16 pixels at a time (few enough registers to
+// keep the taps of four views for the second pass, at two waves per SIMD) leave
+// 0.96 ms: the texture data path is busy 77 % of it, the vector units 45 and the
+// matrix cores 21, and two waves hide no more (gathering again at three 1.10 ms,
+// four waves spill).  The whole adjoint 4.0 -> 1.77 ms.
 template <int C, int MODE>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(MODE == kSortKeep ? kBwdWavesKeep : kBwdWaves)))
 k_uf_backward(const BwdParams p) {

@@ -26,10 +26,12 @@
 //
 // What bounds it: with the fragments in LDS every product read 1.5 operands and
 // the LDS pipe was busy throughout; now it is vector work (GELU, normalisation,
-// ~55 % busy) beside the matrix cores (~25 %).  16 layers of 480x270: 193 -> 134
-// us (570 TFLOP/s), the same bits.  The tile's height is chosen per call (launcher).  Both kernels' fragments in registers (144)
-// spilled and took 298 us; the next tile's input read ahead changed nothing, two
-// workgroups per CU overlap each other's staging.
+// 51 % busy) beside the matrix cores (24 %).  16 layers of 480x270: 193 -> 134 us
+// (570 TFLOP/s), the same bits.  The tile's height is chosen per call
+// (conv_tile_rows).  Both kernels' fragments in registers (144) spilled and took 298
+// us; the next tile's input read ahead changed nothing, two workgroups per CU overlap
+// each other's staging; eight waves on a tile where there is one per unit changed
+// nothing either.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>

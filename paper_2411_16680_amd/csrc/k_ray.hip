@@ -272,13 +272,12 @@ __device__ __forceinline__ void store_n(void *base, int64_t off, const float a[N
 // with C / 4 consecutive channels of its pixel (C = 8: 2, rows 2 and 3 of each
 // group empty).  A wave keeps the weights in registers over its pixels.
 //
-// The low-resolution grid of a 1080p pyramid (8 views, 240 x 135) took 24, 15
-// and 9 us at 32, 16 and 8 channels and 43 us added to its own map at 64, one
-// thread per pixel with the weights as LDS broadcasts or scalars (LDS reads
-// bound the first, few and long waves the rest); now 15, 12, 12 and 26.  The
-// chain of double operations, of which 4 waves per SIMD overlap, bounds it: held
-// to 80 registers for 6 waves it spills (33, 23, 28 us).  A frame's small grids
-// took 12 us a launch, now 5.
+// The low-resolution grid of a 1080p pyramid (8 views, 240 x 135) took 24 and 15 us
+// at 32 and 16 channels and 43 us added to its own map at 64, one thread per pixel
+// with the weights as LDS broadcasts or scalars (LDS reads bound the first, few
+// and long waves the rest); now 17, 12 and 25.  The chain of double operations, of
+// which 4 waves per SIMD overlap, bounds it: held to 80 registers for 6 waves it
+// spills (33, 23, 28 us).  A frame's small grids took 12 us a launch, now 5.
 template <int C, bool LOW, bool BF16>
 __global__ void __launch_bounds__(256) k_ray_encoding(const RayParams p) {
     constexpr int NB = C < 16 ? 1 : C / 16, NCH = C / 4;

@@ -14,18 +14,19 @@
 // maximum, rescaled sums).  Neither the weights nor the per-view samples are
 // stored.
 //
-// The vector unit bounds it: about 50 instructions per pixel, layer and view
-// and 140 more per pixel and layer, a third of them double (a position needs
+// The vector unit bounds it (71 % busy): about 50 instructions per pixel, layer and
+// view and 140 more per pixel and layer, a third of them double (a position needs
 // that: a disparity is worth up to ~1e3 px), at three waves per SIMD.  So the
 // layers share what does not depend on the disparity (A (u, v, 1), three
 // doubles a view in registers: without it 382 us against 311), the projection
 // takes positions from the image's centre on (one comparison per axis), a wave
 // inside the image masks nothing, and texels enter the blend as halves
-// (add_sample).  1080p from 512 x 288, 6 layers, under the profiler: 8 views
-// 402 us before, 296 now (355 and 267 to 287 without it); 5 views, which ran online,
-// 331 and 240.  Did not help: the logit taps in LDS (296; fewer loads, as many
-// more instructions), a layer's logits read ahead (305), 128 registers for a
-// fourth wave (305, spills), 64 x 4 and 32 x 8 tiles (294).
+// (add_sample).  1080p from 512 x 288, 6 layers, repeated: 8 views 382 us before,
+// 241 now; 5 views, which ran online, 321 and 217.  Did not help (under the profiler,
+// 296 us): the logit taps in LDS (296; fewer loads, as many more instructions), a
+// layer's logits read ahead (305), 128 registers for a fourth wave (305, spills), 64 x
+// 4 and 32 x 8 tiles (294); beyond 8 views a loop over groups of four (12 views 333
+// repeated, 361).
 #include <hip/hip_runtime.h>
 
 #include <cstdint>

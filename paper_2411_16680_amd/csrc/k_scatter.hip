@@ -53,7 +53,7 @@ struct Tile {
 // registers.  A record's row of ds is read one and a half times on average.  The
 // first batch of a tile writes its pixels and later ones add to them; ADD: other
 // workgroups add to the same pixels.
-// 16.6 M records of 64 bytes (960x540, L = 8, C = 16, V = 4): 0.48 ms, 2.2 TB/s
+// 16.6 M records of 64 bytes (960x540, L = 8, C = 16, V = 4): 0.50 ms, 2.1 TB/s
 // of rows, bound by the latency of the short lists (8 records a cell there).
 // Tiles are 4 rows high so that such a tile is one batch at six workgroups per
 // CU: 8 rows in two batches took 0.55 ms, in one batch of 2560 0.68 ms; with a

@@ -578,8 +578,8 @@ constexpr bool kReassoc = !BF16 && !FOLD && HD == C;
 
 // ROWS: rows of a workgroup, four waves each.  The reassociated form at C = 64
 // holds 68 KiB of weight fragments, so one workgroup fits a CU: eight waves
-// over two rows share them where that still leaves a workgroup per CU (two
-// waves per SIMD instead of one; 240x135, L = 32, V = 8: 1.16 -> 1.10 ms).
+// over two rows share them where that still leaves a workgroup to each of the
+// chip's 256 CUs (two waves per SIMD instead of one; 240x135, L = 32, V = 8: 1.16 -> 1.10 ms).
 // With one row a wave has the registers to keep the two extra products'
 // fragments in.
 template <bool BATCH>
@@ -1437,12 +1437,15 @@ struct UFLaunch {
 // to 3 times shorter.  A workgroup does a quarter of the work for the same
 // preparation of weights, so a level that fills the chip loses by it: the split
 // workgroups have to run at once (3 on a CU in bfloat16 and 2 in float32, 1 at
-// C = 64), or in two rounds from 7 layers on.  Measured with 4 views, split
+// C = 64, on the 256 CUs of the whole chip, which the rule takes as given),
+// or in two rounds from 7 layers on.  Measured with 4 views, split
 // workgroups and layers, us split against not: bfloat16, C = 32 folded: 576, 2:
 // 6.8 / 9.1; 1212, 2: 11.2 / 10.3, 5: 18 / 20, 7: 19 / 27, 12: 29 / 46; 3600, 7:
 // 47 / 42.  float32, C = 16: 288, 2: 9.9 / 13.2; 606, 2: 15.6 / 13.6, 5: 26 / 27, 7:
 // 27 / 36; 1080, 5: 40 / 36, 7: 43 / 48, 12: 60 / 78; 1800, 7: 62 / 60.  C = 64,
-// bfloat16: 96, 2: 10.7 / 14.9; 576, 2: 31 / 16, 12: 63 / 64.  A 64 x 48 level of 4
+// bfloat16: 96, 2: 10.7 / 14.9; 576, 2: 31 / 16, 12: 63 / 64.  C = 8, float32: 512, 2:
+// 15.5 / 20.0, 12: 40 / 96; 600, 2: 19.9 / 20.4, 5: 44 / 43, 7: 44 / 59; 800, 7: 53 / 62;
+// bfloat16: 600, 2: 9.6 / 13.7, 5: 17 / 28; 800, 2: 13.4 / 13.8, 7: 27 / 36.  A 64 x 48 level of 4
 // layers and 2 views (C = 16, float32): 13 / 22; 128 x 72, 24 layers, 8 views, 4
 // heads, bfloat16: 49 / 138 (138 with the slower preparation of weights too).
 template <int C, bool BF16>

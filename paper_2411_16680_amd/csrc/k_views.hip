@@ -341,8 +341,9 @@ __device__ inline unsigned long long vbin_fixed(float c) {
 // four workgroups fill a CU's wave slots (64 KiB tiles, with 6 % fewer
 // records read twice, ran at half the waves and 14 % longer; 256 or 1024
 // threads and two or four records at a time were slower too).  Eight 1080p
-// views of a 1080p LDM of 4 layers: 1.445 -> 0.76 ms, the whole call 2.34 ->
-// 1.17 ms, the counting and writing passes 0.36 -> 0.21 and 0.49 -> 0.25 ms.
+// views of a 1080p LDM of 4 layers, under the profiler: 1.43 -> 0.73 ms, the
+// counting and writing passes 0.37 -> 0.22 and 0.47 -> 0.26; the whole call 2.34 ->
+// 1.17 ms without it.
 // PL: the distance of the channels' planes where the tile fits it (the adds'
 // offsets are then immediates), 0: as the layers ask.
 template <int PL>
